@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "ecs_cube.h"
 #include "ecs_krylov.h"
 #include "ecsmg.h"
 
@@ -931,6 +932,13 @@ bool fused_vcycle(const ecs_ctx *C) {
          P.gamma_c == 1 && C->nlev > 1;
 }
 
+// The same cycle in 3D: one down and one up kernel per level as well.
+bool fused_vcycle3(const ecs_ctx *C) {
+  const ecs_prec_desc &P = C->prec;
+  return C->dim == 3 && P.smoother == ECS_SMOOTH_RBGS && P.nu1 == 1 && P.nu2 == 1 && P.gamma_f == 1 &&
+         P.gamma_c == 1 && C->nlev > 1;
+}
+
 // Which kernel runs each level of the fused cycle: levels from lt on run in
 // the single-workgroup tail; above it, pair_start[l] marks levels l, l+1 run
 // by one two-level kernel; every other level has its own down and up kernel.
@@ -1090,6 +1098,25 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
   }
 }
 
+template <typename R>
+void vcycle_fused3(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
+  const int lc = C->nlev - 1;
+  const R om = (R)C->prec.omega;
+  const CycleBufs<R> B = hierarchy_bufs<R>(C);
+  for (int l = 0; l < lc; l++) {
+    // reads b, k^2; writes the coarse residual
+    TimedScope ts(C, l == 0 ? kTDown : kTCoarse, (double)C->hl[l].nn * sizeof(R) * 3.25);
+    launch_down3_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), l == 0 ? b0 : B.b[l], B.b[l + 1], om, C->stream);
+  }
+  coarse_solve<R>(C, B.b[lc], B.u[lc]);
+  for (int l = lc - 1; l >= 0; l--) {
+    // reads the coarse correction, b, k^2; writes u
+    TimedScope ts(C, l == 0 ? kTUp : kTCoarse, (double)C->hl[l].nn * sizeof(R) * 5.25);
+    launch_up3_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), l == 0 ? b0 : B.b[l], B.u[l + 1], l == 0 ? u0 : B.u[l], om,
+                     C->stream);
+  }
+}
+
 void drop_graphs(ecs_ctx *C) {
   for (auto &g : C->graphs) (void)hipGraphExecDestroy(g.exec);
   C->graphs.clear();
@@ -1121,7 +1148,7 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   for (int k : {kTSmooth, kTCoarse, kTRestrict, kTProlong, kTDown, kTUp, kTDownP, kTDownS})
     if (C->timers[k].on) return false;
   if (C->graph_mode == ECS_GRAPHS_NEVER || C->no_alloc) return false;
-  if (fused_vcycle(C)) {
+  if (fused_vcycle(C) || fused_vcycle3(C)) {
     if (C->graph_mode == ECS_GRAPHS_AUTO) return false;
   } else if (cycle_launches(C, 0, C->prec.gamma_f, C->prec.gamma_c, 4096) >= 4096) {
     return false;
@@ -1138,6 +1165,7 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   hipStream_t user = C->stream;
   C->stream = C->capture;
   if (fused_vcycle(C)) vcycle_fused<R>(C, b0, u0);
+  else if (fused_vcycle3(C)) vcycle_fused3<R>(C, b0, u0);
   else mg<R>(C, 0, b0, u0, C->prec.gamma_f, C->prec.gamma_c, true);
   C->stream = user;
   hipGraph_t graph = nullptr;
@@ -1253,6 +1281,7 @@ void vcycle(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   if (!fused_vcycle(C)) ensure_sched(C);
   if (vcycle_graph<R>(C, b0, u0)) return;
   if (fused_vcycle(C)) vcycle_fused<R>(C, b0, u0);
+  else if (fused_vcycle3(C)) vcycle_fused3<R>(C, b0, u0);
   else mg<R>(C, 0, b0, u0, C->prec.gamma_f, C->prec.gamma_c, true);
 }
 
