@@ -322,7 +322,8 @@ ecs_status ecs_timing_calibrate(ecs_ctx *ctx, int launches);
 
 /* Launch schedule of the fused 2D V(1,1) red-black cycle.  It chooses which
  * kind of kernel runs each level (one level per kernel, two levels per
- * kernel, the single-workgroup tail) and their tile heights; the method's
+ * kernel, the dense map of the coarse end, the FP32 single-workgroup tail) and
+ * their tile heights; the method's
  * arithmetic is the same under every schedule, but kernels of different kinds
  * order some floating-point operations differently, so the cycle's result
  * can change at the level of rounding (in FP32 enough to move a nested
@@ -332,11 +333,12 @@ ecs_status ecs_timing_calibrate(ecs_ctx *ctx, int launches);
  *   up_rows     fine rows per block of the fused prolongation/post-smoothing
  *               kernel on grids above small_grid: 4, 8, 10, 12, 16 or 32
  *   small_grid  grids with at most this many nodes per axis use 2 / 4 rows
- *   tail_nodes  levels with at most this many nodes per axis run in the
- *               single-workgroup kernel that ends the cycle: 3..65; above 33
- *               it applies to FP32 cycles only (their wide tail holds up to
- *               5696 nodes, e.g. 65^2 down to a 9^2 coarsest), FP64 cycles
- *               and general cycles use min(tail_nodes, 33)
+ *   tail_nodes  the levels with at most this many nodes per axis end the cycle
+ *               as one dense map, built at set-up: 3..65.  Above 33, FP32
+ *               cycles run those levels in a single-workgroup kernel instead
+ *               (up to 5696 nodes, e.g. 65^2 down to a 9^2 coarsest), FP64
+ *               cycles use 33.  General 2D cycles take the map from the finest
+ *               level of at most 41 nodes per axis when tail_nodes >= 33
  *   pair_grid   levels above the tail with at most this many nodes per axis
  *               run two per kernel (pairs counted from the tail up); 0: none
  *   fuse_updates  1: the FP32 Bi-CGSTAB inside FGMRES (desc->inner > 0), and

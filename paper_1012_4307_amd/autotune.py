@@ -2,7 +2,8 @@
 
 It times the cycle under every candidate schedule -- tile heights of the
 fused down / up kernels, the grid size below which short tiles are used, the
-size below which levels run in the single-workgroup tail kernel, and the
+size below which levels end the cycle as one dense map (above 33, FP32: in the
+single-workgroup tail kernel), and the
 size below which levels run two per kernel -- and keeps the fastest.  Two
 objectives:
 

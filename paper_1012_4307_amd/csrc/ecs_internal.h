@@ -192,9 +192,6 @@ void launch_prolong_to(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R>
 template <typename R>
 void launch_prolong_jacobi(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *ec, const cplx<R> *b,
                            const cplx<R> *u, cplx<R> *out, R omega, hipStream_t s);
-template <typename R>
-void launch_coarse_solve(int nunk, const cplx<R> *minv, const int *unk, int n0, int n1, int n2, const cplx<R> *b,
-                         cplx<R> *x, hipStream_t s, const RhsSet &rs = one_rhs());
 // fused V(1,1) red-black kernels (2D): zero-guess pre-sweep + residual + FW
 // (the pre-smoothed iterate is not stored), and the pre-sweep recomputed from
 // b + prolongation + correction + post-sweep into u_out
@@ -233,72 +230,31 @@ template <typename R>
 void launch_up2_rb(const Grid<R> &f, const Grid<R> &m, const Grid<R> &c, const cplx<R> *b_f, const cplx<R> *t_f,
                    const cplx<R> *b_m, const cplx<R> *t_m, const cplx<R> *ec, cplx<R> *u_out, R omega,
                    hipStream_t s, const RhsSet &rs = one_rhs());
-// the coarsest levels of a 2D V(1,1) red-black cycle in one workgroup, every
-// level vector resident in LDS: levels with at most kTailNodes nodes per axis,
-// at least two of them (the last is the coarsest, solved densely), kTailCap
-// nodes in all
+// the coarsest levels of a 2D V(1,1) red-black cycle in FP32 in one workgroup,
+// every level vector resident in LDS (an option of the schedule): levels of up
+// to kTailWideNodes nodes per axis, at least two of them (the last is the
+// coarsest, solved densely), kTailWideCap nodes in all (a 65^2 level down to a
+// 9^2 coarsest: 5684), at most kTailWideWeights 1D weights per axis
 constexpr int kTailMaxLevels = 8;
-constexpr int kTailNodes = 33;
-constexpr int kTailCap = 1536;
-constexpr int kTailMinv = 2401;  // coarsest inverse entries staged in LDS (49 unknowns)
-// FP32 cycles also have a wide tail: levels of up to kTailWideNodes nodes per
-// axis, kTailWideCap nodes in all (a 65^2 level down to a 9^2 coarsest: 5684),
-// with at most kTailWideWeights 1D weights per axis over its levels
+constexpr int kTailNodes = 33;  // levels up to this size end the cycle as a dense map
 constexpr int kTailWideNodes = 65;
 constexpr int kTailWideCap = 5696;
 constexpr int kTailWideWeights = 132;
-template <typename R>
 struct TailArgs {
   int nl;                            // levels in the tail, the last one the coarsest
   int noff[kTailMaxLevels + 1];      // node offsets of the levels in the LDS vectors
   int poff[kTailMaxLevels + 1];      // the same, each level padded to a multiple of 64 nodes
   int woff[kTailMaxLevels + 1];      // offsets of the levels' 1D weights
-  Grid<R> g[kTailMaxLevels];
-  const cplx<R> *b0;                 // right-hand side of the tail's first level
-  cplx<R> *u0;                       // its result
-  const cplx<R> *minvT;              // coarsest inverse, transposed
+  Grid<float> g[kTailMaxLevels];
+  const cplx<float> *b0;             // right-hand side of the tail's first level
+  cplx<float> *u0;                   // its result
+  const cplx<float> *minv;           // coarsest inverse
   int nunk;                          // interior nodes of the coarsest level, row-major
   int tpr;                           // threads per row of the dense solve (power of 2, <= 64)
-  R omega;
+  float omega;
 };
-template <typename R>
-void launch_tail(const TailArgs<R> &a, hipStream_t s, const RhsSet &rs = one_rhs());
+void launch_tail_wide(const TailArgs &a, hipStream_t s, const RhsSet &rs = one_rhs());
 
-// The coarse end of a general cycle (any gamma_f, gamma_c, nu1, nu2,
-// omega-Jacobi or red-black) in one workgroup, driven by a schedule that the
-// host unrolls from Algorithm 1.  One 32-bit word per operation:
-//   bits 0-3 code, 4-7 level k (0 = the tail's first level), 8 zero guess,
-//   9 f0, 10 f1 (buffer / colour selectors, per code):
-//   kSchedJacobi  u[f1] <- one omega-Jacobi sweep of u[f0] (zero guess: of 0)
-//   kSchedRB      one colour f1 of a red-black sweep, in place on u[f0]
-//   kSchedResid   b_{k+1} <- FW (b_k - M_k u[f0]_k)   (uses u[!f0]_k as scratch)
-//   kSchedCoarse  u[f0]_k <- M_k^{-1} b_k              (k: the coarsest level)
-//   kSchedProlong u[f0]_k += P u[f1]_{k+1}
-//   kSchedZero    u[f0]_k <- 0
-//   kSchedEnd     the tail's result is u[f0]_0
-enum : uint32_t { kSchedEnd = 0, kSchedJacobi = 1, kSchedRB = 2, kSchedResid = 3, kSchedCoarse = 4,
-                  kSchedProlong = 5, kSchedZero = 6 };
-constexpr int kSchedPack = kTailCap + 512;  // packed weights + inverse diagonals of the tail levels
-constexpr int kSchedProgCap = 4096;         // operations per schedule
-template <typename R>
-struct SchedArgs {
-  int nl;                             // levels in the tail, the last one the coarsest
-  int noff[kTailMaxLevels + 1];       // node offsets of the levels in the LDS vectors
-  int pko[kTailMaxLevels + 1];        // offsets of the levels in the pack
-  int n0[kTailMaxLevels], n1[kTailMaxLevels];
-  const cplx<R> *pack;                // per level: alpha a-, alpha a+ (x), the same (y), 1 / diag(M)
-  int pack_len;
-  const cplx<R> *minvT;               // coarsest inverse, transposed
-  int nunk, tpr;                      // coarsest interior nodes; threads per row of the dense solve
-  const cplx<R> *b_in;                // right-hand side of the first level
-  const cplx<R> *u_in;                // its initial iterate, or null for a zero guess
-  cplx<R> *u_out;                     // its result (may alias u_in)
-  const uint32_t *prog;
-  int prog_len;
-  R omega;
-};
-template <typename R>
-void launch_sched_tail(const SchedArgs<R> &a, hipStream_t s);
 template <typename R>
 void launch_inject_k2(int n0, int n1, int n2, const double *k2_fine, int f0, int f1, R *k2_coarse, hipStream_t s);
 

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "ecs_cube.h"
+#include "ecs_dense.h"
 #include "ecs_krylov.h"
 #include "ecsmg.h"
 
@@ -143,9 +144,15 @@ struct ecs_ctx {
   cplx<float> *Acm32[3] = {}, *Acp32[3] = {};  // FP32 copy of A's weights (nested form)
   DevLevel<double> L64[kMaxLev];
   DevLevel<float> L32[kMaxLev];
-  cplx<double> *minv64 = nullptr;
-  cplx<float> *minv32 = nullptr;
-  int *unk = nullptr;
+  // the coarse end of the cycle as dense maps (kernels_dense.hip), per level
+  // dtop .. coarsest in FP64: dA for a parent level visited with (gamma_f,
+  // gamma_c), dB for one visited with the two exchanged (the same map when they
+  // are equal); dA[coarsest] is the coarsest inverse.  FP32 cycles: copies of the
+  // coarsest inverse and of the maps of level d32_l, the one in use
+  cplx<double> *dA[kMaxLev] = {}, *dB[kMaxLev] = {};
+  cplx<float> *minv32 = nullptr, *dA32 = nullptr, *dB32 = nullptr;
+  int dtop = 0, d32_l = -1;
+  size_t host_bytes = 0;  // what set-up uploads: the first bytes of the workspace
   int nunk = 0;
   cplx<double> *partials = nullptr;
   double *dscal = nullptr;  // misc device scalars (max k^2 ...)
@@ -181,19 +188,7 @@ struct ecs_ctx {
   // the current direction (reset at every restart)
   int bicg_pflip = 0;
 
-  // coarse end of the general cycle in one workgroup (2D): packed weights and
-  // inverse diagonals of the levels that may form it (levels sfirst .. coarsest,
-  // level l at spko[l] - spko[sfirst]), and the schedules unrolled from
-  // Algorithm 1 for the loaded key (tail level, gamma_f, gamma_c, nu1, nu2,
-  // smoother); variants: (gf, gc) or (gc, gf), each from zero or from a guess
-  cplx<double> *spack64 = nullptr;
-  cplx<float> *spack32 = nullptr;
-  int sfirst = -1;
-  int spko[kMaxLev + 1] = {};
-  uint32_t *sprog = nullptr;
-  int sprog_len[4] = {};
-  int skey[6] = {-2, 0, 0, 0, 0, 0};
-  int gt_l = -1;  // first level of the tail in use, -1: none
+  int gt_l = -1;  // general cycle: first level of the dense end in use
 };
 
 namespace {
@@ -273,9 +268,39 @@ void build_host_levels(ecs_ctx *C) {
 }
 
 // ------------------------------------------------------ workspace plan
+int unknowns(const ecs_ctx *C, int l) {
+  int n = 1;
+  for (int a = 0; a < C->dim; a++) n *= C->hl[l].n[a] - 2;
+  return n;
+}
+
+bool fused_vcycle(const ecs_ctx *C);
+
+// Finest level whose part of the cycle can be a dense map: as far up as maps
+// and their construction fit.  A map costs its bytes, the launches of the levels
+// it replaces cost a few microseconds each, so general cycles, which visit a
+// coarse level up to a dozen times with three launches a visit, take it up to 41^2
+// (37 MB in FP64); the fused 2D cycle, one down and one up kernel a level (two
+// levels a kernel up to 129^2), up to 33^2.
+int dense_top(const ecs_ctx *C) {
+  const int lc = C->nlev - 1;
+  if (C->prec.kind == ECS_PREC_NONE) return lc;
+  const int most = fused_vcycle(C) ? kTailNodes : kDenseNodes;
+  int l = lc;
+  while (l > 0 && C->hl[l - 1].n[0] <= most && unknowns(C, l - 1) <= kDenseMax && C->hl[l - 1].nn <= kDenseNodes &&
+         C->hl[l].nn <= kDenseCoarse)
+    l--;
+  return l;
+}
+
 size_t plan_layout(ecs_ctx *C, Carver &cv) {
   const bool f32 = C->prec.vcycle_dtype == ECS_F32;
-  C->k2_wide = C->k2_dtype == ECS_F32 ? cv.take<double>(C->hl[0].nn) : nullptr;
+  const int lc = C->nlev - 1;
+  C->nunk = unknowns(C, lc);
+  C->dtop = dense_top(C);
+  auto map_size = [&](int l) { return (size_t)unknowns(C, l) * dense_ld(unknowns(C, l)); };
+  // first what the host computes, one region that set-up uploads in one copy:
+  // the weights and the coarsest inverse
   for (int a = 0; a < C->dim; a++) {
     C->Acm[a] = cv.take<cplx<double>>(C->hl[0].n[a]);
     C->Acp[a] = cv.take<cplx<double>>(C->hl[0].n[a]);
@@ -284,19 +309,23 @@ size_t plan_layout(ecs_ctx *C, Carver &cv) {
       C->Acm32[a] = cv.take<cplx<float>>(C->hl[0].n[a]);
       C->Acp32[a] = cv.take<cplx<float>>(C->hl[0].n[a]);
     }
+    for (int l = 0; l < C->nlev; l++) {
+      C->L64[l].cm[a] = cv.take<cplx<double>>(C->hl[l].n[a]);
+      C->L64[l].cp[a] = cv.take<cplx<double>>(C->hl[l].n[a]);
+      if (f32) {
+        C->L32[l].cm[a] = cv.take<cplx<float>>(C->hl[l].n[a]);
+        C->L32[l].cp[a] = cv.take<cplx<float>>(C->hl[l].n[a]);
+      }
+    }
   }
+  C->dA[lc] = C->dB[lc] = cv.take<cplx<double>>(map_size(lc));
+  if (f32) C->minv32 = cv.take<cplx<float>>(map_size(lc));
+  C->host_bytes = cv.off;
+  C->k2_wide = C->k2_dtype == ECS_F32 ? cv.take<double>(C->hl[0].nn) : nullptr;
   for (int l = 0; l < C->nlev; l++) {
     const HostLevel &L = C->hl[l];
     DevLevel<double> &D = C->L64[l];
     DevLevel<float> &S = C->L32[l];
-    for (int a = 0; a < C->dim; a++) {
-      D.cm[a] = cv.take<cplx<double>>(L.n[a]);
-      D.cp[a] = cv.take<cplx<double>>(L.n[a]);
-      if (f32) {
-        S.cm[a] = cv.take<cplx<float>>(L.n[a]);
-        S.cp[a] = cv.take<cplx<float>>(L.n[a]);
-      }
-    }
     D.k2 = (l == 0) ? nullptr : cv.take<double>(L.nn);
     if (f32) S.k2 = cv.take<float>(L.nn);
     if (!f32) {
@@ -309,16 +338,15 @@ size_t plan_layout(ecs_ctx *C, Carver &cv) {
       S.t = cv.take<cplx<float>>(L.nn);
     }
   }
-  const HostLevel &Lc = C->hl[C->nlev - 1];
-  int nunk = 1;
-  for (int a = 0; a < C->dim; a++) nunk *= (Lc.n[a] - 2);
-  C->nunk = nunk;
-  C->minv64 = cv.take<cplx<double>>((size_t)nunk * nunk);
-  if (f32) C->minv32 = cv.take<cplx<float>>((size_t)nunk * nunk);
-  C->unk = cv.take<int>(nunk);
-  C->spack64 = cv.take<cplx<double>>(kSchedPack);
-  if (f32) C->spack32 = cv.take<cplx<float>>(kSchedPack);
-  C->sprog = cv.take<uint32_t>(4 * kSchedProgCap);
+  const bool two = C->prec.gamma_f != C->prec.gamma_c;
+  for (int l = C->dtop; l < lc; l++) {
+    C->dA[l] = cv.take<cplx<double>>(map_size(l));
+    C->dB[l] = two && l > 0 ? cv.take<cplx<double>>(map_size(l)) : C->dA[l];
+  }
+  if (f32 && C->dtop < lc) {
+    C->dA32 = cv.take<cplx<float>>(map_size(C->dtop));
+    C->dB32 = two ? cv.take<cplx<float>>(map_size(C->dtop)) : C->dA32;
+  }
   C->partials = cv.take<cplx<double>>((size_t)kRedBlocks * (2 * kMaxRestart + 2));
   C->dscal = cv.take<double>(kRedBlocks + 8);
   C->gs = cv.take<GmresScalars>(1);
@@ -558,20 +586,48 @@ DevLevel<double> &dev_level<double>(ecs_ctx *C, int l) { return C->L64[l]; }
 template <>
 DevLevel<float> &dev_level<float>(ecs_ctx *C, int l) { return C->L32[l]; }
 
+// the dense map of level l (the coarsest inverse on the coarsest); FP32: copies
+// of the level chosen last by use_dense
 template <typename R>
-const cplx<R> *minv_of(const ecs_ctx *C);
+const cplx<R> *dense_map(const ecs_ctx *C, int l, bool swapped);
 template <>
-const cplx<double> *minv_of<double>(const ecs_ctx *C) { return C->minv64; }
+const cplx<double> *dense_map<double>(const ecs_ctx *C, int l, bool swapped) {
+  return swapped ? C->dB[l] : C->dA[l];
+}
 template <>
-const cplx<float> *minv_of<float>(const ecs_ctx *C) { return C->minv32; }
+const cplx<float> *dense_map<float>(const ecs_ctx *C, int l, bool swapped) {
+  if (l == C->nlev - 1) return C->minv32;
+  return swapped ? C->dB32 : C->dA32;
+}
+
+// u_l = (map of level l) b_l
+template <typename R>
+void dense_apply(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, bool swapped = false,
+                 const RhsSet &rs = one_rhs()) {
+  const HostLevel &L = C->hl[l];
+  launch_dense<R>(dense_map<R>(C, l, swapped), unknowns(C, l), L.n[0], L.n[1], L.n[2], b, u, C->stream, rs);
+}
+
+// FP32 cycles: the maps of level l in FP32 (outside any capture)
+void use_dense(ecs_ctx *C, int l) {
+  if (C->prec.vcycle_dtype != ECS_F32 || l >= C->nlev - 1 || l < C->dtop || C->d32_l == l) return;
+  const int N = unknowns(C, l);
+  const int64_t size = (int64_t)N * dense_ld(N);
+  launch_cast<double, float>(C->dA[l], C->dA32, size, C->stream);
+  if (C->dB[l] != C->dA[l]) launch_cast<double, float>(C->dB[l], C->dB32, size, C->stream);
+  C->d32_l = l;
+}
+
+int general_dense_level(const ecs_ctx *C);
+int fused_dense_level(const ecs_ctx *C);
 
 // ---------------------------------------------------------- setup
+// scale * src, as it will lie in the workspace at dst, into the host's copy of
+// the workspace's first bytes
 template <typename R>
-ecs_status upload_cx(ecs_ctx *C, cplx<R> *dst, const std::vector<cd> &src, cd scale) {
-  std::vector<cplx<R>> h(src.size());
+void stage_cx(ecs_ctx *C, std::vector<char> &host, cplx<R> *dst, const std::vector<cd> &src, cd scale) {
+  cplx<R> *h = reinterpret_cast<cplx<R> *>(host.data() + (reinterpret_cast<char *>(dst) - C->ws));
   for (size_t i = 0; i < src.size(); i++) h[i] = tocx<R>(scale * src[i]);
-  HIP_OK(hipMemcpy(dst, h.data(), h.size() * sizeof(cplx<R>), hipMemcpyHostToDevice));
-  return ECS_OK;
 }
 
 // Gauss-Jordan inverse with partial pivoting (FP64) of a dense complex matrix
@@ -647,25 +703,24 @@ ecs_status setup(ecs_ctx *C) {
   }
   // weights
   const HostLevel &F = C->hl[0];
+  std::vector<char> host(C->host_bytes);
   for (int a = 0; a < C->dim; a++) {
-    ecs_status st;
-    if ((st = upload_cx<double>(C, C->Acm[a], F.am[a], 1.0)) != ECS_OK) return st;
-    if ((st = upload_cx<double>(C, C->Acp[a], F.ap[a], 1.0)) != ECS_OK) return st;
-    if ((st = upload_cx<double>(C, C->Wd[a], F.w[a], 1.0)) != ECS_OK) return st;
+    stage_cx<double>(C, host, C->Acm[a], F.am[a], 1.0);
+    stage_cx<double>(C, host, C->Acp[a], F.ap[a], 1.0);
+    stage_cx<double>(C, host, C->Wd[a], F.w[a], 1.0);
     if (f32) {
-      if ((st = upload_cx<float>(C, C->Acm32[a], F.am[a], 1.0)) != ECS_OK) return st;
-      if ((st = upload_cx<float>(C, C->Acp32[a], F.ap[a], 1.0)) != ECS_OK) return st;
+      stage_cx<float>(C, host, C->Acm32[a], F.am[a], 1.0);
+      stage_cx<float>(C, host, C->Acp32[a], F.ap[a], 1.0);
     }
   }
   for (int l = 0; l < C->nlev; l++) {
     const HostLevel &L = C->hl[l];
     for (int a = 0; a < C->dim; a++) {
-      ecs_status st;
-      if ((st = upload_cx<double>(C, C->L64[l].cm[a], L.am[a], C->alpha)) != ECS_OK) return st;
-      if ((st = upload_cx<double>(C, C->L64[l].cp[a], L.ap[a], C->alpha)) != ECS_OK) return st;
+      stage_cx<double>(C, host, C->L64[l].cm[a], L.am[a], C->alpha);
+      stage_cx<double>(C, host, C->L64[l].cp[a], L.ap[a], C->alpha);
       if (f32) {
-        if ((st = upload_cx<float>(C, C->L32[l].cm[a], L.am[a], C->alpha)) != ECS_OK) return st;
-        if ((st = upload_cx<float>(C, C->L32[l].cp[a], L.ap[a], C->alpha)) != ECS_OK) return st;
+        stage_cx<float>(C, host, C->L32[l].cm[a], L.am[a], C->alpha);
+        stage_cx<float>(C, host, C->L32[l].cp[a], L.ap[a], C->alpha);
       }
     }
     // k^2 on level l: injection from the finest grid (rediscretisation, Sec. 4.2)
@@ -711,60 +766,44 @@ ecs_status setup(ecs_ctx *C) {
   }
   if (!invert(M, nu)) return fail(C, ECS_EINVAL, "coarsest preconditioner matrix is singular");
   {
-    // the solve kernel reads the inverse column by column (transposed layout)
-    std::vector<cd> MT((size_t)nu * nu);
+    const int ld = dense_ld(nu);
+    std::vector<cd> G((size_t)nu * ld, 0.0);
     for (int r = 0; r < nu; r++)
-      for (int q = 0; q < nu; q++) MT[(size_t)q * nu + r] = M[(size_t)r * nu + q];
-    ecs_status st;
-    if ((st = upload_cx<double>(C, C->minv64, MT, 1.0)) != ECS_OK) return st;
-    if (f32 && (st = upload_cx<float>(C, C->minv32, MT, 1.0)) != ECS_OK) return st;
+      for (int q = 0; q < nu; q++) G[(size_t)r * ld + q] = M[(size_t)r * nu + q];
+    stage_cx<double>(C, host, C->dA[lc], G, 1.0);
+    if (f32) stage_cx<float>(C, host, C->minv32, G, 1.0);
   }
-  HIP_OK(hipMemcpy(C->unk, unk.data(), nu * sizeof(int), hipMemcpyHostToDevice));
-  // pack of the levels that may form the one-workgroup tail of a general cycle
-  C->sfirst = -1;
-  C->gt_l = -1;
-  C->skey[0] = -2;
-  if (C->dim == 2 && C->nlev >= 2) {
-    auto plen = [&](int l) { return 2 * C->hl[l].n[0] + 2 * C->hl[l].n[1] + (int)C->hl[l].nn; };
-    int first = lc;
-    int64_t nodes = Lc.nn;
-    int len = plen(lc);
-    while (first > 0 && C->hl[first - 1].n[0] <= kTailNodes && C->hl[first - 1].n[1] <= kTailNodes &&
-           lc - (first - 1) + 1 <= kTailMaxLevels && nodes + C->hl[first - 1].nn <= kTailCap &&
-           len + plen(first - 1) <= kSchedPack) {
-      first--;
-      nodes += C->hl[first].nn;
-      len += plen(first);
-    }
-    if (first < lc) {
-      std::vector<cd> pack;
-      pack.reserve(len);
-      for (int l = first; l <= lc; l++) {
-        const HostLevel &L = C->hl[l];
-        C->spko[l] = (int)pack.size();
-        std::vector<double> k2l(L.nn);
-        const double *src = l == 0 ? C->k2 : C->L64[l].k2;
-        HIP_OK(hipMemcpyAsync(k2l.data(), src, L.nn * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_OK(hipStreamSynchronize(s));
-        for (int a = 0; a < 2; a++) {
-          for (int i = 0; i < L.n[a]; i++) pack.push_back(C->alpha * L.am[a][i]);
-          for (int i = 0; i < L.n[a]; i++) pack.push_back(C->alpha * L.ap[a][i]);
-        }
-        for (int j = 0; j < L.n[1]; j++)
-          for (int i = 0; i < L.n[0]; i++) {
-            const bool in = i >= 1 && i <= L.n[0] - 2 && j >= 1 && j <= L.n[1] - 2;
-            const cd dg = C->alpha * (L.am[0][i] + L.ap[0][i] + L.am[1][j] + L.ap[1][j]) +
-                          C->beta * k2l[(size_t)j * L.n[0] + i] + C->c;
-            pack.push_back(in ? 1.0 / dg : cd(0.0));
-          }
-      }
-      C->spko[lc + 1] = (int)pack.size();
-      ecs_status st;
-      if ((st = upload_cx<double>(C, C->spack64, pack, 1.0)) != ECS_OK) return st;
-      if (f32 && (st = upload_cx<float>(C, C->spack32, pack, 1.0)) != ECS_OK) return st;
-      C->sfirst = first;
+  // one copy (a copy per array cost about 10 us each, 50 and more of them); the
+  // host's memory outlives it: set-up ends with a wait for the stream
+  HIP_OK(hipMemcpyAsync(C->ws, host.data(), C->host_bytes, hipMemcpyHostToDevice, s));
+  // the levels above it whose part of the cycle is a dense map: from the
+  // coarsest up, the visits of Algorithm 1 to level l under a parent visited with
+  // (gf, gc): a first cycle (gf, gc), then gc - 1 cycles (gc, gf)
+  C->d32_l = -1;
+  for (int l = lc - 1; l >= C->dtop; l--) {
+    const HostLevel &Lx = C->hl[l + 1];
+    DenseGen g{};
+    g.f = grid_M<double>(C, l);
+    g.c0 = Lx.n[0];
+    g.c1 = Lx.n[1];
+    g.c2 = Lx.n[2];
+    g.nu1 = P.nu1;
+    g.nu2 = P.nu2;
+    g.red_black = P.smoother == ECS_SMOOTH_RBGS;
+    g.omega = P.omega;
+    g.X1 = C->dA[l + 1];
+    g.X2 = C->dB[l + 1];
+    g.reps = l == 0 ? 1 : P.gamma_c;  // the finest level is visited once
+    g.G = C->dA[l];
+    launch_dense_gen(g, s);
+    if (C->dB[l] != C->dA[l]) {
+      std::swap(g.X1, g.X2);
+      g.reps = P.gamma_f;
+      g.G = C->dB[l];
+      launch_dense_gen(g, s);
     }
   }
+  use_dense(C, fused_vcycle(C) ? fused_dense_level(C) : general_dense_level(C));
   // Krylov scalars start cleared
   HIP_OK(hipMemsetAsync(C->gs, 0, sizeof(GmresScalars), s));
   HIP_OK(hipMemsetAsync(C->bs, 0, kMaxRhs * sizeof(BicgScalars), s));
@@ -796,12 +835,6 @@ void smooth(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, cplx<R> *t, int nsw
   if (nsweeps == 0 && zero_guess) launch_zero<R>(u, nn, C->stream);
 }
 
-template <typename R>
-void coarse_solve(ecs_ctx *C, const cplx<R> *b, cplx<R> *x) {
-  const HostLevel &L = C->hl[C->nlev - 1];
-  launch_coarse_solve<R>(C->nunk, minv_of<R>(C), C->unk, L.n[0], L.n[1], L.n[2], b, x, C->stream);
-}
-
 // omega-Jacobi sweeps of Algorithm 1 on level l, alternating out of place
 // between the iterate's buffer `cur` and `oth` (no copies); returns the
 // buffer that holds the result
@@ -820,61 +853,16 @@ cplx<R> *jacobi_sweeps(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *cur, cplx<R
   return cur;
 }
 
-template <typename R>
-const cplx<R> *spack_of(const ecs_ctx *C);
-template <>
-const cplx<double> *spack_of<double>(const ecs_ctx *C) { return C->spack64; }
-template <>
-const cplx<float> *spack_of<float>(const ecs_ctx *C) { return C->spack32; }
-
-// Algorithm 1 from tail level l to the coarsest in one launch, following the
-// schedule unrolled for (gf, gc) and the guess
-template <typename R>
-void sched_tail(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, bool zero_guess) {
-  const ecs_prec_desc &P = C->prec;
-  const int lc = C->nlev - 1;
-  SchedArgs<R> a{};
-  a.nl = lc - l + 1;
-  const int base = C->spko[l];
-  for (int k = 0; k < a.nl; k++) {
-    const HostLevel &L = C->hl[l + k];
-    a.n0[k] = L.n[0];
-    a.n1[k] = L.n[1];
-    a.noff[k + 1] = a.noff[k] + (int)L.nn;
-    a.pko[k] = C->spko[l + k] - base;
-  }
-  a.pko[a.nl] = C->spko[lc + 1] - base;
-  a.pack = spack_of<R>(C) + base;
-  a.pack_len = a.pko[a.nl];
-  a.minvT = minv_of<R>(C);
-  a.nunk = C->nunk;
-  a.tpr = 64;
-  while (a.tpr > 1 && a.tpr * C->nunk > 1024) a.tpr >>= 1;
-  a.b_in = b;
-  a.u_in = zero_guess ? nullptr : u;
-  a.u_out = u;
-  const int v = ((gf == P.gamma_f && gc == P.gamma_c) ? 0 : 2) + (zero_guess ? 0 : 1);
-  a.prog = C->sprog + (size_t)v * kSchedProgCap;
-  a.prog_len = C->sprog_len[v];
-  a.omega = (R)P.omega;
-  TimedScope ts(C, kTCoarse, 0.0);
-  launch_sched_tail<R>(a, C->stream);
-}
-
 // Algorithm 1: u <- MG(l, M_l, b, u, nu1, nu2, C, gf, gc).  zero_guess: u == 0
-// on entry (u's contents are not read and need not be cleared).  From the
-// tail level on (2D, small levels) the rest of the recursion runs in one
-// launch; above it each step is a launch, omega-Jacobi alternating between u
-// and the level scratch t.
+// on entry (u's contents are not read and need not be cleared).  From level
+// gt_l on the rest of the recursion, with the repeated visits, is one dense map;
+// above it each step is a launch, omega-Jacobi alternating between u and the
+// level scratch t.
 template <typename R>
 void mg(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, bool zero_guess) {
-  const int lc = C->nlev - 1;
-  if (l == lc) {
-    coarse_solve<R>(C, b, u);
-    return;
-  }
-  if (l == C->gt_l) {
-    sched_tail<R>(C, l, b, u, gf, gc, zero_guess);
+  if (l == C->gt_l) {  // the finest level itself
+    TimedScope ts(C, kTCoarse, 0.0);
+    dense_apply<R>(C, l, b, u);
     return;
   }
   DevLevel<R> &D = dev_level<R>(C, l);
@@ -889,8 +877,9 @@ void mg(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, bool ze
     TimedScope ts(C, l == 0 ? kTRestrict : kTCoarse, (double)C->hl[l].nn * sizeof(R) * per);
     launch_residual_restrict<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), b, cur, Dc.b, C->stream);
   }
-  if (l + 1 == lc) {
-    coarse_solve<R>(C, Dc.b, Dc.u);
+  if (l + 1 == C->gt_l) {
+    TimedScope ts(C, kTCoarse, 0.0);
+    dense_apply<R>(C, l + 1, Dc.b, Dc.u, gf != C->prec.gamma_f || gc != C->prec.gamma_c);
   } else {
     for (int i = 1; i <= gc; i++) {
       if (i == 1) mg<R>(C, l + 1, Dc.b, Dc.u, gf, gc, true);
@@ -939,11 +928,13 @@ bool fused_vcycle3(const ecs_ctx *C) {
          P.gamma_c == 1 && C->nlev > 1;
 }
 
-// Which kernel runs each level of the fused cycle: levels from lt on run in
-// the single-workgroup tail; above it, pair_start[l] marks levels l, l+1 run
-// by one two-level kernel; every other level has its own down and up kernel.
+// Which kernel runs each level of the fused cycle: the levels from lt on are one
+// dense map (wide: the FP32 single-workgroup tail); above it, pair_start[l]
+// marks levels l, l+1 run by one two-level kernel; every other level has its
+// own down and up kernel.
 struct FusedPlan {
   int lt;
+  bool wide;
   bool pair_start[kMaxLev + 1];
 };
 
@@ -951,19 +942,22 @@ FusedPlan fused_plan(const ecs_ctx *C) {
   const int lc = C->nlev - 1;
   const ecs_tuning &T = C->tune;
   FusedPlan P{};
-  // first level handled by the tail: the coarsest levels that are small
-  // (FP32 cycles: up to 65 nodes per axis in the wide tail; FP64: up to 33)
-  const bool wide = C->prec.vcycle_dtype == ECS_F32;
-  const int tn = wide ? T.tail_nodes : std::min(T.tail_nodes, kTailNodes);
-  const int64_t cap = wide ? kTailWideCap : kTailCap;
   int lt = lc;
-  int64_t tail_nn = C->hl[lc].nn, tail_w = std::max(C->hl[lc].n[0], C->hl[lc].n[1]);
-  while (lt > 0 && C->hl[lt - 1].n[0] <= tn && C->hl[lt - 1].n[1] <= tn && lc - (lt - 1) + 1 <= kTailMaxLevels &&
-         tail_nn + C->hl[lt - 1].nn <= cap &&
-         tail_w + std::max(C->hl[lt - 1].n[0], C->hl[lt - 1].n[1]) <= (wide ? kTailWideWeights : 128)) {
-    lt--;
-    tail_nn += C->hl[lt].nn;
-    tail_w += std::max(C->hl[lt].n[0], C->hl[lt].n[1]);
+  if (C->prec.vcycle_dtype == ECS_F32 && T.tail_nodes > kTailNodes) {
+    int64_t tail_nn = C->hl[lc].nn, tail_w = std::max(C->hl[lc].n[0], C->hl[lc].n[1]);
+    while (lt > 0 && C->hl[lt - 1].n[0] <= T.tail_nodes && C->hl[lt - 1].n[1] <= T.tail_nodes &&
+           lc - (lt - 1) + 1 <= kTailMaxLevels && tail_nn + C->hl[lt - 1].nn <= kTailWideCap &&
+           tail_w + std::max(C->hl[lt - 1].n[0], C->hl[lt - 1].n[1]) <= kTailWideWeights) {
+      lt--;
+      tail_nn += C->hl[lt].nn;
+      tail_w += std::max(C->hl[lt].n[0], C->hl[lt].n[1]);
+    }
+    P.wide = lt < lc && (C->hl[lt].n[0] > kTailNodes || C->hl[lt].n[1] > kTailNodes);
+  }
+  if (!P.wide) {
+    const int tn = std::min(T.tail_nodes, kTailNodes);
+    lt = lc;
+    while (lt > C->dtop && C->hl[lt - 1].n[0] <= tn && C->hl[lt - 1].n[1] <= tn) lt--;
   }
   P.lt = lt;
   // the levels above the tail with at most pair_grid nodes per axis run two
@@ -972,6 +966,11 @@ FusedPlan fused_plan(const ecs_ctx *C) {
   while (ls > 0 && C->hl[ls - 1].n[0] <= T.pair_grid && C->hl[ls - 1].n[1] <= T.pair_grid) ls--;
   for (int l = lt - 2; l >= ls; l -= 2) P.pair_start[l] = true;
   return P;
+}
+
+int fused_dense_level(const ecs_ctx *C) {
+  const FusedPlan P = fused_plan(C);
+  return P.wide ? C->nlev - 1 : P.lt;
 }
 
 // A Bi-CGSTAB (the nested FP32 one, or the outer one with the FP64 cycle) can
@@ -1047,33 +1046,34 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
                       C->stream, rs);
     l++;
   }
-  if (lt == lc) {
-    // no small levels above the coarsest: dense solve only
-    const cplx<R> *b = lc == 0 ? b0 : B.b[lc];
-    cplx<R> *u = lc == 0 ? u0 : B.u[lc];
-    TimedScope ts(C, kTCoarse, 0.0);
-    const HostLevel &L = C->hl[lc];
-    launch_coarse_solve<R>(C->nunk, minv_of<R>(C), C->unk, L.n[0], L.n[1], L.n[2], b, u, C->stream, rs);
-  } else {
-    TailArgs<R> a{};
-    a.nl = lc - lt + 1;
-    a.noff[0] = a.woff[0] = a.poff[0] = 0;
-    for (int k = 0; k < a.nl; k++) {
-      const int l = lt + k;
-      a.g[k] = grid_M<R>(C, l);
-      a.noff[k + 1] = a.noff[k] + (int)C->hl[l].nn;
-      a.poff[k + 1] = a.poff[k] + ((int)C->hl[l].nn + 63) / 64 * 64;
-      a.woff[k + 1] = a.woff[k] + (int)std::max(C->hl[l].n[0], C->hl[l].n[1]);
+  bool wide = false;
+  if constexpr (sizeof(R) == 4) {
+    wide = plan.wide;
+    if (wide) {
+      TailArgs a{};
+      a.nl = lc - lt + 1;
+      a.noff[0] = a.woff[0] = a.poff[0] = 0;
+      for (int k = 0; k < a.nl; k++) {
+        const int l = lt + k;
+        a.g[k] = grid_M<float>(C, l);
+        a.noff[k + 1] = a.noff[k] + (int)C->hl[l].nn;
+        a.poff[k + 1] = a.poff[k] + ((int)C->hl[l].nn + 63) / 64 * 64;
+        a.woff[k + 1] = a.woff[k] + (int)std::max(C->hl[l].n[0], C->hl[l].n[1]);
+      }
+      a.b0 = lt == 0 ? b0 : B.b[lt];
+      a.u0 = lt == 0 ? u0 : B.u[lt];
+      a.minv = C->minv32;
+      a.nunk = C->nunk;
+      a.tpr = 64;
+      while (a.tpr > 1 && a.tpr * C->nunk > 1024) a.tpr >>= 1;
+      a.omega = om;
+      TimedScope ts(C, kTCoarse, 0.0);
+      launch_tail_wide(a, C->stream, rs);
     }
-    a.b0 = lt == 0 ? b0 : B.b[lt];
-    a.u0 = lt == 0 ? u0 : B.u[lt];
-    a.minvT = minv_of<R>(C);
-    a.nunk = C->nunk;
-    a.tpr = 64;
-    while (a.tpr > 1 && a.tpr * C->nunk > 1024) a.tpr >>= 1;
-    a.omega = om;
+  }
+  if (!wide) {
     TimedScope ts(C, kTCoarse, 0.0);
-    launch_tail<R>(a, C->stream, rs);
+    dense_apply<R>(C, lt, lt == 0 ? b0 : B.b[lt], lt == 0 ? u0 : B.u[lt], false, rs);
   }
   for (int l = lt - 1; l >= 0;) {
     if (l >= 1 && pair_start[l - 1]) {
@@ -1100,16 +1100,19 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
 
 template <typename R>
 void vcycle_fused3(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
-  const int lc = C->nlev - 1;
+  const int lt = C->dtop;
   const R om = (R)C->prec.omega;
   const CycleBufs<R> B = hierarchy_bufs<R>(C);
-  for (int l = 0; l < lc; l++) {
+  for (int l = 0; l < lt; l++) {
     // reads b, k^2; writes the coarse residual
     TimedScope ts(C, l == 0 ? kTDown : kTCoarse, (double)C->hl[l].nn * sizeof(R) * 3.25);
     launch_down3_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), l == 0 ? b0 : B.b[l], B.b[l + 1], om, C->stream);
   }
-  coarse_solve<R>(C, B.b[lc], B.u[lc]);
-  for (int l = lc - 1; l >= 0; l--) {
+  {
+    TimedScope ts(C, kTCoarse, 0.0);
+    dense_apply<R>(C, lt, lt == 0 ? b0 : B.b[lt], lt == 0 ? u0 : B.u[lt]);
+  }
+  for (int l = lt - 1; l >= 0; l--) {
     // reads the coarse correction, b, k^2; writes u
     TimedScope ts(C, l == 0 ? kTUp : kTCoarse, (double)C->hl[l].nn * sizeof(R) * 5.25);
     launch_up3_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), l == 0 ? b0 : B.b[l], B.u[l + 1], l == 0 ? u0 : B.u[l], om,
@@ -1125,10 +1128,9 @@ void drop_graphs(ecs_ctx *C) {
 // launches of one general cycle (capped): cycles with very many coarse
 // visits (large gamma over many levels) are not captured
 int64_t cycle_launches(const ecs_ctx *C, int l, int gf, int gc, int64_t cap) {
-  const int lc = C->nlev - 1;
-  if (l == lc || l == C->gt_l) return 1;
+  if (l == C->gt_l) return 1;
   int64_t n = C->prec.nu1 + C->prec.nu2 + 2;
-  if (l + 1 == lc) return n + 1;
+  if (l + 1 == C->gt_l) return n + 1;
   for (int i = 1; i <= gc && n < cap; i++)
     n += i == 1 ? cycle_launches(C, l + 1, gf, gc, cap) : cycle_launches(C, l + 1, gc, gf, cap);
   return n;
@@ -1178,107 +1180,23 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   return hipGraphLaunch(exec, C->stream) == hipSuccess;
 }
 
-// Unrolls Algorithm 1 from tail level k (0 = the tail's first level) into the
-// operations of k_sched_tail, tracking which of the two LDS buffers of each
-// level holds its iterate (omega-Jacobi alternates; red-black stays in place).
-struct SchedGen {
-  const ecs_prec_desc *P;
-  int nl;
-  int cur[kTailMaxLevels] = {};
-  std::vector<uint32_t> ops;
-  bool overflow = false;
-
-  void emit(uint32_t code, int k, bool zg, int f0, int f1) {
-    if (ops.size() >= (size_t)kSchedProgCap) {
-      overflow = true;
-      return;
-    }
-    ops.push_back(code | (uint32_t)k << 4 | (uint32_t)zg << 8 | (uint32_t)f0 << 9 | (uint32_t)f1 << 10);
-  }
-  void smooth(int k, int nsweeps, bool zero_guess) {
-    for (int q = 0; q < nsweeps; q++) {
-      const bool zg = zero_guess && q == 0;
-      if (P->smoother == ECS_SMOOTH_JACOBI) {
-        emit(kSchedJacobi, k, zg, cur[k], cur[k] ^ 1);
-        cur[k] ^= 1;
-      } else {
-        emit(kSchedRB, k, zg, cur[k], 0);
-        emit(kSchedRB, k, false, cur[k], 1);
-      }
-    }
-    if (nsweeps == 0 && zero_guess) emit(kSchedZero, k, false, cur[k], 0);
-  }
-  void cycle(int k, int gf, int gc, bool zero_guess) {
-    const int last = nl - 1;
-    if (overflow) return;
-    if (k == last) {
-      emit(kSchedCoarse, k, false, cur[k], 0);
-      return;
-    }
-    smooth(k, P->nu1, zero_guess);
-    emit(kSchedResid, k, false, cur[k], 0);
-    if (k + 1 == last) {
-      emit(kSchedCoarse, k + 1, false, cur[k + 1], 0);
-    } else {
-      for (int i = 1; i <= gc && !overflow; i++) {
-        if (i == 1) cycle(k + 1, gf, gc, true);
-        else cycle(k + 1, gc, gf, false);
-      }
-    }
-    emit(kSchedProlong, k, false, cur[k], cur[k + 1]);
-    smooth(k, P->nu2, false);
-  }
-};
-
-// Loads the schedules of the general cycle's tail for the current set-up
-// (outside any capture: it may copy to the device and drops the graphs that
-// replay older schedules).
-void ensure_sched(ecs_ctx *C) {
-  const ecs_prec_desc &P = C->prec;
-  const int lc = C->nlev - 1;
-  int lt = -1;
-  if (C->sfirst >= 0) {
-    lt = lc;
-    const int tn = std::min(C->tune.tail_nodes, kTailNodes);  // the schedule tail holds up to 33^2 levels
-    while (lt - 1 >= C->sfirst && C->hl[lt - 1].n[0] <= tn && C->hl[lt - 1].n[1] <= tn)
-      lt--;
-    if (lt == lc) lt = -1;
-  }
-  const int key[6] = {lt, P.gamma_f, P.gamma_c, P.nu1, P.nu2, P.smoother};
-  if (std::memcmp(key, C->skey, sizeof key) == 0) return;
-  std::memcpy(C->skey, key, sizeof key);
-  C->gt_l = -1;
-  drop_graphs(C);
-  if (lt < 0) return;
-  std::vector<uint32_t> progs[4];
-  for (int v = 0; v < 4; v++) {
-    SchedGen G;
-    G.P = &P;
-    G.nl = lc - lt + 1;
-    const bool swap = v >= 2;
-    G.cycle(0, swap ? P.gamma_c : P.gamma_f, swap ? P.gamma_f : P.gamma_c, (v & 1) == 0);
-    G.emit(kSchedEnd, 0, false, G.cur[0], 0);
-    if (G.overflow) return;  // too long: the per-level launches stay in use
-    progs[v].swap(G.ops);
-  }
-  for (int v = 0; v < 4; v++) {
-    if (hipMemcpyAsync(C->sprog + (size_t)v * kSchedProgCap, progs[v].data(), progs[v].size() * sizeof(uint32_t),
-                       hipMemcpyHostToDevice, C->stream) != hipSuccess)
-      return;
-    C->sprog_len[v] = (int)progs[v].size();
-  }
-  if (hipStreamSynchronize(C->stream) != hipSuccess) return;
-  C->gt_l = lt;
+// First level of a general cycle's dense end: dtop, or the first level below it
+// that a smaller ecs_tuning.tail_nodes allows (2D).
+int general_dense_level(const ecs_ctx *C) {
+  int l = C->nlev - 1;
+  const int tn = C->tune.tail_nodes;
+  while (l > C->dtop && (C->dim == 3 || tn >= kTailNodes || (C->hl[l - 1].n[0] <= tn && C->hl[l - 1].n[1] <= tn))) l--;
+  return l;
 }
 
 // z = M^{-1} v approximately: one cycle from zero on the finest level
 template <typename R>
 void vcycle(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   if (C->nlev == 1) {
-    coarse_solve<R>(C, b0, u0);
+    dense_apply<R>(C, 0, b0, u0);
     return;
   }
-  if (!fused_vcycle(C)) ensure_sched(C);
+  if (!fused_vcycle(C)) C->gt_l = general_dense_level(C);
   if (vcycle_graph<R>(C, b0, u0)) return;
   if (fused_vcycle(C)) vcycle_fused<R>(C, b0, u0);
   else if (fused_vcycle3(C)) vcycle_fused3<R>(C, b0, u0);
@@ -2589,9 +2507,10 @@ ecs_status ecs_coarse_solve(ecs_ctx *C, const void *b, void *x) {
   if (st != ECS_OK) return st;
   if (!b || !x) return fail(C, ECS_EINVAL, "null argument");
   if (C->prec.vcycle_dtype == ECS_F64)
-    coarse_solve<double>(C, reinterpret_cast<const cplx<double> *>(b), reinterpret_cast<cplx<double> *>(x));
+    dense_apply<double>(C, C->nlev - 1, reinterpret_cast<const cplx<double> *>(b),
+                        reinterpret_cast<cplx<double> *>(x));
   else
-    coarse_solve<float>(C, reinterpret_cast<const cplx<float> *>(b), reinterpret_cast<cplx<float> *>(x));
+    dense_apply<float>(C, C->nlev - 1, reinterpret_cast<const cplx<float> *>(b), reinterpret_cast<cplx<float> *>(x));
   HIP_OK(hipGetLastError());
   return ECS_OK;
 }
@@ -2718,6 +2637,7 @@ ecs_status ecs_set_tuning(ecs_ctx *C, const ecs_tuning *t) {
   if (t->fuse_updates != 0 && t->fuse_updates != 1) return fail(C, ECS_EINVAL, "fuse_updates must be 0 or 1");
   C->tune = *t;
   drop_graphs(C);
+  if (C->ready) use_dense(C, fused_vcycle(C) ? fused_dense_level(C) : general_dense_level(C));
   return ECS_OK;
 }
 

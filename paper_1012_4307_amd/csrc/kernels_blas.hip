@@ -705,11 +705,18 @@ __global__ __launch_bounds__(BS) void k_max_partial(const double *__restrict__ x
     partials[blockIdx.x] = r;
   }
 }
-__global__ void k_max_final(const double *partials, int nb, double *out) {
-  if (threadIdx.x != 0) return;
+// one block: a thread's share of the partials, then a tree in LDS (one thread
+// walking 2048 partials took 115 us)
+__global__ __launch_bounds__(BS) void k_max_final(const double *partials, int nb, double *out) {
+  __shared__ double lds[BS];
   double r = -INFINITY;
-  for (int q = 0; q < nb; q++) r = fmax(r, partials[q]);
-  *out = r;
+  for (int q = threadIdx.x; q < nb; q += BS) r = fmax(r, partials[q]);
+  lds[threadIdx.x] = r;
+  for (int h = BS / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if ((int)threadIdx.x < h) lds[threadIdx.x] = fmax(lds[threadIdx.x], lds[threadIdx.x + h]);
+  }
+  if (threadIdx.x == 0) *out = lds[0];
 }
 __global__ __launch_bounds__(BS) void k_copy16(const uint4 *__restrict__ src, uint4 *__restrict__ dst, int64_t n) {
   for (int64_t p = (int64_t)blockIdx.x * BS + threadIdx.x; p < n; p += (int64_t)gridDim.x * BS) dst[p] = src[p];
@@ -902,7 +909,7 @@ void launch_grad_k2(const cplx<double> *lam, const cplx<double> *u, double *g, i
 void launch_max_real(const double *x, int64_t n, double *partials, double *out, hipStream_t s) {
   int nb = red_blocks(n);
   launch_k(k_max_partial, dim3(nb), dim3(BS), 0, s, x, n, partials);
-  launch_k(k_max_final, dim3(1), dim3(1), 0, s, partials, nb, out);
+  launch_k(k_max_final, dim3(1), dim3(BS), 0, s, partials, nb, out);
 }
 void launch_empty(hipStream_t s) { launch_k(k_empty, dim3(1), dim3(64), 0, s); }
 

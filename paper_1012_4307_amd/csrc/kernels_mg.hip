@@ -2,7 +2,7 @@
 // (bin Zubair, Reps, Vanroose, Sec. 3.2 operator, Sec. 4.2 components):
 // stencil apply, residual, omega-Jacobi and red-black SOR sweeps, full-weighting
 // restriction (fused with the residual), bilinear/trilinear prolongation with
-// correction, dense coarsest solve, k^2 injection.
+// correction, k^2 injection.
 //
 // Layout: node-major, x fastest, interleaved complex.  Every kernel maps one
 // thread to one node of a (64 x 4) tile of an x-y plane; the z plane (3D) is
@@ -312,39 +312,6 @@ __global__ __launch_bounds__(256) void k_prolong_jacobi(Grid<R> f, Grid<R> c, co
   out[p] = v + omega * cdiv(res, d);
 }
 
-// x = M_C^{-1} b on the coarsest level from the precomputed dense inverse,
-// stored transposed (minvT[c * nunk + r] = Minv[r][c]) so that the threads of
-// a wave read consecutive entries; b's unknowns are first staged in LDS.
-// Thread t writes the t-th unknown and, if node t is a boundary node, its zero.
-// One block of 1024 threads (nunk <= 2048 unknowns).
-template <typename R, bool MR>
-__global__ __launch_bounds__(1024) void k_coarse_solve(int nunk, const cplx<R> *__restrict__ minvT,
-                                                       const int *__restrict__ unk, int n0, int n1, int n2,
-                                                       const cplx<R> *__restrict__ b, cplx<R> *__restrict__ x,
-                                                       RhsSet rs) {
-  __shared__ cplx<R> sb[2048];
-  const int nn = n0 * n1 * n2;
-  if constexpr (MR) {
-    const int64_t q = rhs_index(rs) * rhs_stride(nn);  // one block per right-hand side
-    b += q;
-    x += q;
-  }
-  for (int t = threadIdx.x; t < nunk; t += blockDim.x) sb[t] = b[unk[t]];
-  for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-    const int i = t % n0, j = (t / n0) % n1, k = t / (n0 * n1);
-    const bool zin = n2 == 1 || (k >= 1 && k <= n2 - 2);
-    const bool interior = i >= 1 && i <= n0 - 2 && j >= 1 && j <= n1 - 2 && zin;
-    if (!interior) x[t] = mk<R>(0, 0);
-  }
-  __syncthreads();
-  for (int r = threadIdx.x; r < nunk; r += blockDim.x) {
-    cplx<R> acc = mk<R>(0, 0);
-#pragma unroll 8
-    for (int c = 0; c < nunk; c++) acc = acc + minvT[(int64_t)c * nunk + r] * sb[c];
-    x[unk[r]] = acc;
-  }
-}
-
 // y = M x with a fused dot product for Bi-CGSTAB (grid-stride over 64 x 4
 // tiles; one thread per node):
 //   kBicgAlpha: sum conj(d0) y  -> alpha = rho / (r^, v)
@@ -565,14 +532,6 @@ void launch_prolong_jacobi(const Grid<R> &fine, const Grid<R> &coarse, const cpl
                            const cplx<R> *u, cplx<R> *out, R omega, hipStream_t s) {
   launch_k((k_prolong_jacobi<R>), grid_of(fine), dim3(TX, TY), 0, s, fine, coarse, ec, b, u, out, omega);
 }
-template <typename R>
-void launch_coarse_solve(int nunk, const cplx<R> *minv, const int *unk, int n0, int n1, int n2, const cplx<R> *b,
-                         cplx<R> *x, hipStream_t s, const RhsSet &rs) {
-  if (multi_rhs(rs))
-    launch_k((k_coarse_solve<R, true>), dim3(1, rs.count), dim3(1024), 0, s, nunk, minv, unk, n0, n1, n2, b, x, rs);
-  else
-    launch_k((k_coarse_solve<R, false>), dim3(1), dim3(1024), 0, s, nunk, minv, unk, n0, n1, n2, b, x, rs);
-}
 template <typename R, typename RI>
 void launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
                       cplx<double> *partials, BicgScalars *S, hipStream_t s, const RhsSet &rs) {
@@ -625,8 +584,6 @@ void launch_inject_k2(int n0, int n1, int n2, const double *k2_fine, int f0, int
                                          const cplx<R> *, cplx<R> *, R, hipStream_t);                           \
   template void launch_prolong_to<R>(const Grid<R> &, const Grid<R> &, const cplx<R> *, const cplx<R> *,         \
                                      cplx<R> *, hipStream_t);                                                   \
-  template void launch_coarse_solve<R>(int, const cplx<R> *, const int *, int, int, int, const cplx<R> *,      \
-                                       cplx<R> *, hipStream_t, const RhsSet &);                                 \
   template void launch_inject_k2<R>(int, int, int, const double *, int, int, R *, hipStream_t);
 
 ECS_INST_MG(double)

@@ -16,6 +16,7 @@
 // recomputed redundantly from a halo staged in LDS, so tiles are independent
 // and no grid-wide synchronisation is needed.  Rows are loaded with
 // consecutive lanes on consecutive x (unit stride, interleaved complex).
+#include "ecs_dense.h"
 #include "ecs_internal.h"
 #include "ecs_krylov.h"
 
@@ -462,36 +463,22 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
 }
 
 // ----------------------------------------------------------------- tail
-// The coarsest levels of the cycle in one workgroup: for grids of a few
-// thousand nodes a launch per level costs more than the work, so the down
-// passes, the dense coarsest solve and the up passes of every level from the
-// tail's first level to the coarsest run in one launch, phases separated by
-// workgroup barriers.  Every level vector of the tail lives in LDS (at most
-// kTailCap nodes over all tail levels): global memory is touched once at the
-// start (the first level's right-hand side, the 1D weights and k^2 of all
-// levels) and once at the end (the first level's result).
-// Per level k (nodes [noff[k], noff[k+1]) of the LDS vectors):
-//   b  right-hand side (the restricted residual of the level above)
-//   t  pre-smoothed iterate
-//   w  residual on the way down, corrected and post-smoothed iterate on the way up
-//   d  inverse diagonal
+// The coarsest levels of an FP32 cycle in one workgroup (an option of the
+// schedule; by default the coarse end is a dense map): the down passes, the
+// dense coarsest solve and the up passes of every level from the tail's first
+// to the coarsest in one launch, phases separated by workgroup barriers, every
+// level vector in LDS.  Global memory is touched once at the start and once at
+// the end.
 constexpr int TT = 1024;  // tail threads
-constexpr int TW = 128;   // LDS weights per axis and kind (>= sum of the tail level sizes)
-
-template <typename R>
-struct TailLds {
-  cplx<R> xm[TW + 1], xp[TW + 1], ym[TW + 1], yp[TW + 1];  // + a spare slot
-  cplx<R> b[kTailCap], t[kTailCap], w[kTailCap], d[kTailCap];
-  cplx<R> mi[kTailMinv + 1];  // the coarsest inverse (transposed) when it fits, and a spare slot
-};
 
 // rows of the dense coarsest solve: tpr lanes per row, partial sums combined
 // across the row's lanes; the interior unknowns are the interior nodes in
 // row-major order.  The node of unknown c (interior row c / ni, column
 // c % ni) comes from a float reciprocal, not an integer division: exact here
 // (c < 1024, so the product stays more than 0.5 / ni away from an integer).
-template <typename R, typename M>
-__device__ __forceinline__ void tail_dense(int nu, int tpr, const M *mi, const cplx<R> *b, cplx<R> *x, int n0) {
+template <typename R>
+__device__ __forceinline__ void tail_dense(int nu, int tpr, const cplx<R> *mi, int ld, const cplx<R> *b, cplx<R> *x,
+                                           int n0) {
   const int tid = threadIdx.x, ni = n0 - 2, rows_per_pass = TT / tpr;
   const float inv = 1.0f / (float)ni;
   auto node = [&](int c) {
@@ -503,7 +490,7 @@ __device__ __forceinline__ void tail_dense(int nu, int tpr, const M *mi, const c
     cplx<R> acc = zero_c<R>();
     if (rr < nu) {
 #pragma unroll 4
-      for (int c = tid % tpr; c < nu; c += tpr) acc = acc + mi[(int64_t)c * nu + rr] * b[node(c)];
+      for (int c = tid % tpr; c < nu; c += tpr) acc = acc + mi[(int64_t)rr * ld + c] * b[node(c)];
     }
     for (int m = tpr >> 1; m >= 1; m >>= 1) {
       acc.re += __shfl_xor(acc.re, m, 64);
@@ -513,221 +500,13 @@ __device__ __forceinline__ void tail_dense(int nu, int tpr, const M *mi, const c
   }
 }
 
-template <typename R, bool MR>
-__global__ __launch_bounds__(TT) void k_tail(TailArgs<R> a, RhsSet rs) {
-  __shared__ TailLds<R> S;
-  const int tid = threadIdx.x;
-  // one workgroup per right-hand side (the kernel argument block is not written)
-  const int64_t rq = MR ? rhs_index(rs) * rhs_stride((int64_t)a.g[0].n0 * a.g[0].n1) : 0;
-  const cplx<R> *const b0 = a.b0 + rq;
-  cplx<R> *const u0 = a.u0 + rq;
-  const R om = a.omega, om1 = R(1) - a.omega;
-  const int last = a.nl - 1;
-  const bool minv_lds = a.nunk * a.nunk <= kTailMinv;
-
-  // setup, one memory round trip: the 1D weights of every level into LDS, the
-  // inverse diagonal of every node of every level, the first level's
-  // right-hand side and its zero-guess red relaxation, the coarsest inverse.
-  // Waves never straddle levels (per-level ranges padded to 64 lanes), so a
-  // wave's level is uniform and the kernel arguments are indexed uniformly.
-  // Loads use clamped (always valid) indexes and are issued before any use.
-  {
-    constexpr int kSlots = (kTailCap + kTailMaxLevels * 63 + TT - 1) / TT;
-    // weights: wave k (k < nl) loads level k's, lane = node index
-    const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool wl = kw < a.nl;
-    const Grid<R> &gw = a.g[wl ? kw : 0];
-    const int ln = tid & 63;
-    const int q0 = ln < gw.n0 ? ln : gw.n0 - 1, q1 = ln < gw.n1 ? ln : gw.n1 - 1;
-    const cplx<R> wxm = gw.cm0[q0], wxp = gw.cp0[q0], wym = gw.cm1[q1], wyp = gw.cp1[q1];
-    // nodes: slot sl of thread tid is padded index P = tid + sl TT
-    cplx<R> cxm[kSlots], cxp[kSlots], cym[kSlots], cyp[kSlots], bv[kSlots];
-    R kv[kSlots];
-    int lv[kSlots], pv[kSlots];
-#pragma unroll
-    for (int sl = 0; sl < kSlots; sl++) {
-      const int P = tid + sl * TT;
-      int k = 0;
-      for (int q = 1; q < a.nl; q++) k = P >= a.poff[q] ? q : k;
-      k = __builtin_amdgcn_readfirstlane(k);
-      const Grid<R> &g = a.g[k];
-      const int nn = g.n0 * g.n1;
-      const int p0 = P - a.poff[k], p = p0 < nn ? p0 : nn - 1;
-      // row from a float reciprocal (exact: p < kTailCap)
-      const int j = (int)(((float)p + 0.5f) * (1.0f / (float)g.n0)), i = p - j * g.n0;
-      lv[sl] = P < a.poff[a.nl] && p0 < nn ? k : -1;
-      pv[sl] = p;
-      cxm[sl] = g.cm0[i];
-      cxp[sl] = g.cp0[i];
-      cym[sl] = g.cm1[j];
-      cyp[sl] = g.cp1[j];
-      kv[sl] = g.k2[p];
-      bv[sl] = b0[k == 0 ? p : 0];
-    }
-    constexpr int kMiSlots = (kTailMinv + TT - 1) / TT;
-    const int nmi = a.nunk * a.nunk;
-    cplx<R> mv[kMiSlots];
-#pragma unroll
-    for (int m = 0; m < kMiSlots; m++) {
-      const int q2 = tid + m * TT;
-      mv[m] = a.minvT[minv_lds && q2 < nmi ? q2 : 0];
-    }
-    // unconditional stores (unused entries to a spare slot) keep the loads
-    // above ahead of every wait
-#pragma unroll
-    for (int m = 0; m < kMiSlots; m++) {
-      const int q2 = tid + m * TT;
-      S.mi[minv_lds && q2 < nmi ? q2 : kTailMinv] = mv[m];
-    }
-    const int wx = wl && ln < gw.n0 ? a.woff[kw] + ln : TW, wy = wl && ln < gw.n1 ? a.woff[kw] + ln : TW;
-    S.xm[wx] = wxm;
-    S.xp[wx] = wxp;
-    S.ym[wy] = wym;
-    S.yp[wy] = wyp;
-#pragma unroll
-    for (int sl = 0; sl < kSlots; sl++) {
-      const int k = lv[sl];
-      if (k < 0) continue;
-      const int kk = __builtin_amdgcn_readfirstlane(k < 0 ? 0 : k);
-      const Grid<R> &g = a.g[kk];
-      const int p = pv[sl], j = (int)(((float)p + 0.5f) * (1.0f / (float)g.n0)), i = p - j * g.n0;
-      const int P = a.noff[kk] + p;
-      const bool in = i >= 1 && i <= g.n0 - 2 && j >= 1 && j <= g.n1 - 2;
-      const cplx<R> dv = in ? inv_c(cxm[sl] + cxp[sl] + cym[sl] + cyp[sl] + (kv[sl] * g.beta + g.c)) : zero_c<R>();
-      S.d[P] = dv;
-      if (kk == 0) {
-        const cplx<R> b = in ? bv[sl] : zero_c<R>();
-        S.b[P] = b;
-        S.t[P] = (in && ((i + j) & 1) == 0) ? om * (b * dv) : zero_c<R>();
-      }
-    }
-  }
-  __syncthreads();
-
-  // Colour phases enumerate node pairs (columns 2h, 2h + 1 of a row: one red,
-  // one black), so every thread has one node of the colour at hand; row
-  // indices come from a float reciprocal (exact for these sizes: the error is
-  // far below the half-node margin), not an integer division.
-  // down: black relaxation, red residual, restriction (which also performs
-  // the next level's zero-guess red relaxation on the nodes it produces)
-  for (int k = 0; k < last; k++) {
-    const Grid<R> &g = a.g[k];
-    const int n0 = g.n0, n1 = g.n1, no = a.noff[k], wo = a.woff[k];
-    const int H = (n0 + 1) >> 1, np = n1 * H;
-    const float invH = 1.0f / (float)H;
-    const cplx<R> *xm = S.xm + wo, *xp = S.xp + wo, *ym = S.ym + wo, *yp = S.yp + wo;
-    cplx<R> *b = S.b + no, *t = S.t + no, *w = S.w + no, *d = S.d + no;
-    for (int q = tid; q < np; q += TT) {
-      const int j = (int)(((float)q + 0.5f) * invH), i = 2 * (q - j * H) + ((j + 1) & 1);  // black
-      if (i >= 1 && i <= n0 - 2 && j >= 1 && j <= n1 - 2) {
-        const int p = j * n0 + i;
-        const cplx<R> tb = b[p] + (xm[i] * t[p - 1] + xp[i] * t[p + 1] + ym[j] * t[p - n0] + yp[j] * t[p + n0]);
-        t[p] = om * (tb * d[p]);
-        w[p] = om1 * tb;  // black residual (1 - w)(b + o)
-      }
-    }
-    __syncthreads();
-    // red residual (1 - w) b + o; only interior residuals are read below
-    for (int q = tid; q < np; q += TT) {
-      const int j = (int)(((float)q + 0.5f) * invH), i = 2 * (q - j * H) + (j & 1);  // red
-      if (i >= 1 && i <= n0 - 2 && j >= 1 && j <= n1 - 2) {
-        const int p = j * n0 + i;
-        w[p] = om1 * b[p] + (xm[i] * t[p - 1] + xp[i] * t[p + 1] + ym[j] * t[p - n0] + yp[j] * t[p + n0]);
-      }
-    }
-    __syncthreads();
-    const Grid<R> &gc = a.g[k + 1];
-    const int c0 = gc.n0, nc = c0 * gc.n1, nco = a.noff[k + 1];
-    const float inv0 = 1.0f / (float)c0;
-    for (int q = tid; q < nc; q += TT) {
-      const int J = (int)(((float)q + 0.5f) * inv0), I = q - J * c0;
-      cplx<R> acc = zero_c<R>(), tv = zero_c<R>();
-      if (I >= 1 && I <= c0 - 2 && J >= 1 && J <= gc.n1 - 2) {
-        const cplx<R> *r0 = w + (2 * J) * n0 + 2 * I;
-        acc = R(0.25) * r0[0] + R(0.125) * (r0[-1] + r0[1] + r0[-n0] + r0[n0]) +
-              R(0.0625) * (r0[-n0 - 1] + r0[-n0 + 1] + r0[n0 - 1] + r0[n0 + 1]);
-        if (((I + J) & 1) == 0) tv = om * (acc * S.d[nco + q]);
-      }
-      S.b[nco + q] = acc;
-      S.t[nco + q] = tv;
-    }
-    __syncthreads();
-  }
-
-  // dense solve on the coarsest level; its boundary nodes (read as 0 by the
-  // prolongation) are cleared by other threads in the same phase: the solve
-  // writes only interior nodes
-  {
-    const Grid<R> &g = a.g[last];
-    const int nn = g.n0 * g.n1, no = a.noff[last];
-    const float inv0 = 1.0f / (float)g.n0;
-    for (int p = tid; p < nn; p += TT) {
-      const int j = (int)(((float)p + 0.5f) * inv0), i = p - j * g.n0;
-      if (i == 0 || i == g.n0 - 1 || j == 0 || j == g.n1 - 1) S.w[no + p] = zero_c<R>();
-    }
-    if (minv_lds) tail_dense(a.nunk, a.tpr, S.mi, S.b + no, S.w + no, g.n0);
-    else tail_dense(a.nunk, a.tpr, a.minvT, S.b + no, S.w + no, g.n0);
-    __syncthreads();
-  }
-
-  // up: prolongation + correction, then the red-black post-sweep in place;
-  // the first level's black sweep writes the result (both nodes of every
-  // pair) to global memory
-  for (int k = last - 1; k >= 0; k--) {
-    const Grid<R> &g = a.g[k];
-    const int n0 = g.n0, n1 = g.n1, no = a.noff[k], wo = a.woff[k];
-    const int H = (n0 + 1) >> 1, np = n1 * H;
-    const float invH = 1.0f / (float)H;
-    const int c0 = a.g[k + 1].n0;
-    const cplx<R> *xm = S.xm + wo, *xp = S.xp + wo, *ym = S.ym + wo, *yp = S.yp + wo;
-    const cplx<R> *b = S.b + no, *t = S.t + no, *d = S.d + no, *e = S.w + a.noff[k + 1];
-    cplx<R> *w = S.w + no;
-    for (int q = tid; q < np; q += TT) {
-      const int j = (int)(((float)q + 0.5f) * invH), i0 = 2 * (q - j * H);
-      const bool yin = j >= 1 && j <= n1 - 2;
-      const cplx<R> *e0 = e + (j >> 1) * c0 + (i0 >> 1);  // i0 even: coarse column i0 / 2
-      // column i0 (even): coarse node or the mean over two coarse rows
-      cplx<R> pa = zero_c<R>(), pb = zero_c<R>();
-      if (yin) {
-        if ((j & 1) == 0) {
-          pa = e0[0];
-          pb = R(0.5) * (e0[0] + e0[1]);
-        } else {
-          pa = R(0.5) * (e0[0] + e0[c0]);
-          pb = R(0.25) * (e0[0] + e0[1] + e0[c0] + e0[c0 + 1]);
-        }
-      }
-      const int p = j * n0 + i0;
-      w[p] = (yin && i0 >= 1 && i0 <= n0 - 2) ? t[p] + pa : zero_c<R>();
-      if (i0 + 1 < n0) w[p + 1] = (yin && i0 + 1 <= n0 - 2) ? t[p + 1] + pb : zero_c<R>();
-    }
-    __syncthreads();
-    for (int colour = 0; colour < 2; colour++) {
-      for (int q = tid; q < np; q += TT) {
-        const int j = (int)(((float)q + 0.5f) * invH), h2 = 2 * (q - j * H);
-        const int i = h2 + ((j + colour) & 1);  // the pair's node of this colour
-        const int p = j * n0 + i;
-        if (i >= 1 && i <= n0 - 2 && j >= 1 && j <= n1 - 2) {
-          const cplx<R> o = xm[i] * w[p - 1] + xp[i] * w[p + 1] + ym[j] * w[p - n0] + yp[j] * w[p + n0];
-          w[p] = om1 * w[p] + om * ((b[p] + o) * d[p]);
-        }
-        if (k == 0 && colour == 1) {
-          const int pp = j * n0 + h2;  // both nodes of the pair (the red one is final)
-          u0[pp] = w[pp];
-          if (h2 + 1 < n0) u0[pp + 1] = w[pp + 1];
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// ------------------------------------------------------------ wide tail
-// The same cycle as k_tail (FP32) from a level of up to 65^2 nodes.  To fit
-// a workgroup's 160 KiB of LDS a node keeps its right-hand side, iterate,
-// residual and k^2 (28 B) and its inverse diagonal is formed where it is used,
-// from the LDS weights and k^2 by k_tail's set-up expression (the same value);
-// the coarsest inverse is read from memory.  The set-up loads the weights
+// From a level of up to 65^2 nodes.  To fit a workgroup's 160 KiB of LDS a node
+// keeps its right-hand side, iterate, residual and k^2 (28 B) and its inverse
+// diagonal is formed where it is used, from the LDS weights and k^2; the
+// coarsest inverse is read from memory.  Colour phases enumerate node pairs
+// (columns 2h, 2h + 1 of a row: one red, one black), so every thread has one
+// node of the colour at hand; row indices come from a float reciprocal (exact
+// for these sizes), not an integer division.  The set-up loads the weights
 // (wave k: level k's, two entries per lane), k^2 of every node and the first
 // level's right-hand side; the first level's zero-guess red relaxation is a
 // phase of its own.
@@ -739,7 +518,7 @@ struct TailLdsWide {
 static_assert(sizeof(TailLdsWide) <= 163840, "the wide tail's vectors fit a workgroup's LDS");
 
 template <bool MR>
-__global__ __launch_bounds__(TT) void k_tail_wide(TailArgs<float> a, RhsSet rs) {
+__global__ __launch_bounds__(TT) void k_tail_wide(TailArgs a, RhsSet rs) {
   __shared__ TailLdsWide S;
   const int tid = threadIdx.x;
   const int64_t rq = MR ? rhs_index(rs) * rhs_stride((int64_t)a.g[0].n0 * a.g[0].n1) : 0;
@@ -814,7 +593,7 @@ __global__ __launch_bounds__(TT) void k_tail_wide(TailArgs<float> a, RhsSet rs) 
   __syncthreads();
 
   // down: black relaxation, red residual, restriction (with the next level's
-  // zero-guess red relaxation), as in k_tail
+  // zero-guess red relaxation)
   for (int k = 0; k < last; k++) {
     const Grid<float> &g = a.g[k];
     const int n0 = g.n0, n1 = g.n1, no = a.noff[k], wo = a.woff[k];
@@ -867,11 +646,13 @@ __global__ __launch_bounds__(TT) void k_tail_wide(TailArgs<float> a, RhsSet rs) 
       const int j = (int)(((float)p + 0.5f) * inv0), i = p - j * g.n0;
       if (i == 0 || i == g.n0 - 1 || j == 0 || j == g.n1 - 1) S.w[no + p] = zero_c<float>();
     }
-    tail_dense(a.nunk, a.tpr, a.minvT, S.b + no, S.w + no, g.n0);
+    tail_dense(a.nunk, a.tpr, a.minv, dense_ld(a.nunk), S.b + no, S.w + no, g.n0);
     __syncthreads();
   }
 
-  // up: prolongation + correction, then the red-black post-sweep, as in k_tail
+  // up: prolongation + correction, then the red-black post-sweep in place; the
+  // first level's black sweep writes the result (both nodes of every pair) to
+  // global memory
   for (int k = last - 1; k >= 0; k--) {
     const Grid<float> &g = a.g[k];
     const int n0 = g.n0, n1 = g.n1, no = a.noff[k], wo = a.woff[k];
@@ -995,18 +776,9 @@ void launch_up_rb(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, 
   else launch_up_mr<R, false>(fine, coarse, b, ec, u_out, omega, rows, s, rs);
 }
 
-template <typename R>
-void launch_tail(const TailArgs<R> &a, hipStream_t s, const RhsSet &rs) {
-  if constexpr (sizeof(R) == 4) {
-    // beyond k_tail's capacity (or a level wider than one wave): the wide tail
-    if (a.noff[a.nl] > kTailCap || a.g[0].n0 > 64 || a.g[0].n1 > 64) {
-      if (multi_rhs(rs)) launch_k((k_tail_wide<true>), dim3(1, rs.count), dim3(TT), 0, s, a, rs);
-      else launch_k((k_tail_wide<false>), dim3(1, 1), dim3(TT), 0, s, a, rs);
-      return;
-    }
-  }
-  if (multi_rhs(rs)) launch_k((k_tail<R, true>), dim3(1, rs.count), dim3(TT), 0, s, a, rs);
-  else launch_k((k_tail<R, false>), dim3(1, 1), dim3(TT), 0, s, a, rs);
+void launch_tail_wide(const TailArgs &a, hipStream_t s, const RhsSet &rs) {
+  if (multi_rhs(rs)) launch_k((k_tail_wide<true>), dim3(1, rs.count), dim3(TT), 0, s, a, rs);
+  else launch_k((k_tail_wide<false>), dim3(1, 1), dim3(TT), 0, s, a, rs);
 }
 
 template void launch_down_rb<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *, cplx<double> *,
@@ -1019,8 +791,6 @@ template void launch_down_rb_src<float>(const Grid<float> &, const Grid<float> &
                                         float, int, hipStream_t);
 template void launch_down_rb_src<double>(const Grid<double> &, const Grid<double> &, const DownSrc<double> &,
                                          cplx<double> *, double, int, hipStream_t);
-template void launch_tail<double>(const TailArgs<double> &, hipStream_t, const RhsSet &);
-template void launch_tail<float>(const TailArgs<float> &, hipStream_t, const RhsSet &);
 template void launch_up_rb<float>(const Grid<float> &, const Grid<float> &, const cplx<float> *, const cplx<float> *,
                                   cplx<float> *, float, int, hipStream_t, const RhsSet &);
 

@@ -268,3 +268,20 @@ def test_side_stream_solver_is_ordered_with_the_callers_stream():
     b3.copy_(ref)
     xb1, st = S1.solve(b3, krylov=big)
     assert st["status"] == 0 and torch.equal(xb1, xb0)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n,coarsest", [(81, 41), (49, 4)])
+def test_batch_dense_end_equals_single_solves(dt, n, coarsest):
+    """Five right-hand sides through one dense map (1521 unknowns: two stages of
+    1024; 529: one) give the single solves' bits."""
+    import torch
+    w = W.coulomb(E=2.0, n=n, coarsest=coarsest)
+    rng = np.random.default_rng(n)
+    kr = E.Krylov(method="bicgstab", rtol=1e-8, maxit=500)
+    S = gpu_for(w, dt, krylov=kr)
+    B = torch.stack([to_gpu(W.random_complex(w.shape, rng)) for _ in range(5)])
+    xs, stats = E.batch_solve([S], [B], kr)
+    assert stats[0]["status"] == 0, stats
+    for r in range(5):
+        assert torch.equal(xs[0][r], S.solve(B[r].contiguous(), krylov=kr)[0]), r

@@ -303,6 +303,32 @@ def test_3d_fused_cycle(dt, n, coarsest, omega):
     assert np.array_equal(to_np(S.vcycle_native(to_gpu(v))), got)
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("dim,n,coarsest,gf,gc,smoother,nu1,nu2",
+                         [(2, 81, 6, 1, 3, "jacobi", 1, 1), (2, 41, 6, 1, 4, "jacobi", 1, 2),
+                          (2, 93, 47, 1, 1, "rbgs", 1, 1), (2, 9, 3, 1, 1, "rbgs", 1, 1), (2, 5, 5, 1, 1, "rbgs", 1, 1),
+                          (3, 17, 3, 1, 1, "rbgs", 1, 1), (3, 21, 6, 2, 2, "jacobi", 1, 1),
+                          (3, 25, 4, 1, 3, "rbgs", 2, 1), (3, 19, 10, 1, 2, "jacobi", 0, 2)])
+def test_dense_coarse_end(dt, dim, n, coarsest, gf, gc, smoother, nu1, nu2):
+    """The dense map of the coarse end against the oracle's cycle: one unknown
+    on the coarsest level, odd and even numbers of unknowns, 1521 and 2025
+    unknowns (more than the 1024 staged at a time), 3D maps, the whole grid as
+    one map, one level, repeated visits with exchanged cycle indices, zero
+    sweeps."""
+    if coarsest < n:
+        w = ragged_workload(n=n, coarsest=coarsest, dim=dim)
+    else:
+        w = W.coulomb(E=1.0, n=n, coarsest=coarsest)
+    cy = dict(smoother=smoother, omega=0.9, nu1=nu1, nu2=nu2, gamma_f=gf, gamma_c=gc, coarsest=coarsest)
+    P = oracle_for(w, cycle=cy)
+    S = gpu_for(w, dt, cycle=cy)
+    v = W.random_complex(w.shape, np.random.default_rng(n))
+    got = to_np(S.vcycle(to_gpu(v)))
+    assert relerr(got, P.mg_apply(v)) < (1e-12 if dt == "f64" else CYCLE_TOL[dt])
+    for a in range(dim):
+        assert np.all(np.take(got, [0, -1], axis=a) == 0)
+
+
 def test_full_size_vcycle_sampled():
     """The benchmark grid (2049^2, h = 0.25, 9 levels): one FP64 cycle checked
     against the oracle on the whole grid (one oracle cycle takes seconds)."""
