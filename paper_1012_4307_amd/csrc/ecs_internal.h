@@ -188,10 +188,6 @@ void launch_prolong_add(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R
 template <typename R>
 void launch_prolong_to(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *ec, const cplx<R> *u_in,
                        cplx<R> *u_out, hipStream_t s);
-// 2D: out = one omega-Jacobi sweep of (u + P ec), out of place
-template <typename R>
-void launch_prolong_jacobi(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *ec, const cplx<R> *b,
-                           const cplx<R> *u, cplx<R> *out, R omega, hipStream_t s);
 // fused V(1,1) red-black kernels (2D): zero-guess pre-sweep + residual + FW
 // (the pre-smoothed iterate is not stored), and the pre-sweep recomputed from
 // b + prolongation + correction + post-sweep into u_out

@@ -19,6 +19,7 @@
 
 #include "ecs_cube.h"
 #include "ecs_dense.h"
+#include "ecs_jacobi.h"
 #include "ecs_krylov.h"
 #include "ecsmg.h"
 
@@ -853,6 +854,10 @@ cplx<R> *jacobi_sweeps(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *cur, cplx<R
   return cur;
 }
 
+bool fused_jacobi(const ecs_ctx *C);
+template <typename R>
+void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, int visits);
+
 // Algorithm 1: u <- MG(l, M_l, b, u, nu1, nu2, C, gf, gc).  zero_guess: u == 0
 // on entry (u's contents are not read and need not be cleared).  From level
 // gt_l on the rest of the recursion, with the repeated visits, is one dense map;
@@ -863,6 +868,10 @@ void mg(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, bool ze
   if (l == C->gt_l) {  // the finest level itself
     TimedScope ts(C, kTCoarse, 0.0);
     dense_apply<R>(C, l, b, u);
+    return;
+  }
+  if (l == 0 && zero_guess && fused_jacobi(C)) {
+    jacobi_visits<R>(C, 0, b, u, gf, gc, 1);
     return;
   }
   DevLevel<R> &D = dev_level<R>(C, l);
@@ -894,8 +903,7 @@ void mg(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, bool ze
     {
       // read u, b, k^2, the coarse correction; write the swept iterate
       TimedScope ts(C, l == 0 ? kTProlong : kTCoarse, (double)C->hl[l].nn * sizeof(R) * (7.0 + 2.0 / 4));
-      launch_prolong_jacobi<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), Dc.u, b, cur, oth, (R)C->prec.omega,
-                               C->stream);
+      launch_jacobi_up<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), b, cur, Dc.u, oth, (R)C->prec.omega, C->stream);
     }
     jacobi_sweeps<R>(C, l, b, oth, cur, nu2 - 1, false);
     return;
@@ -911,6 +919,45 @@ void mg(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, bool ze
   }
   if (jac) jacobi_sweeps<R>(C, l, b, dst, dst == u ? D.t : u, C->prec.nu2, false);
   else smooth<R>(C, l, b, u, D.t, C->prec.nu2, false);
+}
+
+// 2D omega-Jacobi cycles with one sweep before and one after the correction run
+// on the fused level kernel: gamma + 1 launches for the gamma visits that a
+// parent makes in a row.
+bool fused_jacobi(const ecs_ctx *C) {
+  const ecs_prec_desc &P = C->prec;
+  return C->dim == 2 && P.smoother == ECS_SMOOTH_JACOBI && P.nu1 == 1 && P.nu2 == 1;
+}
+
+// Those `visits` of level l from a zero iterate (the loop of Algorithm 1: the
+// first with (gf, gc), the later ones with the two exchanged), the result in u.
+// Every kernel writes the iterate to the other of u and the level scratch.
+template <typename R>
+void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, int visits) {
+  DevLevel<R> &D = dev_level<R>(C, l), &Dc = dev_level<R>(C, l + 1);
+  const Grid<R> g = grid_M<R>(C, l), gx = grid_M<R>(C, l + 1);
+  const R om = (R)C->prec.omega;
+  const int64_t nn = C->hl[l].nn;
+  cplx<R> *x = nullptr;
+  for (int i = 0; i < visits; i++) {
+    cplx<R> *to = ((visits - i) & 1) ? D.t : u;  // visits + 1 writes, the last one to u
+    {
+      // read b, k^2 (later visits: x and the correction); write x and the coarse residual
+      TimedScope ts(C, l == 0 ? kTDown : kTCoarse, (double)nn * sizeof(R) * (i == 0 ? 5.5 : 8.0));
+      launch_jacobi_down<R>(g, gx, b, x, Dc.u, to, Dc.b, om, C->stream);
+    }
+    x = to;
+    const int pf = i == 0 ? gf : gc, pc = i == 0 ? gc : gf;
+    if (l + 1 == C->gt_l) {
+      TimedScope ts(C, kTCoarse, 0.0);
+      dense_apply<R>(C, l + 1, Dc.b, Dc.u, pf != C->prec.gamma_f || pc != C->prec.gamma_c);
+    } else {
+      jacobi_visits<R>(C, l + 1, Dc.b, Dc.u, pf, pc, pc);
+    }
+  }
+  // read x, b, k^2, the correction; write u
+  TimedScope ts(C, l == 0 ? kTUp : kTCoarse, (double)nn * sizeof(R) * 7.5);
+  launch_jacobi_up<R>(g, gx, b, x, Dc.u, u, om, C->stream);
 }
 
 // V(1,1) red-black in 2D (the QD set-up of Sec. 4.2) runs on the fused
@@ -1129,12 +1176,24 @@ void drop_graphs(ecs_ctx *C) {
 // visits (large gamma over many levels) are not captured
 int64_t cycle_launches(const ecs_ctx *C, int l, int gf, int gc, int64_t cap) {
   if (l == C->gt_l) return 1;
+  if (fused_jacobi(C)) {  // one kernel per visit and one after the last; this visit's parent counts the latter
+    int64_t n = 2;
+    if (l + 1 == C->gt_l) return n + 1;
+    for (int i = 1; i <= gc && n < cap; i++)
+      n += cycle_launches(C, l + 1, i == 1 ? gf : gc, i == 1 ? gc : gf, cap) - (i > 1);
+    return n;
+  }
   int64_t n = C->prec.nu1 + C->prec.nu2 + 2;
   if (l + 1 == C->gt_l) return n + 1;
   for (int i = 1; i <= gc && n < cap; i++)
     n += i == 1 ? cycle_launches(C, l + 1, gf, gc, cap) : cycle_launches(C, l + 1, gc, gf, cap);
   return n;
 }
+
+// General cycles of up to this many launches are launched eagerly too: with 3
+// launches (65^2) a GMRES step took 82 us eagerly and 87 as a graph, with 9
+// (161^2, F_1^3) a Bi-CGSTAB solve 9.06 and 9.52 ms; with 33 (641^2) 92.7 and 91.7.
+constexpr int64_t kEagerLaunches = 16;
 
 // A general cycle is several launches per level, most of them a few
 // microseconds of work on the coarse levels, so host launch overhead would
@@ -1152,8 +1211,9 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   if (C->graph_mode == ECS_GRAPHS_NEVER || C->no_alloc) return false;
   if (fused_vcycle(C) || fused_vcycle3(C)) {
     if (C->graph_mode == ECS_GRAPHS_AUTO) return false;
-  } else if (cycle_launches(C, 0, C->prec.gamma_f, C->prec.gamma_c, 4096) >= 4096) {
-    return false;
+  } else {
+    const int64_t n = cycle_launches(C, 0, C->prec.gamma_f, C->prec.gamma_c, 4096);
+    if (n >= 4096 || (C->graph_mode == ECS_GRAPHS_AUTO && n <= kEagerLaunches)) return false;
   }
   for (auto &g : C->graphs)
     if (g.b == b0 && g.u == u0 && g.real_bytes == (int)sizeof(R))

@@ -1,0 +1,275 @@
+// kernels_jacobi.hip -- fused 2D kernels of general omega-Jacobi cycles with one
+// sweep before and after the coarse-grid correction (the F cycles of Sec. 5 of
+// bin Zubair, Reps, Vanroose).  Algorithm 1 visits a level in groups, the gamma
+// visits its parent makes in a row, with the level's right-hand side unchanged;
+// one kernel covers everything the level does between two visits of the next
+// one:
+//
+//   first visit:   x = J(0),                 rc = FW(b - M x)
+//   later visits:  x = J(J(x + P e)),        rc = FW(b - M x)
+//                  (the post-sweep of one visit, the pre-sweep of the next)
+//   after the last: x = J(x + P e)
+//
+// gamma + 1 launches for gamma visits, where a launch per step takes 3 gamma.
+// On the levels in question (a few hundred nodes per axis and less) a launch
+// costs more than its bytes.  A block owns a tile, stages it with a halo (two
+// nodes, two more per further sweep) and recomputes the halo, phases exchanging
+// neighbours through LDS; x is written to the other of two buffers, since the
+// neighbouring blocks read the old one.
+//
+// What bounds them: launch latency and the phases of a block on all levels but
+// the finest of a large grid.  641^2 FP64: first visit 7.5 us (4.9 TB/s of its 37
+// MB with the stores), after the last 7.0 us; 321^2 4.7, later visits 6.8, after
+// the last 4.3; 81^2 4.0, 5.3, 4.8.  The three launches of a visit took 3.5 + 4.8
+// + 4.7 us on average over the levels, 9.4 us for the last on 641^2.  An F_1^3 cycle on 641^2
+// is 33 launches instead of 55: 268 -> 198 us; F_1^4 on 385^2 280 -> 185 us.
+#include "ecs_jacobi.h"
+
+namespace ecs {
+
+namespace {
+
+template <typename R>
+__device__ __forceinline__ cplx<R> zj() {
+  return mk<R>(0, 0);
+}
+
+// MODE 0: first visit, 2: later ones.  Tile: CX x CY coarse nodes from (I0, J0);
+// residuals are needed on fine columns 2 I0 + [-1, 2 CX), x on [-2, 2 CX + 1),
+// and one node further out for each sweep that reads neighbours.
+// Lanes are columns, the 4 waves take every fourth row, a thread keeps b, D,
+// 1 / D and the iterate of its nodes in registers.
+template <typename R, int CY, int MODE>
+__global__ __launch_bounds__(256) void k_jac_down(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
+                                                  const cplx<R> *__restrict__ x, const cplx<R> *__restrict__ e,
+                                                  cplx<R> *__restrict__ out, cplx<R> *__restrict__ rc, R omega,
+                                                  int tiles_x, int tiles) {
+  constexpr int H = 2 + MODE, CX = (64 - (2 * H - 1)) / 2;
+  constexpr int WX = 2 * CX + 2 * H - 1, WY = 2 * CY + 2 * H - 1, RPW = (WY + 3) / 4;
+  __shared__ cplx<R> s0[WY][64], s1[WY][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = xcd_tile(tiles);
+  if (tile < 0) return;
+  const int I0 = (tile % tiles_x) * CX, J0 = (tile / tiles_x) * CY;
+  const int gx0 = 2 * I0 - H, gy0 = 2 * J0 - H, n0 = f.n0, n1 = f.n1;
+  const R om1 = R(1) - omega;
+  const int i = gx0 + lane;
+  const bool xin = lane < WX && i >= 1 && i <= n0 - 2;
+  const cplx<R> xm = xin ? f.cm0[i] : zj<R>(), xp = xin ? f.cp0[i] : zj<R>();
+  const int lm = lane > 0 ? lane - 1 : 0, lp = lane < 63 ? lane + 1 : 63;  // clamped: halo results nobody uses
+  // interior rows of the window through buffer resources: 0 elsewhere
+  const int jl = min(max(gy0, 1), n1 - 1), jh = min(max(gy0 + WY, 1), n1 - 1);
+  const __amdgpu_buffer_rsrc_t rb = rows_rsrc(b, jl, jh, n0), rk = rows_rsrc(f.k2, jl, jh, n0);
+  const __amdgpu_buffer_rsrc_t rx = rows_rsrc(MODE ? x : b, jl, jh, n0);
+  const uint32_t oc = col_off<cplx<R>>(xin, i), ok = col_off<R>(xin, i);
+  // the correction's rows; its column i / 2 and the next (the same when i is even)
+  const int Jl = min(max(gy0 >> 1, 0), c.n1), Jh = min((gy0 + WY) / 2 + 2, c.n1);
+  const __amdgpu_buffer_rsrc_t re = rows_rsrc(MODE ? e : b, Jl, Jh, c.n0);
+  const uint32_t oa = col_off<cplx<R>>(xin, i >> 1), ob = col_off<cplx<R>>(xin, (i >> 1) + (i & 1));
+  cplx<R> B[RPW], X[RPW], D[RPW], V[RPW], ym[RPW], yp[RPW], ea[RPW], eb[RPW], ec[RPW], ed[RPW];
+  R K[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; r++) {
+    const int ly = wv + 4 * r, j = gy0 + ly;
+    const bool yin = ly < WY && j >= 1 && j <= n1 - 2;
+    const int jc = yin ? j : 1;
+    ym[r] = yin ? f.cm1[jc] : zj<R>();
+    yp[r] = yin ? f.cp1[jc] : zj<R>();
+    const uint32_t q = row_off<cplx<R>>(j - jl, n0);
+    B[r] = ld_c(rb, oc + q, cplx<R>());
+    K[r] = ld_r(rk, ok + row_off<R>(j - jl, n0), R());
+    if constexpr (MODE != 0) {
+      X[r] = ld_c(rx, oc + q, cplx<R>());
+      const uint32_t q0 = row_off<cplx<R>>((j >> 1) - Jl, c.n0), q1 = row_off<cplx<R>>((j >> 1) + (j & 1) - Jl, c.n0);
+      ea[r] = ld_c(re, oa + q0, cplx<R>());
+      eb[r] = ld_c(re, ob + q0, cplx<R>());
+      ec[r] = ld_c(re, oa + q1, cplx<R>());
+      ed[r] = ld_c(re, ob + q1, cplx<R>());
+    }
+  }
+  // diagonals; x = J(0) or v = x + P e (0 off the interior)
+#pragma unroll
+  for (int r = 0; r < RPW; r++) {
+    const int ly = wv + 4 * r, j = gy0 + ly;
+    if (ly < WY) {
+      const bool in = xin && j >= 1 && j <= n1 - 2;
+      D[r] = in ? xm + xp + ym[r] + yp[r] + (K[r] * f.beta + f.c) : mk<R>(1, 0);
+      const R s = R(1) / abs2(D[r]);
+      V[r] = mk<R>(D[r].re * s, -D[r].im * s);
+      if constexpr (MODE == 0) X[r] = omega * (B[r] * V[r]);
+      else X[r] = in ? X[r] + R(0.25) * ((ea[r] + eb[r]) + (ec[r] + ed[r])) : zj<R>();
+      s0[ly][lane] = X[r];
+    }
+  }
+  __syncthreads();
+  auto offd = [&](const cplx<R>(*s)[64], int ly, int r) {
+    return xm * s[ly][lm] + xp * s[ly][lp] + ym[r] * s[ly - 1][lane] + yp[r] * s[ly + 1][lane];
+  };
+  if constexpr (MODE != 0) {
+    // two sweeps, each a ring further in (from s0 to s1 and back)
+#pragma unroll
+    for (int sw = 0; sw < 2; sw++) {
+      cplx<R>(*from)[64] = sw == 0 ? s0 : s1;
+      cplx<R>(*to)[64] = sw == 0 ? s1 : s0;
+#pragma unroll
+      for (int r = 0; r < RPW; r++) {
+        const int ly = wv + 4 * r, j = gy0 + ly;
+        if (ly >= 1 + sw && ly <= WY - 2 - sw) {
+          const cplx<R> o = offd(from, ly, r);
+          X[r] = (xin && j >= 1 && j <= n1 - 2) ? om1 * X[r] + omega * ((B[r] + o) * V[r]) : zj<R>();
+          to[ly][lane] = X[r];
+        }
+      }
+      __syncthreads();
+    }
+  }
+  // x of the owned nodes; residual b - M x, 0 off the interior
+  const __amdgpu_buffer_rsrc_t ro = rows_rsrc(out, 2 * J0, min(2 * J0 + 2 * CY, n1), n0);
+  const uint32_t oo = col_off<cplx<R>>(lane >= H && lane < H + 2 * CX && i < n0, i);
+#pragma unroll
+  for (int r = 0; r < RPW; r++) {
+    const int ly = wv + 4 * r, j = gy0 + ly;
+    if (ly >= H && ly < H + 2 * CY && j < n1) st_c(ro, oo + row_off<cplx<R>>(j - 2 * J0, n0), X[r]);
+    if (ly >= H - 1 && ly <= H + 2 * CY - 1) {
+      const cplx<R> o = offd(s0, ly, r);
+      s1[ly][lane] = (xin && j >= 1 && j <= n1 - 2) ? (B[r] + o) - D[r] * X[r] : zj<R>();
+    }
+  }
+  __syncthreads();
+  // full weighting: lane = coarse column, its fine node in column H + 2 lane
+  if (lane < CX) {
+    const int I = I0 + lane, p = H + 2 * lane;
+    for (int cy = wv; cy < CY; cy += 4) {
+      const int J = J0 + cy, y = H + 2 * cy;
+      if (I >= c.n0 || J >= c.n1) continue;
+      cplx<R> acc = zj<R>();
+      if (I >= 1 && I <= c.n0 - 2 && J >= 1 && J <= c.n1 - 2)
+        acc = R(0.25) * s1[y][p] + R(0.125) * (s1[y][p - 1] + s1[y][p + 1] + s1[y - 1][p] + s1[y + 1][p]) +
+              R(0.0625) * (s1[y - 1][p - 1] + s1[y - 1][p + 1] + s1[y + 1][p - 1] + s1[y + 1][p + 1]);
+      rc[(int64_t)J * c.n0 + I] = acc;
+    }
+  }
+}
+
+// out = J(x + P e): the correction and the first post-sweep.  62 x TY owned nodes,
+// staged with a ring of one.
+template <typename R, int TY>
+__global__ __launch_bounds__(256) void k_jac_up(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
+                                                const cplx<R> *__restrict__ x, const cplx<R> *__restrict__ e,
+                                                cplx<R> *__restrict__ out, R omega, int tiles_x, int tiles) {
+  constexpr int TX = 62, WY = TY + 2, RPW = (WY + 3) / 4;
+  __shared__ cplx<R> s0[WY][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = xcd_tile(tiles);
+  if (tile < 0) return;
+  const int x0 = (tile % tiles_x) * TX, y0 = (tile / tiles_x) * TY;
+  const int n0 = f.n0, n1 = f.n1, i = x0 - 1 + lane, gy0 = y0 - 1;
+  const R om1 = R(1) - omega;
+  const bool xin = i >= 1 && i <= n0 - 2;
+  const cplx<R> xm = xin ? f.cm0[i] : zj<R>(), xp = xin ? f.cp0[i] : zj<R>();
+  const int lm = lane > 0 ? lane - 1 : 0, lp = lane < 63 ? lane + 1 : 63;
+  const int jl = min(max(gy0, 1), n1 - 1), jh = min(max(gy0 + WY, 1), n1 - 1);
+  const __amdgpu_buffer_rsrc_t rb = rows_rsrc(b, jl, jh, n0), rk = rows_rsrc(f.k2, jl, jh, n0),
+                               rx = rows_rsrc(x, jl, jh, n0);
+  const uint32_t oc = col_off<cplx<R>>(xin, i), ok = col_off<R>(xin, i);
+  const int Jl = min(max(gy0 >> 1, 0), c.n1), Jh = min((gy0 + WY) / 2 + 2, c.n1);
+  const __amdgpu_buffer_rsrc_t re = rows_rsrc(e, Jl, Jh, c.n0);
+  const uint32_t oa = col_off<cplx<R>>(xin, i >> 1), ob = col_off<cplx<R>>(xin, (i >> 1) + (i & 1));
+  cplx<R> B[RPW], X[RPW], ym[RPW], yp[RPW], ea[RPW], eb[RPW], ec[RPW], ed[RPW];
+  R K[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; r++) {
+    const int ly = wv + 4 * r, j = gy0 + ly;
+    const bool yin = ly < WY && j >= 1 && j <= n1 - 2;
+    const int jc = yin ? j : 1;
+    ym[r] = yin ? f.cm1[jc] : zj<R>();
+    yp[r] = yin ? f.cp1[jc] : zj<R>();
+    const uint32_t q = row_off<cplx<R>>(j - jl, n0);
+    B[r] = ld_c(rb, oc + q, cplx<R>());
+    K[r] = ld_r(rk, ok + row_off<R>(j - jl, n0), R());
+    X[r] = ld_c(rx, oc + q, cplx<R>());
+    const uint32_t q0 = row_off<cplx<R>>((j >> 1) - Jl, c.n0), q1 = row_off<cplx<R>>((j >> 1) + (j & 1) - Jl, c.n0);
+    ea[r] = ld_c(re, oa + q0, cplx<R>());
+    eb[r] = ld_c(re, ob + q0, cplx<R>());
+    ec[r] = ld_c(re, oa + q1, cplx<R>());
+    ed[r] = ld_c(re, ob + q1, cplx<R>());
+  }
+#pragma unroll
+  for (int r = 0; r < RPW; r++) {
+    const int ly = wv + 4 * r, j = gy0 + ly;
+    if (ly < WY) {
+      X[r] = (xin && j >= 1 && j <= n1 - 2) ? X[r] + R(0.25) * ((ea[r] + eb[r]) + (ec[r] + ed[r])) : zj<R>();
+      s0[ly][lane] = X[r];
+    }
+  }
+  __syncthreads();
+  const __amdgpu_buffer_rsrc_t ro = rows_rsrc(out, y0, min(y0 + TY, n1), n0);
+  const uint32_t oo = col_off<cplx<R>>(lane >= 1 && lane <= TX && i < n0, i);
+#pragma unroll
+  for (int r = 0; r < RPW; r++) {
+    const int ly = wv + 4 * r, j = gy0 + ly;
+    if (ly >= 1 && ly <= TY && j < n1) {
+      cplx<R> v = zj<R>();
+      if (xin && j >= 1 && j <= n1 - 2) {
+        const cplx<R> d = xm + xp + ym[r] + yp[r] + (K[r] * f.beta + f.c);
+        const cplx<R> o =
+            xm * s0[ly][lm] + xp * s0[ly][lp] + ym[r] * s0[ly - 1][lane] + yp[r] * s0[ly + 1][lane];
+        v = om1 * X[r] + omega * cdiv(B[r] + o, d);
+      }
+      st_c(ro, oo + row_off<cplx<R>>(j - y0, n0), v);
+    }
+  }
+}
+
+template <typename R, int CY, int MODE>
+void launch_jac(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *x, const cplx<R> *e, cplx<R> *out,
+                cplx<R> *rc, R omega, hipStream_t s) {
+  constexpr int CX = (64 - (2 * (2 + MODE) - 1)) / 2;
+  const int tx = (c.n0 + CX - 1) / CX, tiles = tx * ((c.n1 + CY - 1) / CY);
+  launch_k((k_jac_down<R, CY, MODE>), dim3(xcd_padded(tiles)), dim3(256), 0, s, f, c, b, x, e, out, rc, omega, tx,
+           tiles);
+}
+
+}  // namespace
+
+template <typename R>
+void launch_jacobi_down(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *x, const cplx<R> *e,
+                        cplx<R> *out, cplx<R> *rc, R omega, hipStream_t s) {
+  // two coarse rows a block fill the chip up to 257 coarse rows (a level of 321^2
+  // has 488 blocks of them); four repeat fewer halo rows above
+  const bool low = c.n1 <= 257;
+  if (x == nullptr) {
+    if (low) launch_jac<R, 2, 0>(f, c, b, x, e, out, rc, omega, s);
+    else launch_jac<R, 4, 0>(f, c, b, x, e, out, rc, omega, s);
+  } else {
+    if (low) launch_jac<R, 2, 2>(f, c, b, x, e, out, rc, omega, s);
+    else launch_jac<R, 4, 2>(f, c, b, x, e, out, rc, omega, s);
+  }
+}
+
+template <typename R>
+void launch_jacobi_up(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *x, const cplx<R> *e,
+                      cplx<R> *out, R omega, hipStream_t s) {
+  const int tx = (f.n0 + 61) / 62;
+  const auto go = [&](auto rows) {
+    constexpr int TY = decltype(rows)::value;
+    const int tiles = tx * ((f.n1 + TY - 1) / TY);
+    launch_k((k_jac_up<R, TY>), dim3(xcd_padded(tiles)), dim3(256), 0, s, f, c, b, x, e, out, omega, tx, tiles);
+  };
+  // six rows a block while the level then is a few blocks per CU, 14 above
+  if (f.n1 <= 513) go(std::integral_constant<int, 6>());
+  else go(std::integral_constant<int, 14>());
+}
+
+template void launch_jacobi_up<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
+                                       const cplx<double> *, const cplx<double> *, cplx<double> *, double, hipStream_t);
+template void launch_jacobi_up<float>(const Grid<float> &, const Grid<float> &, const cplx<float> *,
+                                      const cplx<float> *, const cplx<float> *, cplx<float> *, float, hipStream_t);
+template void launch_jacobi_down<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
+                                         const cplx<double> *, const cplx<double> *, cplx<double> *, cplx<double> *,
+                                         double, hipStream_t);
+template void launch_jacobi_down<float>(const Grid<float> &, const Grid<float> &, const cplx<float> *,
+                                        const cplx<float> *, const cplx<float> *, cplx<float> *, cplx<float> *, float,
+                                        hipStream_t);
+
+}  // namespace ecs

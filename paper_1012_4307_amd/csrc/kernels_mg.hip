@@ -276,42 +276,6 @@ __global__ __launch_bounds__(256) void k_prolong_add(Grid<R> f, Grid<R> c, const
   u_out[q.p] = u_in[q.p] + e;
 }
 
-// (P ec) at fine node (i, j) of a 2D level: bilinear in index space; zero on
-// the fine boundary because ec is zero on the coarse boundary.  Branch-free:
-// the mean of the four coarse nodes (I0 or I0 + 1) x (J0 or J0 + 1), where an
-// even index takes the same coarse node twice (never outside the level).
-template <typename R>
-__device__ __forceinline__ cplx<R> prolong_at(const cplx<R> *__restrict__ ec, int c0, int i, int j) {
-  const int I0 = i >> 1, J0 = j >> 1, I1 = I0 + (i & 1), J1 = J0 + (j & 1);
-  const cplx<R> *r0 = ec + (int64_t)J0 * c0, *r1 = ec + (int64_t)J1 * c0;
-  return R(0.25) * ((r0[I0] + r0[I1]) + (r1[I0] + r1[I1]));
-}
-
-// 2D coarse-grid correction fused with the first omega-Jacobi post-sweep, out
-// of place: out = J(u + P ec).  The corrected iterate at the node's four
-// neighbours is formed on the fly (u and ec are zero on their boundaries).
-template <typename R>
-__global__ __launch_bounds__(256) void k_prolong_jacobi(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ ec,
-                                                        const cplx<R> *__restrict__ b,
-                                                        const cplx<R> *__restrict__ u, cplx<R> *__restrict__ out,
-                                                        R omega) {
-  Node<R> q = node_of(f);
-  if (!q.in) return;
-  if (!q.interior) {
-    out[q.p] = mk<R>(0, 0);
-    return;
-  }
-  const int i = q.i, j = q.j, n0 = f.n0, c0 = c.n0;
-  const int64_t p = q.p;
-  const cplx<R> v = u[p] + prolong_at(ec, c0, i, j);
-  const cplx<R> vw = u[p - 1] + prolong_at(ec, c0, i - 1, j), ve = u[p + 1] + prolong_at(ec, c0, i + 1, j);
-  const cplx<R> vs = u[p - n0] + prolong_at(ec, c0, i, j - 1), vn = u[p + n0] + prolong_at(ec, c0, i, j + 1);
-  const cplx<R> o = f.cm0[i] * vw + f.cp0[i] * ve + f.cm1[j] * vs + f.cp1[j] * vn;
-  const cplx<R> d = diag_at(f, i, j, 0, p);
-  const cplx<R> res = b[p] - (d * v - o);
-  out[p] = v + omega * cdiv(res, d);
-}
-
 // y = M x with a fused dot product for Bi-CGSTAB (grid-stride over 64 x 4
 // tiles; one thread per node):
 //   kBicgAlpha: sum conj(d0) y  -> alpha = rho / (r^, v)
@@ -527,11 +491,6 @@ void launch_prolong_to(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R>
                        cplx<R> *u_out, hipStream_t s) {
   launch_k((k_prolong_add<R>), grid_of(fine), dim3(TX, TY), 0, s, fine, coarse, ec, u_in, u_out);
 }
-template <typename R>
-void launch_prolong_jacobi(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *ec, const cplx<R> *b,
-                           const cplx<R> *u, cplx<R> *out, R omega, hipStream_t s) {
-  launch_k((k_prolong_jacobi<R>), grid_of(fine), dim3(TX, TY), 0, s, fine, coarse, ec, b, u, out, omega);
-}
 template <typename R, typename RI>
 void launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
                       cplx<double> *partials, BicgScalars *S, hipStream_t s, const RhsSet &rs) {
@@ -580,8 +539,6 @@ void launch_inject_k2(int n0, int n1, int n2, const double *k2_fine, int f0, int
                                             cplx<R> *, hipStream_t);                                            \
   template void launch_prolong_add<R>(const Grid<R> &, const Grid<R> &, const cplx<R> *, cplx<R> *,              \
                                       hipStream_t);                                                             \
-  template void launch_prolong_jacobi<R>(const Grid<R> &, const Grid<R> &, const cplx<R> *, const cplx<R> *,      \
-                                         const cplx<R> *, cplx<R> *, R, hipStream_t);                           \
   template void launch_prolong_to<R>(const Grid<R> &, const Grid<R> &, const cplx<R> *, const cplx<R> *,         \
                                      cplx<R> *, hipStream_t);                                                   \
   template void launch_inject_k2<R>(int, int, int, const double *, int, int, R *, hipStream_t);

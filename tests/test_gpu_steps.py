@@ -329,6 +329,23 @@ def test_dense_coarse_end(dt, dim, n, coarsest, gf, gc, smoother, nu1, nu2):
         assert np.all(np.take(got, [0, -1], axis=a) == 0)
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n,coarsest,gf,gc", [(61, 16, 1, 1), (113, 8, 1, 3), (125, 32, 2, 2), (113, 8, 2, 1),
+                                              (545, 18, 1, 2)])
+def test_fused_jacobi_cycle(dt, n, coarsest, gf, gc):
+    """The fused omega-Jacobi level kernels against the oracle's cycle: one coarse
+    column and row beyond a tile (61: 31 = 30 + 1; 113: 57 = 2 x 28 + 1; 125 = 2 x
+    62 + 1), groups of one, two and three visits, low and tall tiles (545)."""
+    w = ragged_workload(n=n, coarsest=coarsest, kind="csl", smoother="jacobi", omega=0.8)
+    cy = dict(w.cycle, gamma_f=gf, gamma_c=gc)
+    P = oracle_for(w, cycle=cy)
+    S = gpu_for(w, dt, cycle=cy)
+    v = W.random_complex(w.shape, np.random.default_rng(n))
+    got = to_np(S.vcycle(to_gpu(v)))
+    assert relerr(got, P.mg_apply(v)) < (1e-12 if dt == "f64" else CYCLE_TOL[dt])
+    assert np.all(got[[0, -1]] == 0) and np.all(got[:, [0, -1]] == 0)
+
+
 def test_full_size_vcycle_sampled():
     """The benchmark grid (2049^2, h = 0.25, 9 levels): one FP64 cycle checked
     against the oracle on the whole grid (one oracle cycle takes seconds)."""
