@@ -160,7 +160,7 @@ struct ecs_ctx {
   GmresScalars *gs = nullptr;
   BicgScalars *bs = nullptr, *bs_in = nullptr;
   double *pinned = nullptr;  // host-pinned scalars for readback
-  hipEvent_t step_ev = nullptr;  // completion of the batched driver's last step on this context
+  hipEvent_t step_ev = nullptr;  // completion of the last step's readback on this context
 
   Timer timers[kTClasses];
   std::string err;
@@ -431,8 +431,8 @@ size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
   return cv.off;
 }
 
-// The outer FP64 Bi-CGSTAB forms p and s inside the cycle (bicg_enqueue_step) up to 1025^2 finest
-// nodes, where a launch is short enough that the two it saves count: measured
+// The outer FP64 Bi-CGSTAB forms p and s inside the cycle (bicg_open_step,
+// bicg_close_step) up to 1025^2 finest nodes, where a launch is short enough that the two it saves count: measured
 // 2-3% faster at 513^2 and 1025^2.  At 2049^2 the fused FP64 kernels (121
 // VGPRs for p against 84 for the plain down kernel) lose occupancy on a level
 // that is bandwidth-bound: 1-2% slower for every tile height, so the separate
@@ -1294,6 +1294,28 @@ double read_scalar(ecs_ctx *C, const double *dev) {
   return C->pinned[0];
 }
 
+// Whether a Krylov driver enqueues the next step's opening (the preconditioner
+// and the matvec, which touch neither the solution nor the state that a stop
+// or a restart uses) before it waits for this step's residual estimate.  The
+// device then has work while the host wakes up, reads and launches: 8-15 us a
+// step (513^2 Bi-CGSTAB 135 -> 125 us, 65^2 GMRES 90 -> 78 us).  One opening
+// per stop or restart is wasted, so not on grids whose step takes much longer
+// than the wait.
+constexpr int64_t kAheadMaxNodes = int64_t(1) << 21;
+bool run_ahead(const ecs_ctx *C) {
+  for (const Timer &T : C->timers)
+    if (T.on) return false;  // kernel timers count the launches of the steps reported
+  return nn_of(C) <= kAheadMaxNodes;
+}
+
+// `bytes` (<= 64) from device memory into the pinned buffer, and the event that
+// marks its arrival; take_readback waits for that event only
+bool enqueue_readback(ecs_ctx *C, const void *dev, size_t bytes) {
+  return hipMemcpyAsync(C->pinned, dev, bytes, hipMemcpyDeviceToHost, C->stream) == hipSuccess &&
+         hipEventRecord(C->step_ev, C->stream) == hipSuccess;
+}
+bool wait_readback(ecs_ctx *C) { return hipEventSynchronize(C->step_ev) == hipSuccess; }
+
 template <typename R>
 Grid<R> grid_A_of(const ecs_ctx *C);
 template <>
@@ -1479,18 +1501,21 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
     if (it >= d->maxit) { status = ECS_NOT_CONVERGED; break; }
     int k = 0;
     bool bad = false;
-    for (int j = 0; j < m && it < d->maxit; j++) {
-      cplx<double> *vj = K.V + (int64_t)j * ld;
-      cplx<double> *w = K.V + (int64_t)(j + 1) * ld;
+    // z_j = M^{-1} v_j, w = A z_j
+    auto open_step = [&](int j) {
+      cplx<double> *vj = K.V + (int64_t)j * ld, *w = vj + ld;
       cplx<RZ> *zj = flexible ? Z + (int64_t)j * ld : tz;
       if (d->inner > 0) inner_bicgstab<RZ>(C, K, vj, zj, d->inner);
       else precond<RZ>(C, vj, zj);
+      TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 24));
+      launch_apply<double, RZ, double>(grid_A(C), zj, w, s);
+    };
+    bool opened = false;
+    for (int j = 0; j < m && it < d->maxit; j++) {
+      cplx<double> *w = K.V + (int64_t)(j + 1) * ld;
+      if (!opened) open_step(j);
       st->vcycles += d->inner > 0 ? 2 * d->inner : 1;
       st->inner_iterations += d->inner;
-      {
-        TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 24));
-        launch_apply<double, RZ, double>(grid_A(C), zj, w, s);
-      }
       orthogonalise(C, K.V, ld, j, w, n, C->partials, S, m, d->orth, s);
       later_steps += j > 0;
       launch_gmres_givens(S, j, m, s);
@@ -1498,7 +1523,11 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       it++;
       k = j + 1;
       // est, resid_true, bad, happy are contiguous: one readback per iteration
-      if (!read_bytes(C, &S->est, 2 * sizeof(double) + 2 * sizeof(int))) { bad = true; break; }
+      if (!enqueue_readback(C, &S->est, 2 * sizeof(double) + 2 * sizeof(int))) { bad = true; break; }
+      // a nested run is far longer than the wait
+      opened = d->inner == 0 && j + 1 < m && it < d->maxit && run_ahead(C);
+      if (opened) open_step(j + 1);
+      if (!wait_readback(C)) { bad = true; break; }
       double est;
       int happy;
       std::memcpy(&est, C->pinned, sizeof(double));
@@ -1531,6 +1560,7 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
     if (read_bytes(C, &C->bs_in->bad, 2 * sizeof(int))) std::memcpy(v, C->pinned, sizeof v);
     st->inner_breakdowns = v[1] < 0 ? -1 : v[0] + v[1];
   }
+  HIP_OK(hipStreamSynchronize(s));  // an opening enqueued ahead may still run
   HIP_OK(hipGetLastError());
   return status;
 }
@@ -1568,16 +1598,20 @@ void bicg_enqueue_restart(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *b
 // Bi-CGSTAB): the same values, two launches and two vector passes fewer; p
 // then alternates between two buffers (blocks read the old p around their
 // tiles while others write the new one).
+// The opening (up to v and alpha) leaves x, r and the restart's state alone, so
+// it can be enqueued before the host knows whether the step before was the last.
 template <typename RZ>
-void bicg_enqueue_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x) {
+bool bicg_fuse(const ecs_ctx *C, const KrylovBufs &K) {
+  return sizeof(RZ) == 8 && K.p2 && fused_updates(C);
+}
+
+template <typename RZ>
+void bicg_open_step(ecs_ctx *C, const KrylovBufs &K) {
   const int64_t n = nn_of(C);
   hipStream_t s = C->stream;
   BicgScalars *S = C->bs;
   cplx<RZ> *ph = reinterpret_cast<cplx<RZ> *>(K.ph);
-  cplx<RZ> *sh = reinterpret_cast<cplx<RZ> *>(K.sh);
-  bool fuse = false;
-  if constexpr (sizeof(RZ) == 8) fuse = K.p2 && fused_updates(C);
-  if (fuse) {
+  if (bicg_fuse<RZ>(C, K)) {
     if constexpr (sizeof(RZ) == 8) {
       cplx<double> *p_old = C->bicg_pflip ? K.p2 : K.p, *p_new = C->bicg_pflip ? K.p : K.p2;
       const DownSrc<double> sp{kDownSrcP, K.r, p_old, K.v, p_new, S};
@@ -1592,7 +1626,16 @@ void bicg_enqueue_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x) {
     TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
     launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, s);
   }
-  if (fuse) {
+}
+
+template <typename RZ>
+void bicg_close_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x) {
+  const int64_t n = nn_of(C);
+  hipStream_t s = C->stream;
+  BicgScalars *S = C->bs;
+  cplx<RZ> *ph = reinterpret_cast<cplx<RZ> *>(K.ph);
+  cplx<RZ> *sh = reinterpret_cast<cplx<RZ> *>(K.sh);
+  if (bicg_fuse<RZ>(C, K)) {
     if constexpr (sizeof(RZ) == 8) {
       const DownSrc<double> ss{kDownSrcS, K.r, nullptr, K.v, K.s, S};
       vcycle_fused<double>(C, K.s, sh, &ss);
@@ -1606,15 +1649,6 @@ void bicg_enqueue_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x) {
     launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S, s);
   }
   launch_bicg_xr<double, RZ>(x, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, S, s);
-}
-
-// {est, bad} of the Bi-CGSTAB scalars into the pinned buffer (async)
-void bicg_enqueue_readback(ecs_ctx *C) {
-  (void)hipMemcpyAsync(C->pinned, &C->bs->est, sizeof(double) + sizeof(int), hipMemcpyDeviceToHost, C->stream);
-}
-void bicg_take_readback(const ecs_ctx *C, double *est, int *bad) {
-  std::memcpy(est, C->pinned, sizeof(double));
-  std::memcpy(bad, reinterpret_cast<const char *>(C->pinned) + sizeof(double), sizeof(int));
 }
 
 template <typename RZ>
@@ -1653,15 +1687,20 @@ ecs_status bicgstab(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, co
       }
     }
     last_restart = rt;
+    bool opened = false;
     while (it < d->maxit) {
-      bicg_enqueue_step<RZ>(C, K, x);
-      bicg_enqueue_readback(C);
+      if (!opened) bicg_open_step<RZ>(C, K);
+      bicg_close_step<RZ>(C, K, x);
+      if (!enqueue_readback(C, &S->est, sizeof(double) + sizeof(int))) break;  // est, bad
       st->vcycles += 2;
       it++;
-      if (hipStreamSynchronize(s) != hipSuccess) break;
+      opened = it < d->maxit && run_ahead(C);
+      if (opened) bicg_open_step<RZ>(C, K);
+      if (!wait_readback(C)) break;
       double est;
       int bad;
-      bicg_take_readback(C, &est, &bad);
+      std::memcpy(&est, C->pinned, sizeof(double));
+      std::memcpy(&bad, reinterpret_cast<const char *>(C->pinned) + sizeof(double), sizeof(int));
       if (d->history && it - 1 < d->history_len) d->history[it - 1] = est;
       if (bad) break;  // restart from the current iterate
       if (est <= d->rtol) break;
@@ -1669,6 +1708,7 @@ ecs_status bicgstab(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, co
     st->restarts++;
   }
   st->iterations = it;
+  HIP_OK(hipStreamSynchronize(s));  // an opening enqueued ahead may still run
   HIP_OK(hipGetLastError());
   return status;
 }
@@ -1757,7 +1797,7 @@ void batch_precond(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx<
   }
 }
 
-// one Bi-CGSTAB iteration of every slot in rs (bicg_enqueue_step per slot)
+// one Bi-CGSTAB iteration of every slot in rs (per slot that of the single solve)
 template <typename RZ>
 void batch_step(ecs_ctx *C, const KrylovBufs &K, const RhsSet &rs) {
   const int64_t n = nn_of(C);
@@ -1924,10 +1964,6 @@ ecs_status batch_solve_impl(int n, ecs_ctx *const *ctxs, const ecs_solve_desc *c
     if (need > C->ws_bytes)
       return fail(C, ECS_ENOMEM, "workspace too small for the batched solve (size it with nrhs = " +
                                      std::to_string(I.group) + " right-hand sides at once)");
-    if (!C->step_ev && hipEventCreateWithFlags(&C->step_ev, hipEventDisableTiming) != hipSuccess) {
-      C->step_ev = nullptr;
-      return fail(C, ECS_EDEVICE, "event creation failed");
-    }
     plan_batch(C, I.group, C->ws + C->hier_bytes, &I.K);
     I.C = C;
     I.d = d;
@@ -2213,6 +2249,12 @@ ecs_status ecs_create(ecs_ctx **out, int dim, const int64_t *nodes, const double
   hipError_t se;
   C->scratch = scratch_address(C->device, &se);
   if (!C->scratch) {
+    (void)hipHostFree(C->pinned);
+    delete C;
+    return ECS_EDEVICE;
+  }
+  // here rather than at first use: ecs_solve_static creates nothing
+  if (hipEventCreateWithFlags(&C->step_ev, hipEventDisableTiming) != hipSuccess) {
     (void)hipHostFree(C->pinned);
     delete C;
     return ECS_EDEVICE;
