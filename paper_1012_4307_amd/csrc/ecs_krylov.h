@@ -56,14 +56,13 @@ void launch_reduce_cols(const cplx<double> *partials, int64_t n, int ncols, cplx
 // w <- w - sum_c V_c h_c ; partials[block] = block's share of ||w||^2
 void launch_mupdate_partial(const cplx<double> *V, int64_t ldv, int ncols, const cplx<double> *h, cplx<double> *w,
                             int64_t n, cplx<double> *partials, hipStream_t s, const int *gate = nullptr);
-// delayed second pass (DCGS2): partials of [V_0..V_{ncols-1}, x]^H x and
-// [V_0..V_{ncols-1}, x]^H w (2 ncols + 2 columns, layout in kernels_blas.hip)
-void launch_mdot2_partial(const cplx<double> *V, int64_t ldv, int ncols, const cplx<double> *x,
-                          const cplx<double> *w, int64_t n, cplx<double> *partials, hipStream_t s);
-// x's second pass and w's first from the reduced products d; partials of
-// ||w||^2; hcol[0..ncols] = w's Hessenberg column
-void launch_mupdate2_partial(const cplx<double> *V, int64_t ldv, int ncols, const cplx<double> *d, cplx<double> *x,
-                             cplx<double> *w, int64_t n, cplx<double> *partials, cplx<double> *hcol, hipStream_t s);
+// Delayed second pass (DCGS2).  part 0: the products [V_0..V_{ncols-1}, x]^H x
+// and [V_0..V_{ncols-1}, x]^H w (2 ncols + 2, layout in kernels_blas.hip), reduced
+// into d2 or, on small vectors, left as partials; part 1: x's second pass and
+// w's first from them, partials of ||w||^2, hcol[0..ncols] = w's Hessenberg
+// column.  Part 1 returns the number of ||w||^2 partials for launch_gmres_end.
+int launch_dcgs2(const cplx<double> *V, int64_t ldv, int ncols, cplx<double> *x, cplx<double> *w, int64_t n,
+                 cplx<double> *partials, cplx<double> *d2, cplx<double> *hcol, hipStream_t s, int part);
 // S->reorth = (||w'||^2 = S->nrm2 < eta2 ||w||^2 = H(j+1, j)); counts it
 void launch_reorth_gate(GmresScalars *S, int j, int m, double eta2, hipStream_t s);
 template <typename R>
@@ -73,7 +72,10 @@ void launch_lincomb(const cplx<RZ> *Z, int64_t ldz, int ncols, const cplx<double
                     hipStream_t s);
 void launch_scale_dev(cplx<double> *x, int64_t n, const double *scal, hipStream_t s);
 void launch_gmres_start(GmresScalars *S, int m, hipStream_t s);
-void launch_gmres_givens(GmresScalars *S, int j, int m, hipStream_t s);
+// The end of Arnoldi step j: ||w||^2 (from nb partials of launch_dcgs2, or with
+// nb = 0 from S->nrm2), the Givens step, w scaled to norm 1.
+void launch_gmres_end(GmresScalars *S, int j, int m, const cplx<double> *partials, int nb, cplx<double> *w, int64_t n,
+                      hipStream_t s);
 void launch_gmres_backsolve(GmresScalars *S, int k, int m, hipStream_t s);
 void launch_add_h2(GmresScalars *S, int j, int m, hipStream_t s, const int *gate = nullptr);
 

@@ -1394,22 +1394,19 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
 // restart use the true residual).  z_j = M^{-1} v_j is taken before v_j's
 // second pass: FGMRES accepts any z_j, and for GMRES the mismatch is of the
 // same size.
-void orthogonalise(ecs_ctx *C, cplx<double> *V, int64_t ld, int j, cplx<double> *w, int64_t n,
-                   cplx<double> *partials, GmresScalars *S, int m, int orth, hipStream_t s) {
+// Returns how many partials of ||w||^2 launch_gmres_end has to sum (0: it is in
+// S->nrm2).
+int orthogonalise(ecs_ctx *C, cplx<double> *V, int64_t ld, int j, cplx<double> *w, int64_t n,
+                  cplx<double> *partials, GmresScalars *S, int m, int orth, hipStream_t s) {
   cplx<double> *h = S->H + (int64_t)j * (m + 1);
   if (orth == ECS_ORTH_DCGS2) {
     cplx<double> *vj = V + (int64_t)j * ld;
     {
       TimedScope ts(C, kTMdot, (double)n * 16 * (j + 2));  // read v_0..v_{j-1}, v_j, w
-      launch_mdot2_partial(V, ld, j, vj, w, n, partials, s);
+      launch_dcgs2(V, ld, j, vj, w, n, partials, S->d2, h, s, 0);
     }
-    launch_reduce_cols(partials, n, 2 * j + 2, S->d2, s);
-    {
-      TimedScope ts(C, kTMupdate, (double)n * 16 * (j + (j > 0 ? 4 : 3)));  // read v_0..v_j, w; write v_j, w
-      launch_mupdate2_partial(V, ld, j, S->d2, vj, w, n, partials, h, s);
-    }
-    launch_reduce_cols(partials, n, 1, &S->nrm2, s);
-    return;
+    TimedScope ts(C, kTMupdate, (double)n * 16 * (j + (j > 0 ? 4 : 3)));  // read v_0..v_j, w; write v_j, w
+    return launch_dcgs2(V, ld, j, vj, w, n, partials, S->d2, h, s, 1);
   }
   const bool sel = orth == ECS_ORTH_CGS2_SELECTIVE;
   const int nc = j + 1 + (sel ? 1 : 0);
@@ -1423,7 +1420,7 @@ void orthogonalise(ecs_ctx *C, cplx<double> *V, int64_t ld, int j, cplx<double> 
     launch_mupdate_partial(V, ld, j + 1, h, w, n, partials, s);
   }
   launch_reduce_cols(partials, n, 1, &S->nrm2, s);
-  if (orth == ECS_ORTH_CGS1) return;
+  if (orth == ECS_ORTH_CGS1) return 0;
   const int *gate = nullptr;
   if (sel) {
     launch_reorth_gate(S, j, m, 0.5, s);
@@ -1434,6 +1431,7 @@ void orthogonalise(ecs_ctx *C, cplx<double> *V, int64_t ld, int j, cplx<double> 
   launch_mupdate_partial(V, ld, j + 1, S->h2, w, n, partials, s, gate);
   launch_reduce_cols(partials, n, 1, &S->nrm2, s, gate);
   launch_add_h2(S, j, m, s, gate);
+  return 0;
 }
 
 // second Gram-Schmidt passes of a solve: counted on the device when selective
@@ -1516,10 +1514,9 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       if (!opened) open_step(j);
       st->vcycles += d->inner > 0 ? 2 * d->inner : 1;
       st->inner_iterations += d->inner;
-      orthogonalise(C, K.V, ld, j, w, n, C->partials, S, m, d->orth, s);
+      const int nb = orthogonalise(C, K.V, ld, j, w, n, C->partials, S, m, d->orth, s);
       later_steps += j > 0;
-      launch_gmres_givens(S, j, m, s);
-      launch_scale_dev(w, n, &S->inv, s);
+      launch_gmres_end(S, j, m, C->partials, nb, w, n, s);
       it++;
       k = j + 1;
       // est, resid_true, bad, happy are contiguous: one readback per iteration
@@ -2144,10 +2141,9 @@ ecs_status coupled_fgmres(int nb, ecs_ctx *const *ctx, const double *k2c, const 
         st->vcycles += nb;
       }
       coupled_apply(nb, ctx, k2c, zj, w, nullptr, s);
-      orthogonalise(C, B.V, ld, j, w, N, B.partials, S, m, d->orth, s);
+      const int parts = orthogonalise(C, B.V, ld, j, w, N, B.partials, S, m, d->orth, s);
       later_steps += j > 0;
-      launch_gmres_givens(S, j, m, s);
-      launch_scale_dev(w, N, &S->inv, s);
+      launch_gmres_end(S, j, m, B.partials, parts, w, N, s);
       it++;
       k = j + 1;
       if (!read_bytes(C, &S->est, 2 * sizeof(double) + 2 * sizeof(int))) { bad = true; break; }

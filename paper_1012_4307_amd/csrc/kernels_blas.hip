@@ -150,7 +150,12 @@ __global__ __launch_bounds__(BS) void k_mupdate(const cplx<double> *__restrict__
 //                   c = ncols:        sum conj(x) x        (alpha)
 //                   ncols + 1 + c:    sum conj(V_c) w      (g_c)
 //                   2 ncols + 1:      sum conj(x) w        (beta)
-// Same tiling and fixed summation order as the one-vector multi-dot.
+// Same tiling and fixed summation order as the one-vector multi-dot.  SPLIT
+// (few tiles): block row y takes the columns [CG y, CG y + CG) alone, y = 0 also
+// x itself, so the column groups of a tile run side by side instead of one
+// after the other (65^2 nodes, GMRES(30): 16.4 -> 6.7 us on average); every sum is the
+// same as without.
+template <bool SPLIT>
 __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V, int64_t ldv, int ncols,
                                               const cplx<double> *__restrict__ x, const cplx<double> *__restrict__ w,
                                               int64_t n, cplx<double> *partials) {
@@ -158,6 +163,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V
   __shared__ cplx<double> acc[BS / 64][LDA];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int nout = 2 * ncols + 2;
+  const int first = SPLIT ? (int)blockIdx.y * CG : 0, last = SPLIT ? min(first + CG, ncols) : ncols;
   for (int c = threadIdx.x; c < (BS / 64) * LDA; c += BS) acc[c / LDA][c % LDA] = mk<double>(0, 0);
   __syncthreads();
   const int64_t tile = (int64_t)BS * EPT;
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V
       xv[e] = p < n ? x[p] : mk<double>(0, 0);
       wv[e] = p < n ? w[p] : mk<double>(0, 0);
     }
-    for (int c0 = 0; c0 < ncols; c0 += CG) {
+    for (int c0 = first; c0 < last; c0 += CG) {
       cplx<double> sx[CG], sw[CG];
 #pragma unroll
       for (int g = 0; g < CG; g++) {
@@ -201,6 +207,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V
       }
     }
     // the vector x as a column: alpha = (x, x), beta = (x, w)
+    if (SPLIT && blockIdx.y != 0) continue;
     cplx<double> sa = mk<double>(0, 0), sb = mk<double>(0, 0);
 #pragma unroll
     for (int e = 0; e < EPT; e++) {
@@ -215,6 +222,8 @@ __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V
   }
   __syncthreads();
   for (int c = threadIdx.x; c < nout; c += BS) {
+    const int col = c <= ncols ? c : c - ncols - 1;  // columns of V and, at ncols, x
+    if (SPLIT && (col == ncols ? blockIdx.y != 0 : col < first || col >= last)) continue;
     cplx<double> t = mk<double>(0, 0);
     for (int q = 0; q < BS / 64; q++) t = t + acc[q][c];
     partials[(int64_t)c * gridDim.x + blockIdx.x] = t;
@@ -222,7 +231,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V
 }
 
 // Coefficients of the delayed pass from the reduced products d (layout of
-// k_mdot2) -- every block derives the same values in the same order:
+// k_mdot2, in LDS) -- every block derives the same values in the same order:
 //   nu = sqrt(alpha - sum |s_c|^2)     norm of x after its second pass
 //   h  = (beta - sum conj(s_c) g_c) / nu = (x after the pass, w)
 // With no earlier columns (the first step of a cycle, x = r / ||r|| exactly)
@@ -232,6 +241,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const cplx<double> *__restrict__ V
 __device__ inline void dcgs2_coef(const cplx<double> *d, int ncols, cplx<double> *k) {
   double ss = 0;
   cplx<double> sg = mk<double>(0, 0);
+#pragma unroll 8
   for (int c = 0; c < ncols; c++) {
     ss += abs2(d[c]);
     sg = sg + conjg(d[c]) * d[ncols + 1 + c];
@@ -248,19 +258,40 @@ __device__ inline void dcgs2_coef(const cplx<double> *d, int ncols, cplx<double>
 //   w <- w - sum_c V_c g_c - h x            (w's first pass against V and the new x)
 // partials[block] = the block's share of ||w||^2; block 0 stores the
 // Hessenberg column H(0..ncols, j) = (g_0, ..., g_{ncols-1}, h).
+// A thread holds E nodes, the columns come in groups of G whose loads are in
+// flight together: 4 x 4 streams a large vector; 1 x 16 gives a small one four
+// times the blocks and a quarter of the round trips (65^2 nodes, GMRES(30): 13.2
+// -> 6.0 us on average, the products' reduction, 3.5 us, included).  FOLD (few tiles): the products come as the
+// multi-dot's partials of nb tiles, summed here by every block.
+template <int E, int G, bool FOLD>
 __global__ __launch_bounds__(BS) void k_mupdate2(const cplx<double> *__restrict__ V, int64_t ldv, int ncols,
-                                                 const cplx<double> *__restrict__ d, cplx<double> *__restrict__ x,
-                                                 cplx<double> *__restrict__ w, int64_t n, cplx<double> *partials,
-                                                 cplx<double> *hcol) {
-  __shared__ cplx<double> ss[kMaxRestart], gs[kMaxRestart];
+                                                 const cplx<double> *__restrict__ d, int nb,
+                                                 cplx<double> *__restrict__ x, cplx<double> *__restrict__ w,
+                                                 int64_t n, cplx<double> *partials, cplx<double> *hcol) {
+  __shared__ cplx<double> ds[2 * kMaxRestart + 2];
   __shared__ cplx<double> lds[BS / 64];
   __shared__ cplx<double> kc[2];
-  for (int c = threadIdx.x; c < ncols; c += BS) {
-    ss[c] = d[c];
-    gs[c] = d[ncols + 1 + c];
+  const int nout = 2 * ncols + 2;
+  if constexpr (FOLD) {
+    for (int c0 = 0; c0 < nout; c0 += BS / 4) {  // four lanes a column
+      const int c = c0 + ((int)threadIdx.x >> 2);
+      cplx<double> t = mk<double>(0, 0);
+      if (c < nout)
+        for (int q = threadIdx.x & 3; q < nb; q += 4) t = t + d[(int64_t)c * nb + q];
+#pragma unroll
+      for (int o = 1; o < 4; o <<= 1) {
+        t.re += __shfl_xor(t.re, o, 64);
+        t.im += __shfl_xor(t.im, o, 64);
+      }
+      if (c < nout && (threadIdx.x & 3) == 0) ds[c] = t;
+    }
+  } else {
+    for (int c = threadIdx.x; c < nout; c += BS) ds[c] = d[c];
   }
-  if (threadIdx.x == 0) dcgs2_coef(d, ncols, kc);
   __syncthreads();
+  if (threadIdx.x == 0) dcgs2_coef(ds, ncols, kc);
+  __syncthreads();
+  const cplx<double> *ss = ds, *gs = ds + ncols + 1;
   const double inv_nu = kc[0].re;
   const bool pass = kc[0].im != 0;
   const cplx<double> hx = kc[1];
@@ -269,35 +300,48 @@ __global__ __launch_bounds__(BS) void k_mupdate2(const cplx<double> *__restrict_
     else if ((int)threadIdx.x == ncols) hcol[ncols] = kc[1];
   }
   double nrm = 0;
-  const int64_t tile = (int64_t)BS * EPT;
+  const int64_t tile = (int64_t)BS * E;
   for (int64_t base = (int64_t)blockIdx.x * tile; base < n; base += (int64_t)gridDim.x * tile) {
-    cplx<double> xv[EPT], wv[EPT];
+    cplx<double> xv[E], wv[E];
 #pragma unroll
-    for (int e = 0; e < EPT; e++) {
+    for (int e = 0; e < E; e++) {
       const int64_t p = base + e * BS + threadIdx.x;
       xv[e] = p < n ? x[p] : mk<double>(0, 0);
       wv[e] = p < n ? w[p] : mk<double>(0, 0);
     }
-    for (int c0 = 0; c0 < ncols; c0 += CG) {
+    for (int c0 = 0; c0 < ncols; c0 += G) {
+      if constexpr (E == 1) {
+        const int64_t p = base + threadIdx.x < n ? base + threadIdx.x : n - 1;
+        cplx<double> v[G];
 #pragma unroll
-      for (int g = 0; g < CG; g++) {
-        if (c0 + g < ncols) {
-          const cplx<double> *vc = V + (int64_t)(c0 + g) * ldv;
-          const cplx<double> sc = pass ? ss[c0 + g] : mk<double>(0, 0), gc = gs[c0 + g];
+        for (int g = 0; g < G; g++) v[g] = V[(int64_t)(c0 + g < ncols ? c0 + g : c0) * ldv + p];
 #pragma unroll
-          for (int e = 0; e < EPT; e++) {
-            const int64_t p = base + e * BS + threadIdx.x;
-            if (p < n) {
-              const cplx<double> v = vc[p];
-              xv[e] = xv[e] - v * sc;
-              wv[e] = wv[e] - v * gc;
+        for (int g = 0; g < G; g++)
+          if (c0 + g < ncols) {
+            xv[0] = xv[0] - v[g] * (pass ? ss[c0 + g] : mk<double>(0, 0));
+            wv[0] = wv[0] - v[g] * gs[c0 + g];
+          }
+      } else {
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+          if (c0 + g < ncols) {
+            const cplx<double> *vc = V + (int64_t)(c0 + g) * ldv;
+            const cplx<double> sc = pass ? ss[c0 + g] : mk<double>(0, 0), gc = gs[c0 + g];
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+              const int64_t p = base + e * BS + threadIdx.x;
+              if (p < n) {
+                const cplx<double> v = vc[p];
+                xv[e] = xv[e] - v * sc;
+                wv[e] = wv[e] - v * gc;
+              }
             }
           }
         }
       }
     }
 #pragma unroll
-    for (int e = 0; e < EPT; e++) {
+    for (int e = 0; e < E; e++) {
       const int64_t p = base + e * BS + threadIdx.x;
       if (p < n) {
         const cplx<double> xn = inv_nu * xv[e];
@@ -361,54 +405,119 @@ __global__ void k_gmres_start(GmresScalars *S, int m) {
 // Arnoldi step j: column j of the Hessenberg matrix holds h_{0..j,j} from the
 // orthogonalisation; h_{j+1,j} = sqrt(norm2).  Apply the stored Givens
 // rotations, form the new one, update g and the residual estimate |g_{j+1}|.
-__global__ void k_gmres_givens(GmresScalars *S, int j, int m) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Called by a whole block (at least j + 2 threads): the column and the
+// rotations are staged in LDS (reading them from memory one by one took 4 to 7
+// us), the recurrence runs in thread 0.
+struct GivensLds {
+  cplx<double> h[kMaxRestart + 1], c[kMaxRestart], s[kMaxRestart];
+};
+__device__ __forceinline__ void givens_step(GmresScalars *S, GivensLds &L, int j, int m, double norm2) {
   cplx<double> *h = S->H + (int64_t)j * (m + 1);
-  double hn = sqrt(S->nrm2.re);
-  h[j + 1] = mk<double>(hn, 0);
-  S->inv = hn > 0 ? 1.0 / hn : 0.0;
-  for (int i = 0; i < j; i++) {
-    cplx<double> c = S->cs[i], s = S->sn[i];
-    cplx<double> t = conjg(c) * h[i] + s * h[i + 1];
-    h[i + 1] = (c * h[i + 1]) - (conjg(s) * h[i]);
-    h[i] = t;
+  const int t = threadIdx.x;
+  if (t <= j) L.h[t] = h[t];
+  if (t < j) {
+    L.c[t] = S->cs[t];
+    L.s[t] = S->sn[t];
   }
-  // new rotation zeroing h[j+1]: c = |a|/r (real), s = (a/|a|) conj(b) / r
-  cplx<double> a = h[j], b = h[j + 1];
-  double na = sqrt(abs2(a)), nb = sqrt(abs2(b));
-  cplx<double> c, s;
-  if (nb == 0) {
-    c = mk<double>(1, 0); s = mk<double>(0, 0);
-  } else if (na == 0) {
-    c = mk<double>(0, 0); s = mk<double>(1, 0);
-  } else {
-    double r = sqrt(na * na + nb * nb);
-    c = mk<double>(na / r, 0);
-    s = (1.0 / (na * r)) * (a * conjg(b));
+  __syncthreads();
+  if (t == 0) {
+    const double hn = sqrt(norm2);
+    L.h[j + 1] = mk<double>(hn, 0);
+    S->inv = hn > 0 ? 1.0 / hn : 0.0;
+    cplx<double> lo = L.h[0];
+    for (int i = 0; i < j; i++) {
+      const cplx<double> c = L.c[i], s = L.s[i], hi = L.h[i + 1];
+      L.h[i] = conjg(c) * lo + s * hi;
+      lo = (c * hi) - (conjg(s) * lo);
+    }
+    // new rotation zeroing h[j+1]: c = |a|/r (real), s = (a/|a|) conj(b) / r
+    const cplx<double> a = lo, b = L.h[j + 1];
+    const double na = sqrt(abs2(a)), nb = sqrt(abs2(b));
+    cplx<double> c, s;
+    if (nb == 0) {
+      c = mk<double>(1, 0); s = mk<double>(0, 0);
+    } else if (na == 0) {
+      c = mk<double>(0, 0); s = mk<double>(1, 0);
+    } else {
+      const double r = sqrt(na * na + nb * nb);
+      c = mk<double>(na / r, 0);
+      s = (1.0 / (na * r)) * (a * conjg(b));
+    }
+    S->cs[j] = c;
+    S->sn[j] = s;
+    L.h[j] = conjg(c) * a + s * b;
+    L.h[j + 1] = mk<double>(0, 0);
+    const cplx<double> gj = S->g[j];
+    S->g[j] = conjg(c) * gj;
+    const cplx<double> gn = mk<double>(0, 0) - conjg(s) * gj;
+    S->g[j + 1] = gn;
+    S->est = sqrt(abs2(gn)) / S->bnorm;
+    S->bad = !(S->est == S->est) || isinf(S->est);
+    S->happy = hn == 0;
   }
-  S->cs[j] = c;
-  S->sn[j] = s;
-  h[j] = conjg(c) * a + s * b;
-  h[j + 1] = mk<double>(0, 0);
-  cplx<double> gj = S->g[j];
-  S->g[j] = conjg(c) * gj;
-  S->g[j + 1] = mk<double>(0, 0) - conjg(s) * gj;
-  S->est = sqrt(abs2(S->g[j + 1])) / S->bnorm;
-  S->bad = !(S->est == S->est) || isinf(S->est);
-  S->happy = hn == 0;
+  __syncthreads();
+  if (t <= j + 1) h[t] = L.h[t];
 }
 
-// y = R^{-1} g for the first k columns (upper triangular from the rotated H)
-__global__ void k_gmres_backsolve(GmresScalars *S, int k, int m) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  for (int r = k - 1; r >= 0; r--) {
-    cplx<double> s = S->g[r];
-    for (int c = r + 1; c < k; c++) s = s - S->H[(int64_t)c * (m + 1) + r] * S->y[c];
-    const cplx<double> d = S->H[(int64_t)r * (m + 1) + r];
-    // a zero pivot only arises when the preconditioned vector vanished (w = 0);
-    // that direction then carries no information and gets a zero coefficient
-    S->y[r] = abs2(d) > 0 ? cdiv(s, d) : mk<double>(0, 0);
+// The end of an Arnoldi step.  partials: the nb blocks' shares of ||w||^2 (nb =
+// 0: it is in S->nrm2).  k_gmres_end is one block: the sum and the Givens step.
+// k_gmres_end_scale (few partials) also scales w: every block sums them, block 0
+// takes the Givens step (65^2: 4.0 us for what took three launches, 10.4 us).
+__device__ __forceinline__ double norm2_of(const cplx<double> *partials, int nb, cplx<double> *lds, double *out) {
+  cplx<double> s = block_sum(strided_sum(partials, nb), lds);
+  if (threadIdx.x == 0) *out = s.re;
+  __syncthreads();
+  return *out;
+}
+__global__ __launch_bounds__(BS) void k_gmres_end(GmresScalars *S, int j, int m, const cplx<double> *partials,
+                                                  int nb) {
+  __shared__ cplx<double> lds[BS / 64];
+  __shared__ double nrm;
+  __shared__ GivensLds L;
+  givens_step(S, L, j, m, nb > 0 ? norm2_of(partials, nb, lds, &nrm) : S->nrm2.re);
+}
+__global__ __launch_bounds__(BS) void k_gmres_end_scale(GmresScalars *S, int j, int m, const cplx<double> *partials,
+                                                        int nb, cplx<double> *__restrict__ w, int64_t n) {
+  __shared__ cplx<double> lds[BS / 64];
+  __shared__ double nrm;
+  __shared__ GivensLds L;
+  const int64_t p = (int64_t)blockIdx.x * BS + threadIdx.x;
+  const cplx<double> wv = w[p < n ? p : n - 1];
+  const double norm2 = norm2_of(partials, nb, lds, &nrm), hn = sqrt(norm2);
+  if (p < n) w[p] = (hn > 0 ? 1.0 / hn : 0.0) * wv;
+  if (blockIdx.x == 0) givens_step(S, L, j, m, norm2);
+}
+
+// y = R^{-1} g for the first k columns (upper triangular from the rotated H).
+// One wave, lane r holding row r's remainder: column c's unknown is solved by
+// lane c, broadcast, and taken off the rows above, whose entries are read ahead
+// of the chain: 4 us for 30 columns (one thread reading them in turn took 29 to 52).
+__global__ __launch_bounds__(64) void k_gmres_backsolve(GmresScalars *S, int k, int m) {
+  static_assert(kMaxRestart <= 64, "a lane per row");
+  const int r = threadIdx.x;
+  const cplx<double> *H = S->H;
+  cplx<double> g = r < k ? S->g[r] : mk<double>(0, 0), y = mk<double>(0, 0);
+  const cplx<double> d = r < k ? H[(int64_t)r * (m + 1) + r] : mk<double>(0, 0);
+  constexpr int A = 8;  // columns read ahead
+  for (int c0 = k - 1; c0 >= 0; c0 -= A) {
+    cplx<double> col[A];
+#pragma unroll
+    for (int q = 0; q < A; q++) {
+      const int c = c0 - q;
+      col[q] = c >= 0 && r < c ? H[(int64_t)c * (m + 1) + r] : mk<double>(0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < A; q++) {
+      const int c = c0 - q;
+      if (c < 0) break;
+      // a zero pivot only arises when the preconditioned vector vanished (w = 0);
+      // that direction then carries no information and gets a zero coefficient
+      if (r == c) y = abs2(d) > 0 ? cdiv(g, d) : mk<double>(0, 0);
+      const cplx<double> yc = mk<double>(__shfl(y.re, c, 64), __shfl(y.im, c, 64));
+      g = g - col[q] * yc;
+    }
   }
+  if (r < k) S->y[r] = y;
 }
 
 // second Gram-Schmidt pass: H(:, j) += h2 (when the pass ran)
@@ -753,14 +862,53 @@ void launch_mupdate_partial(const cplx<double> *V, int64_t ldv, int ncols, const
   launch_k(k_mupdate, dim3(red_blocks(n)), dim3(BS), 0, s, V, ldv, ncols, h, w, n, partials, gate);
 }
 
-void launch_mdot2_partial(const cplx<double> *V, int64_t ldv, int ncols, const cplx<double> *x,
-                          const cplx<double> *w, int64_t n, cplx<double> *partials, hipStream_t s) {
-  launch_k(k_mdot2, dim3(red_blocks(n)), dim3(BS), 0, s, V, ldv, ncols, x, w, n, partials);
+// Up to this many multi-dot tiles (1024 nodes each) the column groups run side
+// by side: beyond, the tiles alone fill the chip and the groups would only read
+// x and w again.
+constexpr int kSplitTiles = 512;
+// Up to this many, the update pass sums the tiles' partials itself.
+constexpr int kFoldTiles = 32;
+// its own partials, apart from the multi-dot's that it may be reading
+constexpr int64_t kNormPartials = (int64_t)kRedBlocks * 64;
+
+int launch_dcgs2(const cplx<double> *V, int64_t ldv, int ncols, cplx<double> *x, cplx<double> *w, int64_t n,
+                 cplx<double> *partials, cplx<double> *d2, cplx<double> *hcol, hipStream_t s, int part) {
+  const int tiles = red_blocks(n);
+  const bool small = tiles <= kSplitTiles, fold = tiles <= kFoldTiles;
+  if (part == 0) {
+    if (small)
+      launch_k(k_mdot2<true>, dim3(tiles, ncols > 0 ? (ncols + CG - 1) / CG : 1), dim3(BS), 0, s, V, ldv, ncols,
+               (const cplx<double> *)x, (const cplx<double> *)w, n, partials);
+    else
+      launch_k(k_mdot2<false>, dim3(tiles), dim3(BS), 0, s, V, ldv, ncols, (const cplx<double> *)x,
+               (const cplx<double> *)w, n, partials);
+    if (!fold) launch_reduce_cols(partials, n, 2 * ncols + 2, d2, s);
+    return 0;
+  }
+  cplx<double> *np = partials + kNormPartials;
+  const int nb = small ? (int)((n + BS - 1) / BS) : tiles;
+  if (fold)
+    launch_k((k_mupdate2<1, 16, true>), dim3(nb), dim3(BS), 0, s, V, ldv, ncols, (const cplx<double> *)partials, tiles,
+             x, w, n, np, hcol);
+  else if (small)
+    launch_k((k_mupdate2<1, 16, false>), dim3(nb), dim3(BS), 0, s, V, ldv, ncols, (const cplx<double> *)d2, 0, x, w, n,
+             np, hcol);
+  else
+    launch_k((k_mupdate2<EPT, CG, false>), dim3(nb), dim3(BS), 0, s, V, ldv, ncols, (const cplx<double> *)d2, 0, x, w,
+             n, np, hcol);
+  return nb;
 }
 
-void launch_mupdate2_partial(const cplx<double> *V, int64_t ldv, int ncols, const cplx<double> *d, cplx<double> *x,
-                             cplx<double> *w, int64_t n, cplx<double> *partials, cplx<double> *hcol, hipStream_t s) {
-  launch_k(k_mupdate2, dim3(red_blocks(n)), dim3(BS), 0, s, V, ldv, ncols, d, x, w, n, partials, hcol);
+void launch_gmres_end(GmresScalars *S, int j, int m, const cplx<double> *partials, int nb, cplx<double> *w, int64_t n,
+                      hipStream_t s) {
+  // up to one partial per thread (n <= 65536) every block sums them
+  if (nb > 0 && nb <= BS) {
+    launch_k(k_gmres_end_scale, dim3((unsigned)((n + BS - 1) / BS)), dim3(BS), 0, s, S, j, m, partials + kNormPartials,
+             nb, w, n);
+    return;
+  }
+  launch_k(k_gmres_end, dim3(1), dim3(BS), 0, s, S, j, m, partials + kNormPartials, nb);
+  launch_scale_dev(w, n, &S->inv, s);
 }
 
 void launch_reorth_gate(GmresScalars *S, int j, int m, double eta2, hipStream_t s) {
@@ -786,11 +934,8 @@ void launch_scale_dev(cplx<double> *x, int64_t n, const double *scal, hipStream_
 void launch_gmres_start(GmresScalars *S, int m, hipStream_t s) {
   launch_k(k_gmres_start, dim3(1), dim3(1), 0, s, S, m);
 }
-void launch_gmres_givens(GmresScalars *S, int j, int m, hipStream_t s) {
-  launch_k(k_gmres_givens, dim3(1), dim3(1), 0, s, S, j, m);
-}
 void launch_gmres_backsolve(GmresScalars *S, int k, int m, hipStream_t s) {
-  launch_k(k_gmres_backsolve, dim3(1), dim3(1), 0, s, S, k, m);
+  launch_k(k_gmres_backsolve, dim3(1), dim3(64), 0, s, S, k, m);
 }
 
 void launch_add_h2(GmresScalars *S, int j, int m, hipStream_t s, const int *gate) {

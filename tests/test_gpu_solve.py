@@ -514,3 +514,24 @@ def test_3d_solve_129_residual_by_oracle():
     res = oracle_resid(P, to_np(x), w.rhs[0])
     print(f"129^3: {st['iterations']} iterations, oracle residual {res:.3e}", flush=True)
     assert res <= 1.05e-8
+
+
+@pytest.mark.parametrize("n,coarsest,restart", [(9, 3, 1), (9, 3, 64), (177, 12, 64), (193, 4, 30), (241, 16, 5),
+                                                (257, 5, 30), (705, 12, 30), (769, 7, 30)])
+def test_arnoldi_kernels_by_size(n, coarsest, restart):
+    """Both sides of every size at which the Arnoldi step changes kernels (32 and
+    512 multi-dot tiles, 256 norm partials; 81 nodes: less than a tile), restarts 1
+    and 64: the true residual by the oracle's operator, and the delayed pass
+    within 5% of the iterations of the second pass on every step, whose kernels
+    do not change."""
+    w = W.coulomb(E=1.0, n=n, coarsest=coarsest)
+    P = oracle_for(w)
+    b = w.rhs[0]
+    its = {}
+    for orth in ("dcgs2", "cgs2"):
+        kr = E.Krylov(method="fgmres", restart=restart, rtol=1e-9, maxit=3000, orth=orth)
+        x, st = gpu_for(w, "f64", krylov=kr).solve(to_gpu(b), krylov=kr)
+        assert st["status"] == 0, (orth, st)
+        assert oracle_resid(P, to_np(x), b) <= 1.05e-9, orth
+        its[orth] = st["iterations"]
+    assert abs(its["dcgs2"] - its["cgs2"]) <= max(2, 0.05 * its["cgs2"]), its
