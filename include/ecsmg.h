@@ -342,8 +342,8 @@ ecs_status ecs_timing_calibrate(ecs_ctx *ctx, int launches);
  *   pair_grid   levels above the tail with at most this many nodes per axis
  *               run two per kernel (pairs counted from the tail up); 0: none
  *   fuse_updates  1: the FP32 Bi-CGSTAB inside FGMRES (desc->inner > 0), and
- *               the Bi-CGSTAB solve with the FP64 cycle on grids of at most
- *               1025^2 nodes, form their p and s updates inside the finest
+ *               the Bi-CGSTAB solve (single and batched) with the FP64 cycle
+ *               on grids of at most 1025^2 nodes, form their p and s updates inside the finest
  *               level's down kernel when that level has its own down kernel
  *               and the cycle is not launched as a graph
  *               (ECS_GRAPHS_ALWAYS), with the same values as the separate

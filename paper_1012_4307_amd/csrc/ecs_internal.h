@@ -208,11 +208,16 @@ struct DownSrc {
   int mode;                    // kDownSrcP or kDownSrcS
   const cplx<R> *r, *p, *v;    // p unused for kDownSrcS
   cplx<R> *out;
+  // the step's scalars (BicgFold): with nb > 0 partials of the dot products
+  // behind them are pending
   const BicgScalars *S;
+  BicgScalars *S_out;
+  const cplx<double> *partials;
+  int nb;
 };
 template <typename R>
 void launch_down_rb_src(const Grid<R> &fine, const Grid<R> &coarse, const DownSrc<R> &src, cplx<R> *rc, R omega,
-                        int rows, hipStream_t s);
+                        int rows, hipStream_t s, const RhsSet &rs = one_rhs());
 template <typename R>
 void launch_up_rb(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u_out,
                   R omega, int rows, hipStream_t s, const RhsSet &rs = one_rhs());

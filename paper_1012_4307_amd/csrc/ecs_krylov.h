@@ -42,6 +42,30 @@ struct BicgScalars {
 
 enum { kBicgAlpha = 1, kBicgOmega = 2, kBicgInit = 4, kBicgNormRho = 5 };
 
+// Scalars handed to a kernel that follows a dot product of the step.  nb = 0:
+// they are in *in.  Otherwise the dot products are still partials (nb entries
+// each) and *in holds the scalars before them: the kernel's blocks all sum the
+// partials, in the order of the one-block reduction, and take the update of the
+// recurrence themselves; block 0 stores the updated scalars in *out (another
+// struct than *in, which the other blocks read).  A step goes through three
+// structs per right-hand side: stage 0 (beta; the estimate the host reads), 1
+// (alpha), 2 (omega), kMaxRhs structs apart in a context's array.
+struct BicgFold {
+  const BicgScalars *in;
+  BicgScalars *out;
+  const cplx<double> *partials;
+  int nb;
+};
+inline BicgFold bicg_scalars(const BicgScalars *S) { return BicgFold{S, nullptr, nullptr, 0}; }
+// Partials of at most this many blocks (three a thread) are folded into the
+// kernels that follow, saving a launch: 4.4 us and a gap against the partials'
+// trip from L2 by every block, 9 KB a block and dot product at 1025^2; at 2049^2
+// (2210 blocks) that trip would cost more than the launch.
+constexpr int kFoldPartials = 768;
+// the dot products of the step's last kernel lie this far into the partials, so
+// that the kernel can read those of the matvec before it
+constexpr int kLastPartials = kRhsPartials / 2;
+
 int reduction_blocks(int64_t n);
 
 // The Arnoldi kernels take an optional gate: with gate != null they do
@@ -86,35 +110,47 @@ void launch_pairdot(const cplx<R> *x0, const cplx<R> *y0, const cplx<R> *x1, con
 // rhs_stride(n) elements in, the scalars at S + q and the partials
 // q kRhsPartials entries in.
 template <typename R>
-void launch_bicg_p(cplx<R> *p, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgScalars *S, hipStream_t s,
+void launch_bicg_p(cplx<R> *p, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgFold &f, hipStream_t s,
                    const RhsSet &rs = one_rhs());
 template <typename R>
-void launch_bicg_s(cplx<R> *sv, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgScalars *S, hipStream_t s,
+void launch_bicg_s(cplx<R> *sv, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgFold &f, hipStream_t s,
                    const RhsSet &rs = one_rhs());
 // x += alpha ph + omega sh; r = s - omega t; then ||r||^2 and (r^, r) reduce
-// (fixed-order second stage) into est and the next step's beta
+// (fixed-order second stage) into est and the next step's beta: from f (omega)
+// to S
 template <typename R, typename RZ>
 void launch_bicg_xr(cplx<R> *x, const cplx<RZ> *ph, const cplx<RZ> *sh, cplx<R> *r, const cplx<R> *sv,
-                    const cplx<R> *t, const cplx<R> *rh, int64_t n, cplx<double> *partials, BicgScalars *S,
-                    hipStream_t s, const RhsSet &rs = one_rhs());
+                    const cplx<R> *t, const cplx<R> *rh, int64_t n, cplx<double> *partials, const BicgFold &f,
+                    BicgScalars *S2, BicgScalars *S, hipStream_t s, const RhsSet &rs = one_rhs());
 // The nested Bi-CGSTAB with its x update deferred: r = s - omega t, the
-// same reductions as launch_bicg_xr, and (alpha, omega) of the step stored at
+// same reductions as launch_bicg_xr (left to the next kernel when there are few
+// partials: the result is its BicgFold), and (alpha, omega) of the step stored at
 // coef[0..1]; later x += sum_i alpha_i p^_i + omega_i s^_i over `count`
 // stored steps (ld elements apart), in step order, each step the one-step
 // update's expression.
 template <typename R>
-void launch_bicg_r(cplx<R> *r, const cplx<R> *sv, const cplx<R> *t, const cplx<R> *rh, int64_t n,
-                   cplx<double> *partials, BicgScalars *S, cplx<double> *coef, hipStream_t s);
+BicgFold launch_bicg_r(cplx<R> *r, const cplx<R> *sv, const cplx<R> *t, const cplx<R> *rh, int64_t n,
+                       cplx<double> *partials, const BicgFold &f, BicgScalars *S2, BicgScalars *S,
+                       cplx<double> *coef, hipStream_t s);
 template <typename R>
 void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_t ld, int count,
                         const cplx<double> *coef, int64_t n, hipStream_t s);
 // y = A x with a fused dot product: kBicgAlpha -> (d0, y) gives alpha;
 // kBicgOmega -> (y, d0) and (y, y) give omega (multigrid side, kernels_mg.hip)
-void launch_bicg_final(const cplx<double> *partials, int nblocks, int npairs, BicgScalars *S, int mode,
-                       hipStream_t s, const RhsSet &rs = one_rhs());
+// The one-block reduction and update of the recurrence, from *in to *out.
+void launch_bicg_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in, BicgScalars *out,
+                       int mode, hipStream_t s, const RhsSet &rs = one_rhs());
+// few partials: left to the next kernel (the BicgFold returned), else reduced to *out
+inline BicgFold bicg_fold_or_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in,
+                                   BicgScalars *out, int mode, hipStream_t s, const RhsSet &rs = one_rhs()) {
+  if (nblocks <= kFoldPartials) return BicgFold{in, out, partials, nblocks};
+  launch_bicg_final(partials, nblocks, npairs, in, out, mode, s, rs);
+  return bicg_scalars(out);
+}
 template <typename R, typename RI>
-void launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
-                      cplx<double> *partials, BicgScalars *S, hipStream_t s, const RhsSet &rs = one_rhs());
+BicgFold launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
+                          cplx<double> *partials, const BicgScalars *in, BicgScalars *out, hipStream_t s,
+                          const RhsSet &rs = one_rhs());
 
 template <typename RI, typename RO>
 void launch_cast(const cplx<RI> *x, cplx<RO> *y, int64_t n, hipStream_t s, const RhsSet &rs = one_rhs());

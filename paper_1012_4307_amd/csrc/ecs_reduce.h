@@ -119,4 +119,46 @@ __device__ inline void bicg_update(BicgScalars *S, int mode, cplx<double> d0, cp
   }
 }
 
+// A following kernel's share of a reduction (BicgFold), in two parts so that the
+// kernel can issue its own loads in between: each thread's partials, then the
+// sums (strided_sum and block_sum over the same entries: the one-block
+// reduction's bits) and the update, which every thread reads from LDS.
+constexpr int kFoldU = kFoldPartials / kRedThreads;
+template <int NP>
+struct FoldLoads {
+  cplx<double> v[NP][kFoldU];
+};
+template <int NP>
+__device__ __forceinline__ FoldLoads<NP> fold_load(const cplx<double> *partials, int nb) {
+  FoldLoads<NP> L;
+#pragma unroll
+  for (int q = 0; q < NP; q++)
+#pragma unroll
+    for (int u = 0; u < kFoldU; u++) {
+      const int b = (int)threadIdx.x + u * kRedThreads;
+      L.v[q][u] = partials[(int64_t)q * nb + (b < nb ? b : 0)];
+    }
+  return L;
+}
+template <int NP>
+__device__ __forceinline__ void fold_finish(const FoldLoads<NP> &L, const BicgScalars *in, BicgScalars *out, int nb,
+                                            int mode, cplx<double> *red, BicgScalars *sh) {
+  cplx<double> d[2] = {mk<double>(0, 0), mk<double>(0, 0)};
+#pragma unroll
+  for (int q = 0; q < NP; q++) {
+    cplx<double> s = mk<double>(0, 0);
+#pragma unroll
+    for (int u = 0; u < kFoldU; u++)
+      if ((int)threadIdx.x + u * kRedThreads < nb) s = s + L.v[q][u];
+    d[q] = block_sum(s, red);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    *sh = *in;
+    bicg_update(sh, mode, d[0], d[1]);
+    if (blockIdx.x == 0) *out = *sh;
+  }
+  __syncthreads();
+}
+
 }  // namespace ecs

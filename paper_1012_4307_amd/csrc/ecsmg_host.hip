@@ -351,8 +351,8 @@ size_t plan_layout(ecs_ctx *C, Carver &cv) {
   C->partials = cv.take<cplx<double>>((size_t)kRedBlocks * (2 * kMaxRestart + 2));
   C->dscal = cv.take<double>(kRedBlocks + 8);
   C->gs = cv.take<GmresScalars>(1);
-  C->bs = cv.take<BicgScalars>(kMaxRhs);  // one per right-hand side slot of the batched solve
-  C->bs_in = cv.take<BicgScalars>(1);
+  C->bs = cv.take<BicgScalars>(3 * kMaxRhs);  // per stage, one per right-hand side slot of the batched solve
+  C->bs_in = cv.take<BicgScalars>(3);
   return cv.off;
 }
 
@@ -402,6 +402,14 @@ struct KrylovBufs {
   void *lb[kMaxLev] = {}, *lt[kMaxLev] = {}, *lu[kMaxLev] = {};
 };
 
+// The outer FP64 Bi-CGSTAB forms p and s inside the cycle (bicg_open_step,
+// bicg_close_step, batch_step) up to 1025^2 finest nodes, where a launch is short
+// enough that the two it saves count: 2-3% faster at 513^2 and 1025^2.  At 2049^2 the fused FP64 kernels (121
+// VGPRs for p against 84 for the plain down kernel) lose occupancy on a level
+// that is bandwidth-bound: 1-2% slower for every tile height, so the separate
+// update kernels stay there.
+constexpr int64_t kFuse64MaxNodes = int64_t(1025) * 1025;
+
 // Storage of the batched Bi-CGSTAB for `slots` right-hand sides at once (one
 // group of a system's right-hand sides; see batch_solve_impl).
 size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
@@ -422,6 +430,7 @@ size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
   K->ph = cv.take<char>(sn * zs);
   K->sh = cv.take<char>(sn * zs);
   K->b32 = f32 ? cv.take<char>(sn * zs) : nullptr;
+  K->p2 = !f32 && n <= kFuse64MaxNodes ? cv.take<cplx<double>>(sn) : nullptr;
   for (int l = 0; l < C->nlev; l++) {
     const int64_t sl = rhs_stride(C->hl[l].nn) * slots;
     K->lt[l] = cv.take<char>(sl * zs);
@@ -430,14 +439,6 @@ size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
   }
   return cv.off;
 }
-
-// The outer FP64 Bi-CGSTAB forms p and s inside the cycle (bicg_open_step,
-// bicg_close_step) up to 1025^2 finest nodes, where a launch is short enough that the two it saves count: measured
-// 2-3% faster at 513^2 and 1025^2.  At 2049^2 the fused FP64 kernels (121
-// VGPRs for p against 84 for the plain down kernel) lose occupancy on a level
-// that is bandwidth-bound: 1-2% slower for every tile height, so the separate
-// update kernels stay there.
-constexpr int64_t kFuse64MaxNodes = int64_t(1025) * 1025;
 
 size_t plan_krylov(const ecs_ctx *C, const ecs_solve_desc *d, char *base, KrylovBufs *K) {
   Carver cv(base);
@@ -807,8 +808,8 @@ ecs_status setup(ecs_ctx *C) {
   use_dense(C, fused_vcycle(C) ? fused_dense_level(C) : general_dense_level(C));
   // Krylov scalars start cleared
   HIP_OK(hipMemsetAsync(C->gs, 0, sizeof(GmresScalars), s));
-  HIP_OK(hipMemsetAsync(C->bs, 0, kMaxRhs * sizeof(BicgScalars), s));
-  HIP_OK(hipMemsetAsync(C->bs_in, 0, sizeof(BicgScalars), s));
+  HIP_OK(hipMemsetAsync(C->bs, 0, 3 * kMaxRhs * sizeof(BicgScalars), s));
+  HIP_OK(hipMemsetAsync(C->bs_in, 0, 3 * sizeof(BicgScalars), s));
   HIP_OK(hipStreamSynchronize(s));
   HIP_OK(hipGetLastError());
   return ECS_OK;
@@ -1072,9 +1073,9 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
       // reads the vectors b is formed from (r, p, v or r, v) and k^2;
       // writes b and the coarse residual
       const bool pm = src->mode == kDownSrcP;
-      TimedScope ts(C, pm ? kTDownP : kTDownS, (double)C->hl[0].nn * sizeof(R) * (pm ? 9.5 : 7.5));
+      TimedScope ts(C, pm ? kTDownP : kTDownS, nr * C->hl[0].nn * sizeof(R) * (pm ? 9.5 : 7.5));
       launch_down_rb_src<R>(grid_M<R>(C, 0), grid_M<R>(C, 1), *src, B.b[1], om, small(0) ? 2 : T.down_rows,
-                            C->stream);
+                            C->stream, rs);
       l++;
       continue;
     }
@@ -1350,29 +1351,33 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
   // x = sum of alpha_i p^_i + omega_i s^_i: each step keeps its p^, s^ and
   // scalars, and x is updated once per K.fdefer steps (the same values as
   // a one-step update, in half its traffic per step)
+  BicgScalars *S1 = S + 1, *S2 = S + 2;  // after alpha, after omega
+  BicgFold beta = bicg_scalars(S);
   for (int it = 0; it < iters; it++) {
     const int slot = it % K.fdefer;
     cplx<R> *fph = ph0 + (int64_t)slot * K.ld, *fsh = sh0 + (int64_t)slot * K.ld;
     if (fuse) {
-      const DownSrc<R> sp{kDownSrcP, fr, p_old, fv, p_new, S};
+      const DownSrc<R> sp{kDownSrcP, fr, p_old, fv, p_new, beta.in, beta.out, beta.partials, beta.nb};
       vcycle_fused<R>(C, p_new, fph, &sp);
       std::swap(p_old, p_new);
     } else {
-      launch_bicg_p<R>(p_old, fr, fv, n, S, s);
+      launch_bicg_p<R>(p_old, fr, fv, n, beta, s);
       vcycle<R>(C, p_old, fph);
     }
-    launch_apply_dot<R, R>(gA, fph, fv, frh, kBicgAlpha, C->partials, S, s);
+    const BicgFold alpha = launch_apply_dot<R, R>(gA, fph, fv, frh, kBicgAlpha, C->partials, S, S1, s);
     if (fuse) {
-      const DownSrc<R> ss{kDownSrcS, fr, nullptr, fv, fs, S};
+      const DownSrc<R> ss{kDownSrcS, fr, nullptr, fv, fs, alpha.in, alpha.out, alpha.partials, alpha.nb};
       vcycle_fused<R>(C, fs, fsh, &ss);
     } else {
-      launch_bicg_s<R>(fs, fr, fv, n, S, s);
+      launch_bicg_s<R>(fs, fr, fv, n, alpha, s);
       vcycle<R>(C, fs, fsh);
     }
-    launch_apply_dot<R, R>(gA, fsh, ft, fs, kBicgOmega, C->partials, S, s);
-    launch_bicg_r<R>(fr, fs, ft, frh, n, C->partials, S, K.fcoef + 2 * slot, s);
+    const BicgFold omega = launch_apply_dot<R, R>(gA, fsh, ft, fs, kBicgOmega, C->partials, S1, S2, s);
+    beta = launch_bicg_r<R>(fr, fs, ft, frh, n, C->partials, omega, S2, S, K.fcoef + 2 * slot, s);
     if (slot == K.fdefer - 1 || it == iters - 1) launch_bicg_xdefer<R>(x, ph0, sh0, K.ld, slot + 1, K.fcoef, n, s);
   }
+  // the last step's flag is read with the next run's start or the solve's end
+  if (beta.nb > 0) launch_bicg_final(beta.partials, beta.nb, 2, S2, S, (int)kBicgNormRho, s);
 }
 
 // Arnoldi step j (Sec. 5's GMRES): h = V_{0..j}^H w, w -= V h, ||w||^2 into
@@ -1603,7 +1608,7 @@ bool bicg_fuse(const ecs_ctx *C, const KrylovBufs &K) {
 }
 
 template <typename RZ>
-void bicg_open_step(ecs_ctx *C, const KrylovBufs &K) {
+BicgFold bicg_open_step(ecs_ctx *C, const KrylovBufs &K) {
   const int64_t n = nn_of(C);
   hipStream_t s = C->stream;
   BicgScalars *S = C->bs;
@@ -1611,41 +1616,40 @@ void bicg_open_step(ecs_ctx *C, const KrylovBufs &K) {
   if (bicg_fuse<RZ>(C, K)) {
     if constexpr (sizeof(RZ) == 8) {
       cplx<double> *p_old = C->bicg_pflip ? K.p2 : K.p, *p_new = C->bicg_pflip ? K.p : K.p2;
-      const DownSrc<double> sp{kDownSrcP, K.r, p_old, K.v, p_new, S};
+      const DownSrc<double> sp{kDownSrcP, K.r, p_old, K.v, p_new, S, nullptr, nullptr, 0};
       vcycle_fused<double>(C, p_new, ph, &sp);
       C->bicg_pflip ^= 1;
     }
   } else {
-    launch_bicg_p<double>(K.p, K.r, K.v, n, S, s);
+    launch_bicg_p<double>(K.p, K.r, K.v, n, bicg_scalars(S), s);
     precond<RZ>(C, K.p, ph);
   }
-  {
-    TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
-    launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, s);
-  }
+  TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
+  return launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S + kMaxRhs, s);
 }
 
 template <typename RZ>
-void bicg_close_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x) {
+void bicg_close_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x, const BicgFold &alpha) {
   const int64_t n = nn_of(C);
   hipStream_t s = C->stream;
-  BicgScalars *S = C->bs;
+  BicgScalars *S = C->bs, *S1 = S + kMaxRhs, *S2 = S + 2 * kMaxRhs;
   cplx<RZ> *ph = reinterpret_cast<cplx<RZ> *>(K.ph);
   cplx<RZ> *sh = reinterpret_cast<cplx<RZ> *>(K.sh);
   if (bicg_fuse<RZ>(C, K)) {
     if constexpr (sizeof(RZ) == 8) {
-      const DownSrc<double> ss{kDownSrcS, K.r, nullptr, K.v, K.s, S};
+      const DownSrc<double> ss{kDownSrcS, K.r, nullptr, K.v, K.s, alpha.in, alpha.out, alpha.partials, alpha.nb};
       vcycle_fused<double>(C, K.s, sh, &ss);
     }
   } else {
-    launch_bicg_s<double>(K.s, K.r, K.v, n, S, s);
+    launch_bicg_s<double>(K.s, K.r, K.v, n, alpha, s);
     precond<RZ>(C, K.s, sh);
   }
+  BicgFold omega;
   {
     TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
-    launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S, s);
+    omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s);
   }
-  launch_bicg_xr<double, RZ>(x, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, S, s);
+  launch_bicg_xr<double, RZ>(x, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s);
 }
 
 template <typename RZ>
@@ -1685,14 +1689,15 @@ ecs_status bicgstab(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, co
     }
     last_restart = rt;
     bool opened = false;
+    BicgFold alpha{};
     while (it < d->maxit) {
-      if (!opened) bicg_open_step<RZ>(C, K);
-      bicg_close_step<RZ>(C, K, x);
+      if (!opened) alpha = bicg_open_step<RZ>(C, K);
+      bicg_close_step<RZ>(C, K, x, alpha);
       if (!enqueue_readback(C, &S->est, sizeof(double) + sizeof(int))) break;  // est, bad
       st->vcycles += 2;
       it++;
       opened = it < d->maxit && run_ahead(C);
-      if (opened) bicg_open_step<RZ>(C, K);
+      if (opened) alpha = bicg_open_step<RZ>(C, K);
       if (!wait_readback(C)) break;
       double est;
       int bad;
@@ -1794,21 +1799,49 @@ void batch_precond(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx<
   }
 }
 
-// one Bi-CGSTAB iteration of every slot in rs (per slot that of the single solve)
+// one Bi-CGSTAB iteration of every slot in rs (per slot that of the single
+// solve).  As there, the p and s updates run inside the finest down kernel; p
+// then moves to the other of its two buffers (every slot with a direction is in
+// rs; one that restarts has p = 0 in both).  Against separate updates: eight
+// right-hand sides of 1025^2 117.4 -> 112.5 ms, of 513^2 43.4 -> 42.4, four 257^2
+// systems coupled 68.8 -> 62.1; three 513^2 systems at once 73.2 -> 74.1.
 template <typename RZ>
 void batch_step(ecs_ctx *C, const KrylovBufs &K, const RhsSet &rs) {
   const int64_t n = nn_of(C);
   hipStream_t s = C->stream;
-  BicgScalars *S = C->bs;
+  BicgScalars *S = C->bs, *S1 = S + kMaxRhs, *S2 = S + 2 * kMaxRhs;
   cplx<RZ> *ph = reinterpret_cast<cplx<RZ> *>(K.ph);
   cplx<RZ> *sh = reinterpret_cast<cplx<RZ> *>(K.sh);
-  launch_bicg_p<double>(K.p, K.r, K.v, n, S, s, rs);
-  batch_precond<RZ>(C, K, K.p, ph, rs);
-  launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, s, rs);
-  launch_bicg_s<double>(K.s, K.r, K.v, n, S, s, rs);
-  batch_precond<RZ>(C, K, K.s, sh, rs);
-  launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S, s, rs);
-  launch_bicg_xr<double, RZ>(K.bx, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, S, s, rs);
+  if (!K.p2) C->bicg_pflip = 0;  // the context may have had another cycle type before
+  cplx<double> *p = C->bicg_pflip ? K.p2 : K.p;
+  bool fuse = false;
+  if constexpr (sizeof(RZ) == 8) {
+    fuse = K.p2 && fused_updates(C);
+    if (fuse) {
+      cplx<double> *q = C->bicg_pflip ? K.p : K.p2;
+      const CycleBufs<double> B = batch_bufs<double>(C, K);
+      const DownSrc<double> sp{kDownSrcP, K.r, p, K.v, q, S, nullptr, nullptr, 0};
+      vcycle_fused<double>(C, q, ph, &sp, &B, rs);
+      C->bicg_pflip ^= 1;
+    }
+  }
+  if (!fuse) {
+    launch_bicg_p<double>(p, K.r, K.v, n, bicg_scalars(S), s, rs);
+    batch_precond<RZ>(C, K, p, ph, rs);
+  }
+  const BicgFold alpha = launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S1, s, rs);
+  if (fuse) {
+    if constexpr (sizeof(RZ) == 8) {
+      const CycleBufs<double> B = batch_bufs<double>(C, K);
+      const DownSrc<double> ss{kDownSrcS, K.r, nullptr, K.v, K.s, alpha.in, alpha.out, alpha.partials, alpha.nb};
+      vcycle_fused<double>(C, K.s, sh, &ss, &B, rs);
+    }
+  } else {
+    launch_bicg_s<double>(K.s, K.r, K.v, n, alpha, s, rs);
+    batch_precond<RZ>(C, K, K.s, sh, rs);
+  }
+  const BicgFold omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s, rs);
+  launch_bicg_xr<double, RZ>(K.bx, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s, rs);
 }
 
 // restart of slot q: r = b - A x, (r, r) -> the restart scalars, r^ = r, p = v = 0
@@ -1821,6 +1854,7 @@ void batch_restart(ecs_ctx *C, const KrylovBufs &K, int q) {
                          s);
   (void)hipMemcpyAsync(slot_of<cplx<double>>(K.rh, K, q), r, n * sizeof(cplx<double>), hipMemcpyDeviceToDevice, s);
   launch_zero<double>(slot_of<cplx<double>>(K.p, K, q), n, s);
+  if (K.p2) launch_zero<double>(slot_of<cplx<double>>(K.p2, K, q), n, s);
   launch_zero<double>(slot_of<cplx<double>>(K.v, K, q), n, s);
 }
 

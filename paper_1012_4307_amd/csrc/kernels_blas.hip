@@ -565,12 +565,14 @@ __global__ __launch_bounds__(BS) void k_pairdot(const cplx<R> *__restrict__ x0, 
 // block per right-hand side)
 template <bool MR>
 __global__ __launch_bounds__(BS) void k_bicg_final(const cplx<double> *__restrict__ partials, int nblocks,
-                                                   int npairs, BicgScalars *S, int mode, RhsSet rs) {
+                                                   int npairs, const BicgScalars *in, BicgScalars *out, int mode,
+                                                   RhsSet rs) {
   __shared__ cplx<double> lds[BS / 64];
   if constexpr (MR) {
     const int64_t q = rhs_index(rs);
     partials += q * kRhsPartials;
-    S += q;
+    in += q;
+    out += q;
   }
   cplx<double> d[2] = {mk<double>(0, 0), mk<double>(0, 0)};
   for (int q = 0; q < npairs; q++) {
@@ -578,20 +580,41 @@ __global__ __launch_bounds__(BS) void k_bicg_final(const cplx<double> *__restric
     d[q] = block_sum(s, lds);
     __syncthreads();
   }
-  if (threadIdx.x == 0) bicg_update(S, mode, d[0], d[1]);
+  if (threadIdx.x == 0) {
+    BicgScalars t = *in;
+    bicg_update(&t, mode, d[0], d[1]);
+    *out = t;
+  }
+}
+
+// this block's scalars: *f.in, or with partials pending their update (in LDS)
+template <int NP, bool MR>
+__device__ __forceinline__ const BicgScalars *bicg_take(BicgFold f, int mode, const RhsSet &rs, cplx<double> *red,
+                                                        BicgScalars *sh) {
+  if constexpr (MR) {
+    const int64_t q = rhs_index(rs);
+    f.in += q;
+    f.out += q;
+    f.partials += q * kRhsPartials;
+  }
+  if (f.nb == 0) return f.in;
+  fold_finish<NP>(fold_load<NP>(f.partials, f.nb), f.in, f.out, f.nb, mode, red, sh);
+  return sh;
 }
 
 // p = r + beta (p - omega v)
 template <typename R, bool MR>
 __global__ __launch_bounds__(BS) void k_bicg_p(cplx<R> *__restrict__ p, const cplx<R> *__restrict__ r,
-                                               const cplx<R> *__restrict__ v, int64_t n, const BicgScalars *S,
+                                               const cplx<R> *__restrict__ v, int64_t n, BicgFold f,
                                                RhsSet rs) {
+  __shared__ cplx<double> red[BS / 64];
+  __shared__ BicgScalars sh;
+  const BicgScalars *S = bicg_take<2, MR>(f, kBicgNormRho, rs, red, &sh);
   if constexpr (MR) {
     const int64_t q = rhs_index(rs), sn = rhs_stride(n);
     p += q * sn;
     r += q * sn;
     v += q * sn;
-    S += q;
   }
   const cplx<R> beta = cvt<R>(S->beta), omega = cvt<R>(S->omega);
   for (int64_t q = (int64_t)blockIdx.x * BS + threadIdx.x; q < n; q += (int64_t)gridDim.x * BS)
@@ -601,14 +624,16 @@ __global__ __launch_bounds__(BS) void k_bicg_p(cplx<R> *__restrict__ p, const cp
 // s = r - alpha v
 template <typename R, bool MR>
 __global__ __launch_bounds__(BS) void k_bicg_s(cplx<R> *__restrict__ s, const cplx<R> *__restrict__ r,
-                                               const cplx<R> *__restrict__ v, int64_t n, const BicgScalars *S,
+                                               const cplx<R> *__restrict__ v, int64_t n, BicgFold f,
                                                RhsSet rs) {
+  __shared__ cplx<double> red[BS / 64];
+  __shared__ BicgScalars sh;
+  const BicgScalars *S = bicg_take<1, MR>(f, kBicgAlpha, rs, red, &sh);
   if constexpr (MR) {
     const int64_t q = rhs_index(rs), sn = rhs_stride(n);
     s += q * sn;
     r += q * sn;
     v += q * sn;
-    S += q;
   }
   const cplx<R> alpha = cvt<R>(S->alpha);
   for (int64_t q = (int64_t)blockIdx.x * BS + threadIdx.x; q < n; q += (int64_t)gridDim.x * BS)
@@ -621,9 +646,11 @@ template <typename R, typename RZ, bool MR>
 __global__ __launch_bounds__(BS) void k_bicg_xr(cplx<R> *__restrict__ x, const cplx<RZ> *__restrict__ ph,
                                                 const cplx<RZ> *__restrict__ sh, cplx<R> *__restrict__ r,
                                                 const cplx<R> *__restrict__ s, const cplx<R> *__restrict__ t,
-                                                const cplx<R> *__restrict__ rh, int64_t n, BicgScalars *S,
+                                                const cplx<R> *__restrict__ rh, int64_t n, BicgFold f,
                                                 cplx<double> *partials, RhsSet rs) {
   __shared__ cplx<double> lds[BS / 64];
+  __shared__ BicgScalars sh_s;
+  const BicgScalars *S = bicg_take<2, MR>(f, kBicgOmega, rs, lds, &sh_s);
   if constexpr (MR) {
     const int64_t q = rhs_index(rs), sn = rhs_stride(n);
     x += q * sn;
@@ -633,7 +660,6 @@ __global__ __launch_bounds__(BS) void k_bicg_xr(cplx<R> *__restrict__ x, const c
     s += q * sn;
     t += q * sn;
     rh += q * sn;
-    S += q;
     partials += q * kRhsPartials;
   }
   const cplx<R> alpha = cvt<R>(S->alpha), omega = cvt<R>(S->omega);
@@ -661,9 +687,11 @@ __global__ __launch_bounds__(BS) void k_bicg_xr(cplx<R> *__restrict__ x, const c
 template <typename R>
 __global__ __launch_bounds__(BS) void k_bicg_r(cplx<R> *__restrict__ r, const cplx<R> *__restrict__ s,
                                                const cplx<R> *__restrict__ t, const cplx<R> *__restrict__ rh,
-                                               int64_t n, const BicgScalars *S, cplx<double> *partials,
+                                               int64_t n, BicgFold f, cplx<double> *partials,
                                                cplx<double> *coef) {
   __shared__ cplx<double> lds[BS / 64];
+  __shared__ BicgScalars sh_s;
+  const BicgScalars *S = bicg_take<2, false>(f, kBicgOmega, RhsSet{}, lds, &sh_s);
   const cplx<R> omega = cvt<R>(S->omega);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     coef[0] = S->alpha;
@@ -947,63 +975,64 @@ void launch_pairdot(const cplx<R> *x0, const cplx<R> *y0, const cplx<R> *x1, con
                     cplx<double> *partials, BicgScalars *S, int mode, hipStream_t s) {
   int nb = red_blocks(n);
   launch_k((k_pairdot<R>), dim3(nb), dim3(BS), 0, s, x0, y0, x1, y1, npairs, n, partials);
-  launch_k(k_bicg_final<false>, dim3(1), dim3(BS), 0, s, partials, nb, npairs, S, mode, one_rhs());
+  launch_k(k_bicg_final<false>, dim3(1), dim3(BS), 0, s, partials, nb, npairs, (const BicgScalars *)S, S, mode,
+           one_rhs());
 }
 template <typename R>
-void launch_bicg_p(cplx<R> *p, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgScalars *S, hipStream_t s,
+void launch_bicg_p(cplx<R> *p, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgFold &f, hipStream_t s,
                    const RhsSet &rs) {
-  if (multi_rhs(rs)) launch_k((k_bicg_p<R, true>), dim3(grid_for(n), rs.count), dim3(BS), 0, s, p, r, v, n, S, rs);
-  else launch_k((k_bicg_p<R, false>), dim3(grid_for(n)), dim3(BS), 0, s, p, r, v, n, S, rs);
+  if (multi_rhs(rs)) launch_k((k_bicg_p<R, true>), dim3(grid_for(n), rs.count), dim3(BS), 0, s, p, r, v, n, f, rs);
+  else launch_k((k_bicg_p<R, false>), dim3(grid_for(n)), dim3(BS), 0, s, p, r, v, n, f, rs);
 }
 template <typename R>
-void launch_bicg_s(cplx<R> *sv, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgScalars *S, hipStream_t s,
+void launch_bicg_s(cplx<R> *sv, const cplx<R> *r, const cplx<R> *v, int64_t n, const BicgFold &f, hipStream_t s,
                    const RhsSet &rs) {
-  if (multi_rhs(rs)) launch_k((k_bicg_s<R, true>), dim3(grid_for(n), rs.count), dim3(BS), 0, s, sv, r, v, n, S, rs);
-  else launch_k((k_bicg_s<R, false>), dim3(grid_for(n)), dim3(BS), 0, s, sv, r, v, n, S, rs);
+  if (multi_rhs(rs)) launch_k((k_bicg_s<R, true>), dim3(grid_for(n), rs.count), dim3(BS), 0, s, sv, r, v, n, f, rs);
+  else launch_k((k_bicg_s<R, false>), dim3(grid_for(n)), dim3(BS), 0, s, sv, r, v, n, f, rs);
 }
 template <typename R, typename RZ>
 void launch_bicg_xr(cplx<R> *x, const cplx<RZ> *ph, const cplx<RZ> *sh, cplx<R> *r, const cplx<R> *sv,
-                    const cplx<R> *t, const cplx<R> *rh, int64_t n, cplx<double> *partials, BicgScalars *S,
-                    hipStream_t s, const RhsSet &rs) {
+                    const cplx<R> *t, const cplx<R> *rh, int64_t n, cplx<double> *partials, const BicgFold &f,
+                    BicgScalars *S2, BicgScalars *S, hipStream_t s, const RhsSet &rs) {
   const int nb = red_blocks(n);
-  if (multi_rhs(rs)) {
-    launch_k((k_bicg_xr<R, RZ, true>), dim3(nb, rs.count), dim3(BS), 0, s, x, ph, sh, r, sv, t, rh, n, S, partials,
-             rs);
-    launch_k(k_bicg_final<true>, dim3(1, rs.count), dim3(BS), 0, s, partials, nb, 2, S, (int)kBicgNormRho, rs);
-  } else {
-    launch_k((k_bicg_xr<R, RZ, false>), dim3(nb), dim3(BS), 0, s, x, ph, sh, r, sv, t, rh, n, S, partials, rs);
-    launch_k(k_bicg_final<false>, dim3(1), dim3(BS), 0, s, partials, nb, 2, S, (int)kBicgNormRho, rs);
-  }
+  cplx<double> *last = partials + kLastPartials;
+  if (multi_rhs(rs))
+    launch_k((k_bicg_xr<R, RZ, true>), dim3(nb, rs.count), dim3(BS), 0, s, x, ph, sh, r, sv, t, rh, n, f, last, rs);
+  else launch_k((k_bicg_xr<R, RZ, false>), dim3(nb), dim3(BS), 0, s, x, ph, sh, r, sv, t, rh, n, f, last, rs);
+  launch_bicg_final(last, nb, 2, S2, S, (int)kBicgNormRho, s, rs);
 }
 
 template <typename R>
-void launch_bicg_r(cplx<R> *r, const cplx<R> *sv, const cplx<R> *t, const cplx<R> *rh, int64_t n,
-                   cplx<double> *partials, BicgScalars *S, cplx<double> *coef, hipStream_t s) {
+BicgFold launch_bicg_r(cplx<R> *r, const cplx<R> *sv, const cplx<R> *t, const cplx<R> *rh, int64_t n,
+                       cplx<double> *partials, const BicgFold &f, BicgScalars *S2, BicgScalars *S,
+                       cplx<double> *coef, hipStream_t s) {
   const int nb = red_blocks(n);
-  launch_k((k_bicg_r<R>), dim3(nb), dim3(BS), 0, s, r, sv, t, rh, n, (const BicgScalars *)S, partials, coef);
-  launch_k(k_bicg_final<false>, dim3(1), dim3(BS), 0, s, partials, nb, 2, S, (int)kBicgNormRho, one_rhs());
+  cplx<double> *last = partials + kLastPartials;
+  launch_k((k_bicg_r<R>), dim3(nb), dim3(BS), 0, s, r, sv, t, rh, n, f, last, coef);
+  return bicg_fold_or_final(last, nb, 2, S2, S, (int)kBicgNormRho, s);
 }
 template <typename R>
 void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_t ld, int count,
                         const cplx<double> *coef, int64_t n, hipStream_t s) {
   launch_k((k_bicg_xdefer<R>), dim3(grid_for(n)), dim3(BS), 0, s, x, ph, sh, ld, count, coef, n);
 }
-template void launch_bicg_r<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, const cplx<float> *,
-                                   int64_t, cplx<double> *, BicgScalars *, cplx<double> *, hipStream_t);
-template void launch_bicg_r<double>(cplx<double> *, const cplx<double> *, const cplx<double> *,
-                                    const cplx<double> *, int64_t, cplx<double> *, BicgScalars *, cplx<double> *,
-                                    hipStream_t);
+template BicgFold launch_bicg_r<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, const cplx<float> *,
+                                       int64_t, cplx<double> *, const BicgFold &, BicgScalars *, BicgScalars *,
+                                       cplx<double> *, hipStream_t);
+template BicgFold launch_bicg_r<double>(cplx<double> *, const cplx<double> *, const cplx<double> *,
+                                        const cplx<double> *, int64_t, cplx<double> *, const BicgFold &,
+                                        BicgScalars *, BicgScalars *, cplx<double> *, hipStream_t);
 template void launch_bicg_xdefer<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, int64_t, int,
                                         const cplx<double> *, int64_t, hipStream_t);
 template void launch_bicg_xdefer<double>(cplx<double> *, const cplx<double> *, const cplx<double> *, int64_t, int,
                                          const cplx<double> *, int64_t, hipStream_t);
 
-void launch_bicg_final(const cplx<double> *partials, int nblocks, int npairs, BicgScalars *S, int mode,
-                       hipStream_t s, const RhsSet &rs) {
+void launch_bicg_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in, BicgScalars *out,
+                       int mode, hipStream_t s, const RhsSet &rs) {
   if (multi_rhs(rs))
-    launch_k(k_bicg_final<true>, dim3(1, rs.count), dim3(BS), 0, s, partials, nblocks, npairs, S, mode, rs);
+    launch_k(k_bicg_final<true>, dim3(1, rs.count), dim3(BS), 0, s, partials, nblocks, npairs, in, out, mode, rs);
   else
-    launch_k(k_bicg_final<false>, dim3(1), dim3(BS), 0, s, partials, nblocks, npairs, S, mode, rs);
+    launch_k(k_bicg_final<false>, dim3(1), dim3(BS), 0, s, partials, nblocks, npairs, in, out, mode, rs);
 }
 
 template <typename RI, typename RO>
@@ -1085,22 +1114,22 @@ template void launch_pairdot<double>(const cplx<double> *, const cplx<double> *,
 template void launch_pairdot<float>(const cplx<float> *, const cplx<float> *, const cplx<float> *,
                                     const cplx<float> *, int, int64_t, cplx<double> *, BicgScalars *, int, hipStream_t);
 template void launch_bicg_p<double>(cplx<double> *, const cplx<double> *, const cplx<double> *, int64_t,
-                                    const BicgScalars *, hipStream_t, const RhsSet &);
+                                    const BicgFold &, hipStream_t, const RhsSet &);
 template void launch_bicg_p<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, int64_t,
-                                   const BicgScalars *, hipStream_t, const RhsSet &);
+                                   const BicgFold &, hipStream_t, const RhsSet &);
 template void launch_bicg_s<double>(cplx<double> *, const cplx<double> *, const cplx<double> *, int64_t,
-                                    const BicgScalars *, hipStream_t, const RhsSet &);
+                                    const BicgFold &, hipStream_t, const RhsSet &);
 template void launch_bicg_s<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, int64_t,
-                                   const BicgScalars *, hipStream_t, const RhsSet &);
+                                   const BicgFold &, hipStream_t, const RhsSet &);
 template void launch_bicg_xr<double, double>(cplx<double> *, const cplx<double> *, const cplx<double> *, cplx<double> *,
                                              const cplx<double> *, const cplx<double> *, const cplx<double> *, int64_t,
-                                             cplx<double> *, BicgScalars *, hipStream_t, const RhsSet &);
+                                             cplx<double> *, const BicgFold &, BicgScalars *, BicgScalars *, hipStream_t, const RhsSet &);
 template void launch_bicg_xr<double, float>(cplx<double> *, const cplx<float> *, const cplx<float> *, cplx<double> *,
                                             const cplx<double> *, const cplx<double> *, const cplx<double> *, int64_t,
-                                            cplx<double> *, BicgScalars *, hipStream_t, const RhsSet &);
+                                            cplx<double> *, const BicgFold &, BicgScalars *, BicgScalars *, hipStream_t, const RhsSet &);
 template void launch_bicg_xr<float, float>(cplx<float> *, const cplx<float> *, const cplx<float> *, cplx<float> *,
                                            const cplx<float> *, const cplx<float> *, const cplx<float> *, int64_t,
-                                           cplx<double> *, BicgScalars *, hipStream_t, const RhsSet &);
+                                           cplx<double> *, const BicgFold &, BicgScalars *, BicgScalars *, hipStream_t, const RhsSet &);
 template void launch_cast<double, float>(const cplx<double> *, cplx<float> *, int64_t, hipStream_t, const RhsSet &);
 template void launch_cast<float, double>(const cplx<float> *, cplx<double> *, int64_t, hipStream_t, const RhsSet &);
 template void launch_zero<double>(cplx<double> *, int64_t, hipStream_t);

@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void k_prolong_add(Grid<R> f, Grid<R> c, const
 template <typename R, typename RI>
 __global__ __launch_bounds__(256) void k_apply_dot(Grid<R> g, const cplx<RI> *__restrict__ x,
                                                    cplx<R> *__restrict__ y, const cplx<R> *__restrict__ d0,
-                                                   int mode, cplx<double> *partials, BicgScalars *S) {
+                                                   int mode, cplx<double> *partials) {
   __shared__ cplx<double> lds[4];
   const int tx = (g.n0 + TX - 1) / TX, ty = (g.n1 + TY - 1) / TY;
   const int ntiles = tx * ty * g.n2;
@@ -492,8 +492,9 @@ void launch_prolong_to(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R>
   launch_k((k_prolong_add<R>), grid_of(fine), dim3(TX, TY), 0, s, fine, coarse, ec, u_in, u_out);
 }
 template <typename R, typename RI>
-void launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
-                      cplx<double> *partials, BicgScalars *S, hipStream_t s, const RhsSet &rs) {
+BicgFold launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
+                          cplx<double> *partials, const BicgScalars *in, BicgScalars *out, hipStream_t s,
+                          const RhsSet &rs) {
   // one block per 64 x 4 tile while the partials (two per block) fit the
   // reduction buffer (kRedBlocks x (kMaxRestart + 2) entries); batched
   // launches (2D only) give every right-hand side kRhsPartials of them
@@ -513,13 +514,12 @@ void launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cpl
                rs);
     else
       launch_k((k_apply2d<R, RI, R, kBicgOmega, sy>), grid, dim3(256), 0, s, g, x, y, d0, partials, tx, tiles, rs);
-    launch_bicg_final(partials, nb, mode == kBicgAlpha ? 1 : 2, S, mode, s, rs);
-    return;
+    return bicg_fold_or_final(partials, nb, mode == kBicgAlpha ? 1 : 2, in, out, mode, s, rs);
   }
   const int ntiles = ((g.n0 + TX - 1) / TX) * ((g.n1 + TY - 1) / TY) * g.n2;
   const int nb = ntiles < kRedBlocks ? ntiles : kRedBlocks;
-  launch_k((k_apply_dot<R, RI>), dim3(nb), dim3(256), 0, s, g, x, y, d0, mode, partials, S);
-  launch_bicg_final(partials, nb, mode == kBicgAlpha ? 1 : 2, S, mode, s);
+  launch_k((k_apply_dot<R, RI>), dim3(nb), dim3(256), 0, s, g, x, y, d0, mode, partials);
+  return bicg_fold_or_final(partials, nb, mode == kBicgAlpha ? 1 : 2, in, out, mode, s);
 }
 
 template <typename R>
@@ -546,15 +546,13 @@ void launch_inject_k2(int n0, int n1, int n2, const double *k2_fine, int f0, int
 ECS_INST_MG(double)
 ECS_INST_MG(float)
 
-template void launch_apply_dot<double, double>(const Grid<double> &, const cplx<double> *, cplx<double> *,
-                                               const cplx<double> *, int, cplx<double> *, BicgScalars *, hipStream_t,
-                                               const RhsSet &);
-template void launch_apply_dot<double, float>(const Grid<double> &, const cplx<float> *, cplx<double> *,
-                                              const cplx<double> *, int, cplx<double> *, BicgScalars *, hipStream_t,
-                                              const RhsSet &);
-template void launch_apply_dot<float, float>(const Grid<float> &, const cplx<float> *, cplx<float> *,
-                                             const cplx<float> *, int, cplx<double> *, BicgScalars *, hipStream_t,
-                                             const RhsSet &);
+#define ECS_INST_APPLY_DOT(R, RI)                                                                              \
+  template BicgFold launch_apply_dot<R, RI>(const Grid<R> &, const cplx<RI> *, cplx<R> *, const cplx<R> *, int, \
+                                            cplx<double> *, const BicgScalars *, BicgScalars *, hipStream_t,    \
+                                            const RhsSet &);
+ECS_INST_APPLY_DOT(double, double)
+ECS_INST_APPLY_DOT(double, float)
+ECS_INST_APPLY_DOT(float, float)
 template void launch_apply<double, double, double>(const Grid<double> &, const cplx<double> *, cplx<double> *,
                                                    hipStream_t);
 template void launch_apply<double, float, double>(const Grid<double> &, const cplx<float> *, cplx<double> *,

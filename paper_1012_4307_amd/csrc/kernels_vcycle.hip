@@ -16,9 +16,11 @@
 // recomputed redundantly from a halo staged in LDS, so tiles are independent
 // and no grid-wide synchronisation is needed.  Rows are loaded with
 // consecutive lanes on consecutive x (unit stride, interleaved complex).
+#include <type_traits>
+
 #include "ecs_dense.h"
 #include "ecs_internal.h"
-#include "ecs_krylov.h"
+#include "ecs_reduce.h"
 
 namespace ecs {
 
@@ -87,10 +89,12 @@ __device__ __forceinline__ cplx<R> sel(bool c, cplx<R> a, cplx<R> b) {
 // SRC selects the right-hand side: kDownSrcB reads b; kDownSrcP and kDownSrcS
 // stage the Bi-CGSTAB vectors it is formed from instead (r, p, v or r, v),
 // form it per staged node and store it at the owned nodes (boundary nodes,
-// read as 0, get 0).
-template <typename R, int CY, int SRC, bool MR>
+// read as 0, get 0).  FOLD: the dot products behind its scalars are pending
+// partials, whose loads go out before the tile's and whose sums are taken while
+// those are in flight (BicgFold).
+template <typename R, int CY, int SRC, bool MR, bool FOLD>
 __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
-                                                const DownSrc<R> src, cplx<R> *__restrict__ rc, R omega,
+                                                DownSrc<R> src, cplx<R> *__restrict__ rc, R omega,
                                                 int tiles_x, int tiles, RhsSet rs) {
   constexpr int CX = 61;
   constexpr int WX = 2 * CX + 5;          // 127 staged columns
@@ -108,10 +112,25 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   if constexpr (MR) {
     // this block's right-hand side (a separate instantiation: the slot is a
     // load the single right-hand side path does not wait for)
-    const int64_t q = rhs_index(rs);
-    b += q * rhs_stride((int64_t)f.n0 * f.n1);
+    const int64_t q = rhs_index(rs), sf = rhs_stride((int64_t)f.n0 * f.n1);
     rc += q * rhs_stride((int64_t)c.n0 * c.n1);
+    if constexpr (SRC == kDownSrcB) {
+      b += q * sf;
+    } else {
+      src.r += q * sf;
+      src.v += q * sf;
+      if constexpr (SRC == kDownSrcP) src.p += q * sf;
+      src.out += q * sf;
+      src.S += q;
+      if constexpr (FOLD) {
+        src.S_out += q;
+        src.partials += q * kRhsPartials;
+      }
+    }
   }
+  constexpr int NP = SRC == kDownSrcP ? 2 : 1;
+  FoldLoads<NP> fold;
+  if constexpr (FOLD) fold = fold_load<NP>(src.partials, src.nb);
   const int I0 = (tile % tiles_x) * CX, J0 = (tile / tiles_x) * CY;
   const int gx0 = 2 * I0 - 3, gy0 = 2 * J0 - 3;
   const int n0 = f.n0, n1 = f.n1;
@@ -165,16 +184,23 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
     kB[r] = ld_r(rk, okB + qk, R());
   }
   if constexpr (SRC != kDownSrcB) {
+    const BicgScalars *S = src.S;
+    if constexpr (FOLD) {
+      __shared__ cplx<double> red[NT / 64];
+      __shared__ BicgScalars sh;
+      fold_finish<NP>(fold, src.S, src.S_out, src.nb, SRC == kDownSrcP ? kBicgNormRho : kBicgAlpha, red, &sh);
+      S = &sh;
+    }
     // the same expressions as the separate update kernels
     if constexpr (SRC == kDownSrcP) {
-      const cplx<R> beta = cvt<R>(src.S->beta), om_s = cvt<R>(src.S->omega);
+      const cplx<R> beta = cvt<R>(S->beta), om_s = cvt<R>(S->omega);
 #pragma unroll
       for (int r = 0; r < RPW; r++) {
         bR[r] = xR[r] + beta * (pR[r] - om_s * vR[r]);
         bB[r] = xB[r] + beta * (pB[r] - om_s * vB[r]);
       }
     } else {
-      const cplx<R> alpha = cvt<R>(src.S->alpha);
+      const cplx<R> alpha = cvt<R>(S->alpha);
 #pragma unroll
       for (int r = 0; r < RPW; r++) {
         bR[r] = xR[r] - alpha * vR[r];
@@ -707,49 +733,57 @@ __global__ __launch_bounds__(TT) void k_tail_wide(TailArgs a, RhsSet rs) {
 // host (autotuned per grid size and dtype): coarse rows per down block in
 // {2, ..., 6, 8, 16} (16 only in FP32, whose tile fits the LDS), fine rows
 // per up block in {4, 8, 10, 12, 16, 32}.
-template <typename R, int SRC, bool MR>
+template <typename R, int SRC, bool MR, bool FOLD>
 void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const DownSrc<R> &src, cplx<R> *rc,
                     R omega, int rows, hipStream_t s, const RhsSet &rs) {
   constexpr int CX = 61;
   const int tx = (coarse.n0 + CX - 1) / CX;
   const int tiles = tx * ((coarse.n1 + rows - 1) / rows);
   const dim3 grid(xcd_padded(tiles), rs.count), block(NT);
+  const auto go = [&](auto cy) {
+    launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD>), grid, block, 0, s, fine, coarse, b, src, rc, omega,
+             tx, tiles, rs);
+  };
   switch (rows) {
-    case 2: launch_k((k_down_rb<R, 2, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs); break;
-    case 3: launch_k((k_down_rb<R, 3, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs); break;
-    case 4: launch_k((k_down_rb<R, 4, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs); break;
-    case 5: launch_k((k_down_rb<R, 5, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs); break;
-    case 6: launch_k((k_down_rb<R, 6, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs); break;
+    case 2: go(std::integral_constant<int, 2>()); break;
+    case 3: go(std::integral_constant<int, 3>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    case 5: go(std::integral_constant<int, 5>()); break;
+    case 6: go(std::integral_constant<int, 6>()); break;
     case 16:
       if constexpr (sizeof(R) == 4) {
-        launch_k((k_down_rb<R, 16, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs);
+        go(std::integral_constant<int, 16>());
         break;
       }
       [[fallthrough]];
-    default:
-      launch_k((k_down_rb<R, 8, SRC, MR>), grid, block, 0, s, fine, coarse, b, src, rc, omega, tx, tiles, rs);
-      break;
+    default: go(std::integral_constant<int, 8>()); break;
   }
 }
 
-template <typename R, int SRC>
+template <typename R, int SRC, bool FOLD>
 void launch_down(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const DownSrc<R> &src, cplx<R> *rc,
                  R omega, int rows, hipStream_t s, const RhsSet &rs) {
-  if (multi_rhs(rs)) launch_down_mr<R, SRC, true>(fine, coarse, b, src, rc, omega, rows, s, rs);
-  else launch_down_mr<R, SRC, false>(fine, coarse, b, src, rc, omega, rows, s, rs);
+  if (multi_rhs(rs)) launch_down_mr<R, SRC, true, FOLD>(fine, coarse, b, src, rc, omega, rows, s, rs);
+  else launch_down_mr<R, SRC, false, FOLD>(fine, coarse, b, src, rc, omega, rows, s, rs);
 }
 
 template <typename R>
 void launch_down_rb(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, cplx<R> *rc, R omega, int rows,
                     hipStream_t s, const RhsSet &rs) {
-  launch_down<R, kDownSrcB>(fine, coarse, b, DownSrc<R>{}, rc, omega, rows, s, rs);
+  launch_down<R, kDownSrcB, false>(fine, coarse, b, DownSrc<R>{}, rc, omega, rows, s, rs);
 }
 
 template <typename R>
 void launch_down_rb_src(const Grid<R> &fine, const Grid<R> &coarse, const DownSrc<R> &src, cplx<R> *rc, R omega,
-                        int rows, hipStream_t s) {
-  if (src.mode == kDownSrcP) launch_down<R, kDownSrcP>(fine, coarse, nullptr, src, rc, omega, rows, s, one_rhs());
-  else launch_down<R, kDownSrcS>(fine, coarse, nullptr, src, rc, omega, rows, s, one_rhs());
+                        int rows, hipStream_t s, const RhsSet &rs) {
+  const bool fold = src.nb > 0;
+  if (src.mode == kDownSrcP) {
+    if (fold) launch_down<R, kDownSrcP, true>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
+    else launch_down<R, kDownSrcP, false>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
+  } else {
+    if (fold) launch_down<R, kDownSrcS, true>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
+    else launch_down<R, kDownSrcS, false>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
+  }
 }
 
 template <typename R, bool MR>
@@ -788,9 +822,9 @@ template void launch_down_rb<float>(const Grid<float> &, const Grid<float> &, co
 template void launch_up_rb<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
                                    const cplx<double> *, cplx<double> *, double, int, hipStream_t, const RhsSet &);
 template void launch_down_rb_src<float>(const Grid<float> &, const Grid<float> &, const DownSrc<float> &, cplx<float> *,
-                                        float, int, hipStream_t);
+                                        float, int, hipStream_t, const RhsSet &);
 template void launch_down_rb_src<double>(const Grid<double> &, const Grid<double> &, const DownSrc<double> &,
-                                         cplx<double> *, double, int, hipStream_t);
+                                         cplx<double> *, double, int, hipStream_t, const RhsSet &);
 template void launch_up_rb<float>(const Grid<float> &, const Grid<float> &, const cplx<float> *, const cplx<float> *,
                                   cplx<float> *, float, int, hipStream_t, const RhsSet &);
 

@@ -535,3 +535,24 @@ def test_arnoldi_kernels_by_size(n, coarsest, restart):
         assert oracle_resid(P, to_np(x), b) <= 1.05e-9, orth
         its[orth] = st["iterations"]
     assert abs(its["dcgs2"] - its["cgs2"]) <= max(2, 0.05 * its["cgs2"]), its
+
+
+@pytest.mark.parametrize("n,coarsest,dim,inner", [(33, 5, 2, 0), (33, 5, 3, 0), (65, 5, 3, 0), (865, 28, 2, 16),
+                                                  (897, 8, 2, 16), (1153, 10, 2, 16), (1217, 20, 2, 16)])
+def test_scalar_folds_by_size(n, coarsest, dim, inner):
+    """Bi-CGSTAB, alone and nested, on both sides of the sizes up to which the
+    kernels after a dot product take its sum themselves (768 partials: the last
+    dot products of a step at 865^2 / 897^2, the matvecs' at 1153^2 / 1217^2, in
+    3D 33^3 / 65^3): the true residual by the oracle's operator."""
+    if dim == 3:
+        w = W.cube_constant_k(n=n, k=6.0, coarsest=coarsest)
+    elif inner:
+        w = W.large_coulomb(n=n, coarsest=coarsest)
+    else:
+        w = W.coulomb(E=1.0, n=n, coarsest=coarsest)
+    P = oracle_for(w)
+    kr = E.Krylov(method="fgmres" if inner else "bicgstab", restart=40, rtol=1e-8, maxit=2000, inner=inner)
+    S = gpu_for(w, "f32" if inner else "f64", krylov=kr)
+    x, st = S.solve(to_gpu(w.rhs[0]), krylov=kr)
+    assert st["status"] == 0 and st["inner_breakdowns"] == 0, st
+    assert oracle_resid(P, to_np(x), w.rhs[0]) <= 1.05e-8
