@@ -72,9 +72,17 @@ __device__ __forceinline__ cplx<R> inv_cycle(cplx<R> d) {
   return mk<R>(d.re * s, -d.im * s);
 }
 
-template <typename R>
-__device__ __forceinline__ cplx<R> sel(bool c, cplx<R> a, cplx<R> b) {
-  return c ? a : b;
+// GS: omega = 1 (Gauss-Seidel, the QD set-ups' sweep) known at compile time.  A
+// relaxed node then forgets its old value and has no residual: the down kernel
+// stores no black residuals (two arrays of LDS instead of three) and restricts
+// five values instead of nine, the up kernel corrects only the black nodes and
+// drops the terms of the old values.  The values are those of omega = 1 in the
+// general kernel (1 x and 0 x + y are exact).  Finest level of 2049^2, FP32:
+// down 16.2 -> 15.7 us, up 24.4 -> 23.5; 1025^2 up 10.5 -> 10.0.
+template <bool GS, typename R>
+__device__ __forceinline__ cplx<R> relaxed(R omega, cplx<R> v) {
+  if constexpr (GS) return v;
+  else return omega * v;
 }
 
 // ----------------------------------------------------------------- down
@@ -92,7 +100,7 @@ __device__ __forceinline__ cplx<R> sel(bool c, cplx<R> a, cplx<R> b) {
 // read as 0, get 0).  FOLD: the dot products behind its scalars are pending
 // partials, whose loads go out before the tile's and whose sums are taken while
 // those are in flight (BicgFold).
-template <typename R, int CY, int SRC, bool MR, bool FOLD>
+template <typename R, int CY, int SRC, bool MR, bool FOLD, bool GS>
 __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                                 DownSrc<R> src, cplx<R> *__restrict__ rc, R omega,
                                                 int tiles_x, int tiles, RhsSet rs) {
@@ -103,7 +111,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   // relaxed iterate by colour; the residual by colour, the red one in the
   // red iterate's slots (in the residual phase a lane reads only its own red
   // node there, before overwriting it): three arrays keep eight blocks per CU
-  __shared__ cplx<R> sR[WY][64], sB[WY][64], rB[WY][64];
+  __shared__ cplx<R> sR[WY][64], sB[WY][64], rB[GS ? 1 : WY][64];
   cplx<R>(*const rR)[64] = sR;
   // the wave index is uniform: row indices and row weights live in scalars
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
       const bool yin = j >= 1 && j <= n1 - 2;
       dR[r] = (yin && inR) ? inv_cycle(xmR + xpR + cym[r] + cyp[r] + (kR[r] * f.beta + f.c)) : zero_c<R>();
       dB[r] = (yin && inBk) ? inv_cycle(xmB + xpB + cym[r] + cyp[r] + (kB[r] * f.beta + f.c)) : zero_c<R>();
-      sR[ly][lane] = omega * (bR[r] * dR[r]);
+      sR[ly][lane] = relaxed<GS>(omega, bR[r] * dR[r]);
       sB[ly][lane] = zero_c<R>();
     }
   }
@@ -253,18 +261,17 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   // left = red of lane - 1, right = own red.  Weights of the own-pair and the
   // other-pair neighbour:
   const cplx<R> wBo = ared ? xmB : xpB, wBn = ared ? xpB : xmB;
-  cplx<R> resB[RPW], tB[RPW];
+  cplx<R> resB[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
     const int ly = wv + 4 * r;
-    resB[r] = tB[r] = zero_c<R>();
+    resB[r] = zero_c<R>();
     if (ly >= 1 && ly <= WY - 2) {
       if (pin) {
         const cplx<R> tb =
             bB[r] + (wBo * sR[ly][lane] + wBn * sR[ly][ps] + cym[r] * sR[ly - 1][lane] + cyp[r] * sR[ly + 1][lane]);
-        tB[r] = omega * (tb * dB[r]);
-        resB[r] = om1 * tb;
-        sB[ly][lane] = tB[r];
+        if constexpr (!GS) resB[r] = om1 * tb;
+        sB[ly][lane] = relaxed<GS>(omega, tb * dB[r]);
       }
     }
   }
@@ -285,12 +292,13 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
       const bool yin = j >= 1 && j <= n1 - 2;
       cplx<R> resR = zero_c<R>();
       if (yin && ly >= 1 && ly <= WY - 2) {
-        if (inR && qin)
-          resR = om1 * bR[r] +
-                 (wRo * sB[ly][lane] + wRn * sB[ly][pq] + cym[r] * sB[ly - 1][lane] + cyp[r] * sB[ly + 1][lane]);
+        if (inR && qin) {
+          resR = wRo * sB[ly][lane] + wRn * sB[ly][pq] + cym[r] * sB[ly - 1][lane] + cyp[r] * sB[ly + 1][lane];
+          if constexpr (!GS) resR = om1 * bR[r] + resR;
+        }
       }
       rR[ly][lane] = resR;
-      rB[ly][lane] = (yin && inBk) ? resB[r] : zero_c<R>();
+      if constexpr (!GS) rB[ly][lane] = (yin && inBk) ? resB[r] : zero_c<R>();
     }
   }
   __syncthreads();
@@ -305,8 +313,9 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
       cplx<R> acc = zero_c<R>();
       if (I >= 1 && I <= c.n0 - 2 && J >= 1 && J <= c.n1 - 2) {
         const int y = 3 + 2 * cy;
-        acc = R(0.25) * rR[y][P] + R(0.125) * (rB[y][P] + rB[y][P + 1] + rB[y - 1][P] + rB[y + 1][P]) +
-              R(0.0625) * (rR[y - 1][P] + rR[y - 1][P + 1] + rR[y + 1][P] + rR[y + 1][P + 1]);
+        acc = R(0.25) * rR[y][P];
+        if constexpr (!GS) acc = acc + R(0.125) * (rB[y][P] + rB[y][P + 1] + rB[y - 1][P] + rB[y + 1][P]);
+        acc = acc + R(0.0625) * (rR[y - 1][P] + rR[y - 1][P + 1] + rR[y + 1][P] + rR[y + 1][P + 1]);
       }
       rc[(int64_t)J * c.n0 + I] = acc;
     }
@@ -324,7 +333,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
 // on the tile reads red values on ring 1.  Column a = x0 - 4 + 2 lane is even,
 // so both columns of pair l interpolate from coarse column x0/2 - 2 + l
 // (= staged coarse column l).
-template <typename R, int TY, bool MR>
+template <typename R, int TY, bool MR, bool GS>
 __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                               const cplx<R> *__restrict__ ec, cplx<R> *__restrict__ u_out, R omega,
                                               int tiles_x, int tiles, RhsSet rs) {
@@ -399,7 +408,7 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
       const bool yin = j >= 1 && j <= n1 - 2;
       dR[r] = (yin && inR) ? inv_cycle(xmR + xpR + cym[r] + cyp[r] + (kR[r] * f.beta + f.c)) : zero_c<R>();
       dB[r] = (yin && inBk) ? inv_cycle(xmB + xpB + cym[r] + cyp[r] + (kB[r] * f.beta + f.c)) : zero_c<R>();
-      vR[r] = omega * (bR[r] * dR[r]);
+      vR[r] = relaxed<GS>(omega, bR[r] * dR[r]);
       sR[ly][lane] = vR[r];
     }
   }
@@ -425,9 +434,14 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
       if (pin) {
         const cplx<R> tb =
             bB[r] + (wBo * sR[ly][lane] + wBn * sR[ly][psc] + cym[r] * sR[ly - 1][lane] + cyp[r] * sR[ly + 1][lane]);
-        vB[r] = omega * (tb * dB[r]);
+        vB[r] = relaxed<GS>(omega, tb * dB[r]);
       }
-      if (yin) {
+      if (GS && yin) {
+        // black is column b where j is even (ared), a where it is odd
+        const int cj = (j >> 1) - cy0;
+        const cplx<R> e1 = ared ? se[cj][lane + 1] : se[cj + 1][lane];
+        if (inBk) vB[r] = vB[r] + R(0.5) * (se[cj][lane] + e1);
+      } else if (yin) {
         const int cj = (j >> 1) - cy0;
         cplx<R> pa, pb;
         if ((j & 1) == 0) {
@@ -459,7 +473,8 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
       if (qin && inR) {
         const cplx<R> o =
             wRo * sB[ly][lane] + wRn * sB[ly][pq] + cym[r] * sB[ly - 1][lane] + cyp[r] * sB[ly + 1][lane];
-        vR[r] = om1 * vR[r] + omega * ((bR[r] + o) * dR[r]);
+        if constexpr (GS) vR[r] = (bR[r] + o) * dR[r];
+        else vR[r] = om1 * vR[r] + omega * ((bR[r] + o) * dR[r]);
         sR[ly][lane] = vR[r];
       }
     }
@@ -479,7 +494,8 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
       if (own_x && inBk && j >= 1 && j <= n1 - 2) {
         const cplx<R> o =
             wBo * sR[ly][lane] + wBn * sR[ly][psc] + cym[r] * sR[ly - 1][lane] + cyp[r] * sR[ly + 1][lane];
-        outB = om1 * outB + omega * ((bB[r] + o) * dB[r]);
+        if constexpr (GS) outB = (bB[r] + o) * dB[r];
+        else outB = om1 * outB + omega * ((bB[r] + o) * dB[r]);
       }
       const uint32_t qo = row_off<cplx<R>>(j - y0, n0);
       st_c(ro, osR + qo, vR[r]);
@@ -741,9 +757,16 @@ void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b
   const int tiles = tx * ((coarse.n1 + rows - 1) / rows);
   const dim3 grid(xcd_padded(tiles), rs.count), block(NT);
   const auto go = [&](auto cy) {
-    launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD>), grid, block, 0, s, fine, coarse, b, src, rc, omega,
-             tx, tiles, rs);
+    launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD, false>), grid, block, 0, s, fine, coarse, b, src, rc,
+             omega, tx, tiles, rs);
   };
+  const auto go_gs = [&](auto cy) {
+    launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD, true>), grid, block, 0, s, fine, coarse, b, src, rc,
+             omega, tx, tiles, rs);
+  };
+  // the heights that the schedule takes by default have the omega = 1 form
+  if (omega == R(1) && rows == 2) return go_gs(std::integral_constant<int, 2>());
+  if (omega == R(1) && rows == 4) return go_gs(std::integral_constant<int, 4>());
   switch (rows) {
     case 2: go(std::integral_constant<int, 2>()); break;
     case 3: go(std::integral_constant<int, 3>()); break;
@@ -793,13 +816,19 @@ void launch_up_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, 
   const int tx = (fine.n0 + TX - 1) / TX;
   const int tiles = tx * ((fine.n1 + rows - 1) / rows);
   const dim3 grid(xcd_padded(tiles), rs.count), block(NT);
+  const auto go = [&](auto ty, auto gs) {
+    launch_k((k_up_rb<R, decltype(ty)::value, MR, decltype(gs)::value>), grid, block, 0, s, fine, coarse, b, ec, u_out,
+             omega, tx, tiles, rs);
+  };
+  if (omega == R(1) && rows == 4) return go(std::integral_constant<int, 4>(), std::true_type());
+  if (omega == R(1) && rows == 8) return go(std::integral_constant<int, 8>(), std::true_type());
   switch (rows) {
-    case 4: launch_k((k_up_rb<R, 4, MR>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs); break;
-    case 8: launch_k((k_up_rb<R, 8, MR>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs); break;
-    case 10: launch_k((k_up_rb<R, 10, MR>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs); break;
-    case 12: launch_k((k_up_rb<R, 12, MR>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs); break;
-    case 32: launch_k((k_up_rb<R, 32, MR>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs); break;
-    default: launch_k((k_up_rb<R, 16, MR>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs); break;
+    case 4: go(std::integral_constant<int, 4>(), std::false_type()); break;
+    case 8: go(std::integral_constant<int, 8>(), std::false_type()); break;
+    case 10: go(std::integral_constant<int, 10>(), std::false_type()); break;
+    case 12: go(std::integral_constant<int, 12>(), std::false_type()); break;
+    case 32: go(std::integral_constant<int, 32>(), std::false_type()); break;
+    default: go(std::integral_constant<int, 16>(), std::false_type()); break;
   }
 }
 

@@ -39,9 +39,9 @@ COPY_BYTES = 512 << 20   # the copy probe moves 512 MiB each way
 # grid of each is the one recorded
 # (the single right-hand side instantiations: a trailing ", false" where the
 # kernel also has a multi-right-hand-side form)
-CLASSES = (("up", r"k_up_rb<float, \d+(, false)?>"), ("down_p", r"k_down_rb<float, \d+, 1(, false)?>"),
-           ("down_s", r"k_down_rb<float, \d+, 2(, false)?>"), ("down_f64", r"k_down_rb<double, \d+, 0(, false)?>"),
-           ("up_f64", r"k_up_rb<double, \d+(, false)?>"))
+CLASSES = (("up", r"k_up_rb<float, \d+(, false(, \w+)*)?>"), ("down_p", r"k_down_rb<float, \d+, 1(, false(, \w+)*)?>"),
+           ("down_s", r"k_down_rb<float, \d+, 2(, false(, \w+)*)?>"), ("down_f64", r"k_down_rb<double, \d+, 0(, false(, \w+)*)?>"),
+           ("up_f64", r"k_up_rb<double, \d+(, false(, \w+)*)?>"))
 # algorithmic bytes per fine node: every input read once, every output written
 # once.  FP32 complex 8 B, real 4 B: up reads the coarse correction (a quarter
 # node), b, k^2 and writes u (5.5 reals = 22 B); the p-forming down kernel

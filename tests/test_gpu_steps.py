@@ -189,6 +189,26 @@ def test_vcycle_tile_heights(dt):
             assert relerr(to_np(S.vcycle(to_gpu(v))), ref) < CYCLE_TOL[dt], (d, u)
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("omega", [1.0, 0.85])
+@pytest.mark.parametrize("n,coarsest", [(37, 10), (125, 32), (193, 7)])
+def test_vcycle_relaxation_factor(dt, omega, n, coarsest):
+    """The forms of the fused kernels with omega = 1 known at compile time and
+    with any omega, one and two levels per kernel, on grids of less than one tile
+    and one column beyond a tile (125 = 120 + 5, 63 = 60 + 3), against the
+    oracle's cycle."""
+    w = ragged_workload(n=n, coarsest=coarsest, omega=omega)
+    P = oracle_for(w)
+    S = gpu_for(w, dt)
+    v = W.random_complex(w.shape, np.random.default_rng(n))
+    ref = P.mg_apply(v)
+    for tuning in (dict(pair_grid=0), dict(pair_grid=n), dict(pair_grid=0, small_grid=3, down_rows=4, up_rows=8)):
+        S.set_tuning(tail_nodes=9, **tuning)
+        got = to_np(S.vcycle(to_gpu(v)))
+        assert relerr(got, ref) < CYCLE_TOL[dt], tuning
+        assert np.all(got[[0, -1]] == 0) and np.all(got[:, [0, -1]] == 0)
+
+
 @pytest.mark.parametrize("gf,gc,smoother,omega,nu", [(2, 2, "rbgs", 1.05, 1), (1, 2, "jacobi", 0.8, 1),
                                                       (1, 4, "jacobi", 0.5, 2), (1, 1, "rbgs", 1.0, 2)])
 def test_general_cycles(gf, gc, smoother, omega, nu):
