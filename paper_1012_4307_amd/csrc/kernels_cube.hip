@@ -21,8 +21,8 @@
 //
 // What bounds it: the issue and latency of a step (one barrier, an LDS round
 // trip, 160-220 vector instructions of a thread at 2-3 waves per SIMD: 0.8-1.3
-// us), not HBM.  Finest level of a 129^3 cycle, FP64: down 23 us (56 MB, 2.5
-// TB/s), up 37 us (94 MB, 2.6 TB/s); FP32 18 and 26 us.  The separate kernels
+// us), not HBM.  Finest level of a 129^3 cycle, FP64: down 22 us (56 MB, 2.5
+// TB/s), up 32 us (94 MB, 2.9 TB/s).  The separate kernels
 // of the general cycle make seven passes over a level, and their residual +
 // full weighting forms every fine residual 3.4 times (27 per coarse node): the
 // whole cycle took 390 us FP64, 300 us FP32, now 148 and 119 us.
@@ -54,6 +54,16 @@ __device__ __forceinline__ cplx<R> keep(bool c, cplx<R> a) {
 template <typename R>
 __device__ __forceinline__ cplx<R> fma_c(cplx<R> w, cplx<R> u, cplx<R> acc) {
   return mk<R>(fma(-w.im, u.im, fma(w.re, u.re, acc.re)), fma(w.im, u.re, fma(w.re, u.im, acc.im)));
+}
+// GS: omega = 1 known at compile time; a relaxed node then forgets its old
+// value and has no residual, so a down step writes and weights the red residuals
+// alone (five reads in even planes, four in odd ones, of nine) and an up step
+// corrects the black nodes alone.  129^3 FP64 down 24.0 -> 22.1 us, up 34.3 ->
+// 32.1; 97^3 FP32 14.3 -> 13.8 and 18.9 -> 17.8.
+template <bool GS, typename R>
+__device__ __forceinline__ cplx<R> relaxed(R omega, cplx<R> v) {
+  if constexpr (GS) return v;
+  else return omega * v;
 }
 // 1 / d.  FP64: the hardware estimate of 1 / |d|^2 and two Newton steps
 // y <- y + y (1 - a y), which doubles the correct bits each time; a third of
@@ -161,13 +171,14 @@ struct DownTile {
   static constexpr int NT = (PX * ROWS + 63) / 64 * 64;
 };
 
-template <typename R, int CY>
+template <typename R, int CY, bool GS>
 __global__ __launch_bounds__(DownTile<CY>::NT) void k_down3(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                                             cplx<R> *__restrict__ rc, R omega, int tx, int ty, int cz,
                                                             int tiles) {
   constexpr int ROWS = DownTile<CY>::ROWS, NT = DownTile<CY>::NT;
   // [half][thread]; the residuals by position, a in [0, NT), b in [NT, 2 NT)
-  __shared__ cplx<R> sRed[2][NT], sBlk[2][NT], sRes[2][2 * NT];
+  // (GS: only the red ones, at their thread)
+  __shared__ cplx<R> sRed[2][NT], sBlk[2][NT], sRes[2][GS ? NT : 2 * NT];
   const int tid = threadIdx.x;
   const int tile = xcd_tile(tiles);
   if (tile < 0) return;
@@ -222,23 +233,33 @@ __global__ __launch_bounds__(DownTile<CY>::NT) void k_down3(Grid<R> f, Grid<R> c
       for (int e = 0; e < 2; e++) D[e][m0] = inv_d(q.xy[e] + zz + K2[e] * f.beta);
     }
     load(z + 1, m3);
-    T[r][m0] = (omega * B[r][m0]) * D[r][m0];
+    T[r][m0] = relaxed<GS>(omega, B[r][m0]) * D[r][m0];
     sRed[h][tid] = T[r][m0];
     // black on z - 1, and its residual (1 - w)(b + o)
     const cplx<R> tb = offd3(q, r, B[r][m1], T[1 - r][m1], sRed[ho], nb[r], ym, yp, zm[m1], T[r][m2], zp[m1],
                              T[r][m0]);
-    T[r][m1] = (omega * tb) * D[r][m1];
+    T[r][m1] = relaxed<GS>(omega, tb) * D[r][m1];
     sBlk[h][tid] = T[r][m1];
     // residual of plane z - 2: red (1 - w) b + o, black from the step before
-    sRes[h][pos[r]] = offd3(q, r, om1 * B[r][m2], T[1 - r][m2], sBlk[ho], nb[r], ym, yp, zm[m2], T[r][m3], zp[m2],
-                            T[r][m1]);
-    sRes[h][pos[1 - r]] = resB;
-    resB = om1 * tb;
+    if constexpr (GS) {
+      sRes[h][tid] = offd3(q, r, zc<R>(), T[1 - r][m2], sBlk[ho], nb[r], ym, yp, zm[m2], T[r][m3], zp[m2], T[r][m1]);
+    } else {
+      sRes[h][pos[r]] = offd3(q, r, om1 * B[r][m2], T[1 - r][m2], sBlk[ho], nb[r], ym, yp, zm[m2], T[r][m3], zp[m2],
+                              T[r][m1]);
+      sRes[h][pos[1 - r]] = resB;
+      resB = om1 * tb;
+    }
     // full weighting of plane z - 3: its x-y average, then 1/4, 1/2, 1/4 in z
     if (fw) {
-      const cplx<R> *ra = sRes[ho], *rb = sRes[ho] + NT;
-      const cplx<R> S = R(0.25) * rb[ft] + R(0.125) * (ra[ft] + ra[ft + 1] + rb[ft - PX] + rb[ft + PX]) +
-                        R(0.0625) * (ra[ft - PX] + ra[ft - PX + 1] + ra[ft + PX] + ra[ft + PX + 1]);
+      const cplx<R> *ra = sRes[ho], *rb = ra + NT;
+      cplx<R> S;
+      if constexpr (GS && (m0 & 1) == 0)  // red: the centre (b) and the corners (a)
+        S = R(0.25) * ra[ft] + R(0.0625) * (ra[ft - PX] + ra[ft - PX + 1] + ra[ft + PX] + ra[ft + PX + 1]);
+      else if constexpr (GS)  // red: the neighbours in x (a) and y (b)
+        S = R(0.125) * (ra[ft] + ra[ft + 1] + ra[ft - PX] + ra[ft + PX]);
+      else
+        S = R(0.25) * rb[ft] + R(0.125) * (ra[ft] + ra[ft + 1] + rb[ft - PX] + rb[ft + PX]) +
+            R(0.0625) * (ra[ft - PX] + ra[ft - PX + 1] + ra[ft + PX] + ra[ft + PX + 1]);
       if constexpr ((m0 & 1) == 0) {
         acc = acc + R(0.5) * S;  // s - 3 odd: the centre plane
       } else {
@@ -265,7 +286,7 @@ __global__ __launch_bounds__(DownTile<CY>::NT) void k_down3(Grid<R> f, Grid<R> c
 // recomputed from b, as in 2D.  The coarse correction is interpolated in x and
 // y per coarse plane and pair (column a is odd: the mean of two coarse columns;
 // four cached reads a pair), and between two coarse planes in registers.
-template <typename R, int ROWS, int NT>
+template <typename R, int ROWS, int NT, bool GS>
 __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                             const cplx<R> *__restrict__ ec, cplx<R> *__restrict__ u, R omega, int tx,
                                             int ty, int cz, int tiles) {
@@ -302,7 +323,8 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
   }
 
   // per plane (slot = step & 3): b and 1 / D of both columns; of the red node
-  // t, v = t + P e and the post-relaxed u; of the black node v
+  // t, v = t + P e (not GS: its new value does not use it) and the post-relaxed
+  // u; of the black node v
   cplx<R> B[2][4], D[2][4], T[4], vR[4], vB[4], uR[4], nB[2], Ec[2], En[2];
   cplx<R> zm[4], zp[4], nzm, nzp;  // z weights of the planes (uniform)
   R K2[2];
@@ -351,7 +373,7 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
 #pragma unroll
       for (int w = 0; w < 4; w++) raw[w] = ld_c(re, oe[w], cplx<R>());
     }
-    T[m0] = (omega * B[r][m0]) * D[r][m0];
+    T[m0] = relaxed<GS>(omega, B[r][m0]) * D[r][m0];
     sRed[h][tid] = T[m0];
     // black t on z - 1, then v = t + P e on both nodes of the pair
     {
@@ -362,22 +384,25 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
         pb = R(0.5) * (pb + En[r]);
         pr = R(0.5) * (pr + En[1 - r]);
       }
-      vB[m1] = fma_c(omega * tb, D[r][m1], pb);
-      vR[m1] = T[m1] + pr;
+      vB[m1] = fma_c(relaxed<GS>(omega, tb), D[r][m1], pb);
+      if constexpr (!GS) vR[m1] = T[m1] + pr;
       sBlk[h][tid] = vB[m1];
     }
     // red post-relaxation on z - 2
     {
       const cplx<R> o = offd3(q, r, B[r][m2], vB[m2], sBlk[ho], nb[r], ym, yp, zm[m2], vB[m3],
                               zp[m2], vB[m1]);
-      uR[m2] = fma_c(omega * o, D[r][m2], om1 * vR[m2]);
+      if constexpr (GS) uR[m2] = o * D[r][m2];
+      else uR[m2] = fma_c(omega * o, D[r][m2], om1 * vR[m2]);
       sRel[h][tid] = uR[m2];
     }
     // black post-relaxation on z - 3; both nodes are final
     if (s >= 6) {
       const cplx<R> o = offd3(q, r, B[r][m3], uR[m3], sRel[ho], nb[r], ym, yp, zm[m3], uR[m0],
                               zp[m3], uR[m2]);
-      const cplx<R> uB = fma_c(omega * o, D[r][m3], om1 * vB[m3]);
+      cplx<R> uB;
+      if constexpr (GS) uB = o * D[r][m3];
+      else uB = fma_c(omega * o, D[r][m3], om1 * vB[m3]);
       const bool zin = z - 3 >= 1 && z - 3 <= f.n2 - 2;
       const __amdgpu_buffer_rsrc_t ro = plane_rsrc(u, z - 3, z - 3 < f.n2, plane);
       st_c(ro, os[r], keep(q.in[r] && zin, uB));
@@ -437,8 +462,9 @@ void launch_down3_t(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, cplx<R
                     hipStream_t s) {
   const int tx = (c.n0 + CXD - 1) / CXD, ty = (c.n1 + CY - 1) / CY;
   const int tiles = tx * ty * ((c.n2 + cz - 1) / cz);
-  launch_k((k_down3<R, CY>), dim3(xcd_padded(tiles)), dim3(DownTile<CY>::NT), 0, s, f, c, b, rc, omega, tx, ty, cz,
-           tiles);
+  const dim3 grid(xcd_padded(tiles)), block(DownTile<CY>::NT);
+  if (omega == R(1)) launch_k((k_down3<R, CY, true>), grid, block, 0, s, f, c, b, rc, omega, tx, ty, cz, tiles);
+  else launch_k((k_down3<R, CY, false>), grid, block, 0, s, f, c, b, rc, omega, tx, ty, cz, tiles);
 }
 
 template <typename R, int ROWS>
@@ -447,7 +473,9 @@ void launch_up3_t(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cp
   constexpr int NT = (PX * ROWS + 63) / 64 * 64;
   const int tx = (f.n0 + kOwn - 1) / kOwn, ty = (f.n1 + ROWS - 7) / (ROWS - 6);
   const int tiles = tx * ty * ((f.n2 + cz - 1) / cz);
-  launch_k((k_up3<R, ROWS, NT>), dim3(xcd_padded(tiles)), dim3(NT), 0, s, f, c, b, ec, u, omega, tx, ty, cz, tiles);
+  const dim3 grid(xcd_padded(tiles)), block(NT);
+  if (omega == R(1)) launch_k((k_up3<R, ROWS, NT, true>), grid, block, 0, s, f, c, b, ec, u, omega, tx, ty, cz, tiles);
+  else launch_k((k_up3<R, ROWS, NT, false>), grid, block, 0, s, f, c, b, ec, u, omega, tx, ty, cz, tiles);
 }
 
 }  // namespace
