@@ -329,9 +329,11 @@ ecs_status ecs_timing_calibrate(ecs_ctx *ctx, int launches);
  * can change at the level of rounding (in FP32 enough to move a nested
  * solve's outer iteration count by a few percent):
  *   down_rows   coarse rows per block of the fused pre-smoothing/restriction
- *               kernel on grids above small_grid: 2 to 6, 8 (16 in FP32)
+ *               kernel on grids above small_grid: 2 to 6, 8 (16 in FP32, where
+ *               4 runs as 8)
  *   up_rows     fine rows per block of the fused prolongation/post-smoothing
- *               kernel on grids above small_grid: 4, 8, 10, 12, 16 or 32
+ *               kernel on grids above small_grid: 4, 8, 10, 12, 16 or 32 (in
+ *               FP32 8 runs as 16)
  *   small_grid  grids with at most this many nodes per axis use 2 / 4 rows
  *   tail_nodes  the levels with at most this many nodes per axis end the cycle
  *               as one dense map, built at set-up: 3..65.  Above 33, FP32

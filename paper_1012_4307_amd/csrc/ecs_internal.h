@@ -221,6 +221,37 @@ void launch_down_rb_src(const Grid<R> &fine, const Grid<R> &coarse, const DownSr
 template <typename R>
 void launch_up_rb(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u_out,
                   R omega, int rows, hipStream_t s, const RhsSet &rs = one_rhs());
+// The up kernel can apply an operator on the same grid (same k^2) to its result
+// while that is in LDS: y = A u at every node, 0 on the boundary, with the
+// expression of the separate matvec, and the dot products that launch_apply_dot
+// forms (mode kBicgAlpha / kBicgOmega with d0; kUpApplyOnly: none) as
+// up_rb_blocks(...) partials each.  omega = 1 and up_applies<R>(rows) only.
+constexpr int kUpApplyOnly = 3;
+template <typename R>
+struct UpApply {
+  int mode;
+  const cplx<R> *cm0, *cp0, *cm1, *cp1;  // A's weights
+  cplx<R> beta, c;
+  const cplx<R> *d0;
+  cplx<R> *y;
+  cplx<double> *partials;
+};
+// the up kernel's default tall tile, which has the omega = 1 and operator forms
+// as the height 4 has
+template <typename R>
+constexpr int up_tall() {
+  return sizeof(R) == 4 ? 16 : 8;
+}
+template <typename R>
+constexpr bool up_applies(int rows) {
+  return rows == 4 || rows == up_tall<R>();
+}
+inline int up_rb_blocks(int n0, int n1, int rows) {
+  return xcd_padded((n0 + 119) / 120 * ((n1 + rows - 1) / rows));
+}
+template <typename R>
+void launch_up_rb_apply(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec,
+                        cplx<R> *u_out, const UpApply<R> &ap, int rows, hipStream_t s, const RhsSet &rs = one_rhs());
 // two levels of the fused cycle in one kernel (small levels): down over
 // levels l, l+1 (writes u_l, u_{l+1}, b_{l+1} and b_{l+2}); up over levels
 // l+1, l (reads the correction u_{l+2}, writes u_l)

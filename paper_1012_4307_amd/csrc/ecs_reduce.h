@@ -46,8 +46,10 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// block-wide sum of a complex value (blockDim.x == kRedThreads); result in thread 0
-__device__ __forceinline__ cplx<double> block_sum(cplx<double> v, cplx<double> *lds /* >= 4 */) {
+// block-wide sum of a complex value over the first NW waves of the block; result
+// in thread 0.  lds: one entry for each wave of the block.
+template <int NW>
+__device__ __forceinline__ cplx<double> block_sum_n(cplx<double> v, cplx<double> *lds) {
   v.re = wave_sum(v.re);
   v.im = wave_sum(v.im);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -56,8 +58,11 @@ __device__ __forceinline__ cplx<double> block_sum(cplx<double> v, cplx<double> *
   __syncthreads();
   cplx<double> s = mk<double>(0, 0);
   if (threadIdx.x == 0)
-    for (int q = 0; q < kRedThreads / 64; q++) s = s + lds[q];
+    for (int q = 0; q < NW; q++) s = s + lds[q];
   return s;
+}
+__device__ __forceinline__ cplx<double> block_sum(cplx<double> v, cplx<double> *lds /* >= 4 */) {
+  return block_sum_n<kRedThreads / 64>(v, lds);
 }
 
 // This thread's share of a second-stage reduction: x[t] + x[t + B] + ... over

@@ -177,6 +177,7 @@ struct ecs_ctx {
     const void *b;
     void *u;
     int real_bytes;
+    bool no_up;  // the fused cycle without its finest up pass
     hipGraphExec_t exec;
   };
   std::vector<GraphEntry> graphs;
@@ -1031,6 +1032,25 @@ bool fused_updates(const ecs_ctx *C) {
   return P.lt > 0 && !P.pair_start[0];
 }
 
+// Tile heights of level l.  FP32 blocks of 8 coarse / 16 fine rows have eight
+// waves and take the place of the heights 4 and 8 (four waves): they stage 21
+// rows for 16 and 22 for 16 instead of 13 for 8 and 14 for 8.  2049^2 cycle
+// 87.9 -> 85.3 us, a nested FP32 iteration 174 -> 169; 1025^2 cycle 53.9 -> 53.5.
+// FP64 tiles of that height leave two blocks a CU: up 16 rows 120.4 us, 8 rows 118.5.
+bool small_level(const ecs_ctx *C, int l) {
+  return C->hl[l].n[0] <= C->tune.small_grid && C->hl[l].n[1] <= C->tune.small_grid;
+}
+template <typename R>
+int down_rows(const ecs_ctx *C, int l) {
+  if (small_level(C, l)) return 2;
+  return sizeof(R) == 4 && C->tune.down_rows == 4 ? 8 : C->tune.down_rows;
+}
+template <typename R>
+int up_rows(const ecs_ctx *C, int l) {
+  if (small_level(C, l)) return 4;
+  return sizeof(R) == 4 && C->tune.up_rows == 8 ? 16 : C->tune.up_rows;
+}
+
 // Level buffers of the fused cycle: the hierarchy's own (one right-hand
 // side), or for the batched solve arrays holding one copy per right-hand side
 // slot, rhs_stride(level nodes) elements apart.
@@ -1051,22 +1071,68 @@ CycleBufs<R> hierarchy_bufs(ecs_ctx *C) {
   return B;
 }
 
+// Whether the finest up kernel applies A to the cycle's result (UpApply) for a
+// Krylov method in the cycle's dtype: when that level has its own up kernel with
+// the form and two partials per block fit `cap` entries.  The gain is a launch and
+// a pass over u and k^2 on small grids (513^2 Bi-CGSTAB 12.7 -> 12.0 ms); on large
+// ones the kernel takes about what the two took (seven right-hand sides of 1025^2,
+// FP64: 133 us and a reduction, against 71 + 66 with the reduction folded into the
+// next kernel; three sizes batched 170.6 -> 168.7 ms; 2049^2 nested 794 -> 771 ms).
+template <typename R>
+bool fuse_apply(const ecs_ctx *C, int64_t cap) {
+  if (C->prec.kind == ECS_PREC_NONE || !fused_vcycle(C) || C->prec.omega != 1.0) return false;
+  const FusedPlan P = fused_plan(C);
+  const int rows = up_rows<R>(C, 0);
+  return P.lt > 0 && !P.pair_start[0] && up_applies<R>(rows) &&
+         2 * (int64_t)up_rb_blocks(C->hl[0].n[0], C->hl[0].n[1], rows) <= cap;
+}
+
+template <typename R>
+UpApply<R> up_apply(const Grid<R> &A, int mode, const cplx<R> *d0, cplx<R> *y, cplx<double> *partials) {
+  return UpApply<R>{mode, A.cm0, A.cp0, A.cm1, A.cp1, A.beta, A.c, d0, y, partials};
+}
+
+// what launch_apply_dot returns, of the kernel launched with `ap`
+template <typename R>
+BicgFold up_apply_dot(const ecs_ctx *C, const UpApply<R> &ap, const BicgScalars *in, BicgScalars *out, hipStream_t s,
+                      const RhsSet &rs = one_rhs()) {
+  return bicg_fold_or_final(ap.partials, up_rb_blocks(C->hl[0].n[0], C->hl[0].n[1], up_rows<R>(C, 0)),
+                            ap.mode == kBicgAlpha ? 1 : 2, in, out, ap.mode, s, rs);
+}
+
+// The finest level's up pass of the fused cycle, with A applied to its result
+// where ap is given.
+template <typename R>
+void finest_up(ecs_ctx *C, const cplx<R> *b0, const cplx<R> *ec, cplx<R> *u0, const UpApply<R> *ap, const RhsSet &rs) {
+  const double by = (double)rs.count * C->hl[0].nn * sizeof(R);
+  if (ap) {
+    // as below, and d0 (with a dot product) and y
+    TimedScope ts(C, kTUp, by * (ap->mode == kUpApplyOnly ? 7.5 : 9.5));
+    launch_up_rb_apply<R>(grid_M<R>(C, 0), grid_M<R>(C, 1), b0, ec, u0, *ap, up_rows<R>(C, 0), C->stream, rs);
+    return;
+  }
+  // reads the coarse correction, b, k^2; writes u (5.5 reals per node)
+  TimedScope ts(C, kTUp, by * 5.5);
+  launch_up_rb<R>(grid_M<R>(C, 0), grid_M<R>(C, 1), b0, ec, u0, (R)C->prec.omega, up_rows<R>(C, 0), C->stream, rs);
+}
+
 // src (FP32, finest level by its own down kernel): the right-hand side b0 is
 // formed by that kernel from src and stored in b0 == src->out.  cb / rs (the
 // batched solve): the cycle of every right-hand side slot in rs at once, b0
-// and u0 holding one vector per slot rhs_stride(nodes) apart.
+// and u0 holding one vector per slot rhs_stride(nodes) apart.  ap (fuse_apply): the
+// finest up kernel applies A as well; no_up: without the finest up pass (which
+// the caller launches).
 template <typename R>
 void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *src = nullptr,
-                  const CycleBufs<R> *cb = nullptr, const RhsSet &rs = one_rhs()) {
+                  const CycleBufs<R> *cb = nullptr, const RhsSet &rs = one_rhs(), const UpApply<R> *ap = nullptr,
+                  bool no_up = false) {
   const int lc = C->nlev - 1;
   const R om = (R)C->prec.omega;
-  const ecs_tuning &T = C->tune;
   const FusedPlan plan = fused_plan(C);
   const int lt = plan.lt;
   const bool *pair_start = plan.pair_start;
   const CycleBufs<R> B = cb ? *cb : hierarchy_bufs<R>(C);
   const double nr = rs.count;  // algorithmic bytes scale with the right-hand sides of a launch
-  auto small = [&](int l) { return C->hl[l].n[0] <= T.small_grid && C->hl[l].n[1] <= T.small_grid; };
   for (int l = 0; l < lt;) {
     const cplx<R> *b = l == 0 ? b0 : B.b[l];
     if (l == 0 && src) {
@@ -1074,7 +1140,7 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
       // writes b and the coarse residual
       const bool pm = src->mode == kDownSrcP;
       TimedScope ts(C, pm ? kTDownP : kTDownS, nr * C->hl[0].nn * sizeof(R) * (pm ? 9.5 : 7.5));
-      launch_down_rb_src<R>(grid_M<R>(C, 0), grid_M<R>(C, 1), *src, B.b[1], om, small(0) ? 2 : T.down_rows,
+      launch_down_rb_src<R>(grid_M<R>(C, 0), grid_M<R>(C, 1), *src, B.b[1], om, down_rows<R>(C, 0),
                             C->stream, rs);
       l++;
       continue;
@@ -1090,7 +1156,7 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
     }
     // reads b, k^2; writes the coarse residual (3.5 reals per node)
     TimedScope ts(C, l == 0 ? kTDown : kTCoarse, nr * C->hl[l].nn * sizeof(R) * 3.5);
-    launch_down_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), b, B.b[l + 1], om, small(l) ? 2 : T.down_rows,
+    launch_down_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), b, B.b[l + 1], om, down_rows<R>(C, l),
                       C->stream, rs);
     l++;
   }
@@ -1136,12 +1202,13 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
       l -= 2;
       continue;
     }
-    const cplx<R> *b = l == 0 ? b0 : B.b[l];
-    cplx<R> *out = l == 0 ? u0 : B.u[l];
-    // reads the coarse correction, b, k^2; writes u (5.5 reals per node)
-    TimedScope ts(C, l == 0 ? kTUp : kTCoarse, nr * C->hl[l].nn * sizeof(R) * 5.5);
-    launch_up_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), b, B.u[l + 1], out, om, small(l) ? 4 : T.up_rows,
-                    C->stream, rs);
+    if (l == 0) {
+      if (!no_up) finest_up<R>(C, b0, B.u[1], u0, ap, rs);
+      break;
+    }
+    TimedScope ts(C, kTCoarse, nr * C->hl[l].nn * sizeof(R) * 5.5);
+    launch_up_rb<R>(grid_M<R>(C, l), grid_M<R>(C, l + 1), B.b[l], B.u[l + 1], B.u[l], om, up_rows<R>(C, l), C->stream,
+                    rs);
     l--;
   }
 }
@@ -1204,9 +1271,10 @@ constexpr int64_t kEagerLaunches = 16;
 // before the next kernel on the stream) costs more than the host launches it
 // saves, so the automatic mode launches it eagerly.  Per-kernel timing needs
 // eager launches, so graphs are bypassed while any cycle timer is on.
-// Returns false when the caller should launch the cycle eagerly.
+// Returns false when the caller should launch the cycle eagerly.  no_up: the
+// fused cycle without its finest up pass.
 template <typename R>
-bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
+bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, bool no_up = false) {
   for (int k : {kTSmooth, kTCoarse, kTRestrict, kTProlong, kTDown, kTUp, kTDownP, kTDownS})
     if (C->timers[k].on) return false;
   if (C->graph_mode == ECS_GRAPHS_NEVER || C->no_alloc) return false;
@@ -1217,7 +1285,7 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
     if (n >= 4096 || (C->graph_mode == ECS_GRAPHS_AUTO && n <= kEagerLaunches)) return false;
   }
   for (auto &g : C->graphs)
-    if (g.b == b0 && g.u == u0 && g.real_bytes == (int)sizeof(R))
+    if (g.b == b0 && g.u == u0 && g.real_bytes == (int)sizeof(R) && g.no_up == no_up)
       return hipGraphLaunch(g.exec, C->stream) == hipSuccess;
   if (!C->capture && hipStreamCreateWithFlags(&C->capture, hipStreamNonBlocking) != hipSuccess) {
     C->capture = nullptr;
@@ -1227,7 +1295,7 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   if (hipStreamBeginCapture(C->capture, hipStreamCaptureModeRelaxed) != hipSuccess) return false;
   hipStream_t user = C->stream;
   C->stream = C->capture;
-  if (fused_vcycle(C)) vcycle_fused<R>(C, b0, u0);
+  if (fused_vcycle(C)) vcycle_fused<R>(C, b0, u0, nullptr, nullptr, one_rhs(), nullptr, no_up);
   else if (fused_vcycle3(C)) vcycle_fused3<R>(C, b0, u0);
   else mg<R>(C, 0, b0, u0, C->prec.gamma_f, C->prec.gamma_c, true);
   C->stream = user;
@@ -1237,7 +1305,7 @@ bool vcycle_graph(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
   if (e != hipSuccess) return false;
-  C->graphs.push_back({b0, u0, (int)sizeof(R), exec});
+  C->graphs.push_back({b0, u0, (int)sizeof(R), no_up, exec});
   return hipGraphLaunch(exec, C->stream) == hipSuccess;
 }
 
@@ -1250,9 +1318,15 @@ int general_dense_level(const ecs_ctx *C) {
   return l;
 }
 
-// z = M^{-1} v approximately: one cycle from zero on the finest level
+// z = M^{-1} v approximately: one cycle from zero on the finest level; with ap
+// (fuse_apply) A z as well, by a last kernel outside the cycle's graph
 template <typename R>
-void vcycle(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
+void vcycle(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const UpApply<R> *ap = nullptr) {
+  if (ap) {
+    if (vcycle_graph<R>(C, b0, u0, true)) finest_up<R>(C, b0, dev_level<R>(C, 1).u, u0, ap, one_rhs());
+    else vcycle_fused<R>(C, b0, u0, nullptr, nullptr, one_rhs(), ap);
+    return;
+  }
   if (C->nlev == 1) {
     dense_apply<R>(C, 0, b0, u0);
     return;
@@ -1264,22 +1338,30 @@ void vcycle(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0) {
   else mg<R>(C, 0, b0, u0, C->prec.gamma_f, C->prec.gamma_c, true);
 }
 
-// preconditioner application from an FP64 vector into the cycle's dtype
+// preconditioner application from an FP64 vector into the cycle's dtype (ap: of
+// an FP64 cycle only, outer_fuse_apply)
 template <typename RZ>
-void precond(ecs_ctx *C, const cplx<double> *v, cplx<RZ> *z);
+void precond(ecs_ctx *C, const cplx<double> *v, cplx<RZ> *z, const UpApply<double> *ap = nullptr);
 template <>
-void precond<double>(ecs_ctx *C, const cplx<double> *v, cplx<double> *z) {
+void precond<double>(ecs_ctx *C, const cplx<double> *v, cplx<double> *z, const UpApply<double> *ap) {
   if (C->prec.kind == ECS_PREC_NONE) {
     (void)hipMemcpyAsync(z, v, nn_of(C) * sizeof(cplx<double>), hipMemcpyDeviceToDevice, C->stream);
     return;
   }
-  vcycle<double>(C, v, z);
+  vcycle<double>(C, v, z, ap);
 }
 template <>
-void precond<float>(ecs_ctx *C, const cplx<double> *v, cplx<float> *z) {
+void precond<float>(ecs_ctx *C, const cplx<double> *v, cplx<float> *z, const UpApply<double> *) {
   cplx<float> *b0 = C->L32[0].b;
   launch_cast<double, float>(v, b0, nn_of(C), C->stream);
   vcycle<float>(C, b0, z);
+}
+// Whether an outer Krylov method's matvec runs inside the FP64 cycle: the
+// partials of a batched right-hand side's share, so that a system solved in a
+// batch and alone take the same kernels; not while the matvec is timed.
+template <typename RZ>
+bool outer_fuse_apply(const ecs_ctx *C) {
+  return sizeof(RZ) == 8 && !C->timers[kTApply].on && fuse_apply<double>(C, kRhsPartials);
 }
 
 // ----------------------------------------------------------- Krylov
@@ -1347,6 +1429,9 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
   // fused (FP32): the finest down kernel forms p (into the other p buffer:
   // blocks read the old p around their tiles) and s; the same values either way
   const bool fuse = sizeof(R) == 4 && fused_updates(C);
+  const bool fa = fuse_apply<R>(C, kRedBlocks * (kMaxRestart + 2));
+  const UpApply<R> av = up_apply<R>(gA, kBicgAlpha, frh, fv, C->partials);
+  const UpApply<R> at = up_apply<R>(gA, kBicgOmega, fs, ft, C->partials);
   cplx<R> *p_old = reinterpret_cast<cplx<R> *>(K.fp), *p_new = reinterpret_cast<cplx<R> *>(K.fp2);
   // x = sum of alpha_i p^_i + omega_i s^_i: each step keeps its p^, s^ and
   // scalars, and x is updated once per K.fdefer steps (the same values as
@@ -1358,21 +1443,23 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
     cplx<R> *fph = ph0 + (int64_t)slot * K.ld, *fsh = sh0 + (int64_t)slot * K.ld;
     if (fuse) {
       const DownSrc<R> sp{kDownSrcP, fr, p_old, fv, p_new, beta.in, beta.out, beta.partials, beta.nb};
-      vcycle_fused<R>(C, p_new, fph, &sp);
+      vcycle_fused<R>(C, p_new, fph, &sp, nullptr, one_rhs(), fa ? &av : nullptr);
       std::swap(p_old, p_new);
     } else {
       launch_bicg_p<R>(p_old, fr, fv, n, beta, s);
-      vcycle<R>(C, p_old, fph);
+      vcycle<R>(C, p_old, fph, fa ? &av : nullptr);
     }
-    const BicgFold alpha = launch_apply_dot<R, R>(gA, fph, fv, frh, kBicgAlpha, C->partials, S, S1, s);
+    const BicgFold alpha = fa ? up_apply_dot<R>(C, av, S, S1, s)
+                              : launch_apply_dot<R, R>(gA, fph, fv, frh, kBicgAlpha, C->partials, S, S1, s);
     if (fuse) {
       const DownSrc<R> ss{kDownSrcS, fr, nullptr, fv, fs, alpha.in, alpha.out, alpha.partials, alpha.nb};
-      vcycle_fused<R>(C, fs, fsh, &ss);
+      vcycle_fused<R>(C, fs, fsh, &ss, nullptr, one_rhs(), fa ? &at : nullptr);
     } else {
       launch_bicg_s<R>(fs, fr, fv, n, alpha, s);
-      vcycle<R>(C, fs, fsh);
+      vcycle<R>(C, fs, fsh, fa ? &at : nullptr);
     }
-    const BicgFold omega = launch_apply_dot<R, R>(gA, fsh, ft, fs, kBicgOmega, C->partials, S1, S2, s);
+    const BicgFold omega = fa ? up_apply_dot<R>(C, at, S1, S2, s)
+                              : launch_apply_dot<R, R>(gA, fsh, ft, fs, kBicgOmega, C->partials, S1, S2, s);
     beta = launch_bicg_r<R>(fr, fs, ft, frh, n, C->partials, omega, S2, S, K.fcoef + 2 * slot, s);
     if (slot == K.fdefer - 1 || it == iters - 1) launch_bicg_xdefer<R>(x, ph0, sh0, K.ld, slot + 1, K.fcoef, n, s);
   }
@@ -1509,7 +1596,10 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       cplx<double> *vj = K.V + (int64_t)j * ld, *w = vj + ld;
       cplx<RZ> *zj = flexible ? Z + (int64_t)j * ld : tz;
       if (d->inner > 0) inner_bicgstab<RZ>(C, K, vj, zj, d->inner);
-      else precond<RZ>(C, vj, zj);
+      else if (outer_fuse_apply<RZ>(C)) {
+        const UpApply<double> aw = up_apply<double>(grid_A(C), kUpApplyOnly, nullptr, w, nullptr);
+        return precond<RZ>(C, vj, zj, &aw);
+      } else precond<RZ>(C, vj, zj);
       TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 24));
       launch_apply<double, RZ, double>(grid_A(C), zj, w, s);
     };
@@ -1613,17 +1703,20 @@ BicgFold bicg_open_step(ecs_ctx *C, const KrylovBufs &K) {
   hipStream_t s = C->stream;
   BicgScalars *S = C->bs;
   cplx<RZ> *ph = reinterpret_cast<cplx<RZ> *>(K.ph);
+  const bool fa = outer_fuse_apply<RZ>(C);
+  const UpApply<double> av = up_apply<double>(grid_A(C), kBicgAlpha, K.rh, K.v, C->partials);
   if (bicg_fuse<RZ>(C, K)) {
     if constexpr (sizeof(RZ) == 8) {
       cplx<double> *p_old = C->bicg_pflip ? K.p2 : K.p, *p_new = C->bicg_pflip ? K.p : K.p2;
       const DownSrc<double> sp{kDownSrcP, K.r, p_old, K.v, p_new, S, nullptr, nullptr, 0};
-      vcycle_fused<double>(C, p_new, ph, &sp);
+      vcycle_fused<double>(C, p_new, ph, &sp, nullptr, one_rhs(), fa ? &av : nullptr);
       C->bicg_pflip ^= 1;
     }
   } else {
     launch_bicg_p<double>(K.p, K.r, K.v, n, bicg_scalars(S), s);
-    precond<RZ>(C, K.p, ph);
+    precond<RZ>(C, K.p, ph, fa ? &av : nullptr);
   }
+  if (fa) return up_apply_dot<double>(C, av, S, S + kMaxRhs, s);
   TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
   return launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S + kMaxRhs, s);
 }
@@ -1635,17 +1728,21 @@ void bicg_close_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x, const Bic
   BicgScalars *S = C->bs, *S1 = S + kMaxRhs, *S2 = S + 2 * kMaxRhs;
   cplx<RZ> *ph = reinterpret_cast<cplx<RZ> *>(K.ph);
   cplx<RZ> *sh = reinterpret_cast<cplx<RZ> *>(K.sh);
+  const bool fa = outer_fuse_apply<RZ>(C);
+  const UpApply<double> at = up_apply<double>(grid_A(C), kBicgOmega, K.s, K.tt, C->partials);
   if (bicg_fuse<RZ>(C, K)) {
     if constexpr (sizeof(RZ) == 8) {
       const DownSrc<double> ss{kDownSrcS, K.r, nullptr, K.v, K.s, alpha.in, alpha.out, alpha.partials, alpha.nb};
-      vcycle_fused<double>(C, K.s, sh, &ss);
+      vcycle_fused<double>(C, K.s, sh, &ss, nullptr, one_rhs(), fa ? &at : nullptr);
     }
   } else {
     launch_bicg_s<double>(K.s, K.r, K.v, n, alpha, s);
-    precond<RZ>(C, K.s, sh);
+    precond<RZ>(C, K.s, sh, fa ? &at : nullptr);
   }
   BicgFold omega;
-  {
+  if (fa) {
+    omega = up_apply_dot<double>(C, at, S1, S2, s);
+  } else {
     TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
     omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s);
   }
@@ -1783,7 +1880,8 @@ CycleBufs<RZ> batch_bufs(ecs_ctx *C, const KrylovBufs &K) {
 
 // z = M^{-1} v for every slot in rs (FP64 in, cycle dtype out)
 template <typename RZ>
-void batch_precond(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx<RZ> *z, const RhsSet &rs) {
+void batch_precond(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx<RZ> *z, const RhsSet &rs,
+                   const UpApply<double> *ap) {
   const int64_t n = nn_of(C);
   if (!fused_vcycle(C)) {  // one slot, slot 0: the single solve's cycle
     precond<RZ>(C, v, z);
@@ -1795,7 +1893,7 @@ void batch_precond(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx<
     launch_cast<double, float>(v, b, n, C->stream, rs);
     vcycle_fused<float>(C, b, z, nullptr, &B, rs);
   } else {
-    vcycle_fused<double>(C, v, z, nullptr, &B, rs);
+    vcycle_fused<double>(C, v, z, nullptr, &B, rs, ap);
   }
 }
 
@@ -1815,32 +1913,39 @@ void batch_step(ecs_ctx *C, const KrylovBufs &K, const RhsSet &rs) {
   if (!K.p2) C->bicg_pflip = 0;  // the context may have had another cycle type before
   cplx<double> *p = C->bicg_pflip ? K.p2 : K.p;
   bool fuse = false;
+  const bool fa = outer_fuse_apply<RZ>(C);
+  const UpApply<double> av = up_apply<double>(grid_A(C), kBicgAlpha, K.rh, K.v, C->partials);
+  const UpApply<double> at = up_apply<double>(grid_A(C), kBicgOmega, K.s, K.tt, C->partials);
   if constexpr (sizeof(RZ) == 8) {
     fuse = K.p2 && fused_updates(C);
     if (fuse) {
       cplx<double> *q = C->bicg_pflip ? K.p : K.p2;
       const CycleBufs<double> B = batch_bufs<double>(C, K);
       const DownSrc<double> sp{kDownSrcP, K.r, p, K.v, q, S, nullptr, nullptr, 0};
-      vcycle_fused<double>(C, q, ph, &sp, &B, rs);
+      vcycle_fused<double>(C, q, ph, &sp, &B, rs, fa ? &av : nullptr);
       C->bicg_pflip ^= 1;
     }
   }
   if (!fuse) {
     launch_bicg_p<double>(p, K.r, K.v, n, bicg_scalars(S), s, rs);
-    batch_precond<RZ>(C, K, p, ph, rs);
+    batch_precond<RZ>(C, K, p, ph, rs, fa ? &av : nullptr);
   }
-  const BicgFold alpha = launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S1, s, rs);
+  const BicgFold alpha =
+      fa ? up_apply_dot<double>(C, av, S, S1, s, rs)
+         : launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S1, s, rs);
   if (fuse) {
     if constexpr (sizeof(RZ) == 8) {
       const CycleBufs<double> B = batch_bufs<double>(C, K);
       const DownSrc<double> ss{kDownSrcS, K.r, nullptr, K.v, K.s, alpha.in, alpha.out, alpha.partials, alpha.nb};
-      vcycle_fused<double>(C, K.s, sh, &ss, &B, rs);
+      vcycle_fused<double>(C, K.s, sh, &ss, &B, rs, fa ? &at : nullptr);
     }
   } else {
     launch_bicg_s<double>(K.s, K.r, K.v, n, alpha, s, rs);
-    batch_precond<RZ>(C, K, K.s, sh, rs);
+    batch_precond<RZ>(C, K, K.s, sh, rs, fa ? &at : nullptr);
   }
-  const BicgFold omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s, rs);
+  const BicgFold omega =
+      fa ? up_apply_dot<double>(C, at, S1, S2, s, rs)
+         : launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s, rs);
   launch_bicg_xr<double, RZ>(K.bx, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s, rs);
 }
 

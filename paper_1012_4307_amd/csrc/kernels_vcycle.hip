@@ -26,8 +26,6 @@ namespace ecs {
 
 namespace {
 
-constexpr int NT = 256;
-
 template <typename R>
 __device__ __forceinline__ cplx<R> zero_c() {
   return mk<R>(0, 0);
@@ -72,13 +70,20 @@ __device__ __forceinline__ cplx<R> inv_cycle(cplx<R> d) {
   return mk<R>(d.re * s, -d.im * s);
 }
 
+// Waves of a block by its tile height: a tall tile repeats fewer halo rows, and
+// with eight waves a wave still holds three rows in registers (four waves and 16
+// rows: six).  2049^2 FP32, down 15.7 -> 14.4 us with 8 coarse rows and eight waves
+// instead of 4 and four, up 22.9 -> 21.6 with 16 and eight instead of 8 and four.
+constexpr int down_waves(int coarse_rows) { return coarse_rows >= 8 ? 8 : 4; }
+constexpr int up_waves(int rows) { return rows >= 16 ? 8 : 4; }
+
 // GS: omega = 1 (Gauss-Seidel, the QD set-ups' sweep) known at compile time.  A
 // relaxed node then forgets its old value and has no residual: the down kernel
 // stores no black residuals (two arrays of LDS instead of three) and restricts
 // five values instead of nine, the up kernel corrects only the black nodes and
 // drops the terms of the old values.  The values are those of omega = 1 in the
 // general kernel (1 x and 0 x + y are exact).  Finest level of 2049^2, FP32:
-// down 16.2 -> 15.7 us, up 24.4 -> 23.5; 1025^2 up 10.5 -> 10.0.
+// down 16.2 -> 15.7 us, up 24.4 -> 23.5 (tiles of four waves).
 template <bool GS, typename R>
 __device__ __forceinline__ cplx<R> relaxed(R omega, cplx<R> v) {
   if constexpr (GS) return v;
@@ -101,13 +106,14 @@ __device__ __forceinline__ cplx<R> relaxed(R omega, cplx<R> v) {
 // partials, whose loads go out before the tile's and whose sums are taken while
 // those are in flight (BicgFold).
 template <typename R, int CY, int SRC, bool MR, bool FOLD, bool GS>
-__global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
+__global__ __launch_bounds__(64 * down_waves(CY)) void k_down_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                                 DownSrc<R> src, cplx<R> *__restrict__ rc, R omega,
                                                 int tiles_x, int tiles, RhsSet rs) {
   constexpr int CX = 61;
   constexpr int WX = 2 * CX + 5;          // 127 staged columns
   constexpr int WY = 2 * CY + 5;
-  constexpr int RPW = (WY + 3) / 4;       // rows per wave
+  constexpr int NW = down_waves(CY);
+  constexpr int RPW = (WY + NW - 1) / NW;  // rows per wave
   // relaxed iterate by colour; the residual by colour, the red one in the
   // red iterate's slots (in the residual phase a lane reads only its own red
   // node there, before overwriting it): three arrays keep eight blocks per CU
@@ -168,7 +174,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   cplx<R> xR[RPW], xB[RPW], vR[RPW], vB[RPW], pR[RPW], pB[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     const int j = gy0 + ly;
     const bool yin = ly < WY && j >= 1 && j <= n1 - 2;
     const int jc = yin ? j : 1;
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   if constexpr (SRC != kDownSrcB) {
     const BicgScalars *S = src.S;
     if constexpr (FOLD) {
-      __shared__ cplx<double> red[NT / 64];
+      __shared__ cplx<double> red[NW];
       __shared__ BicgScalars sh;
       fold_finish<NP>(fold, src.S, src.S_out, src.nb, SRC == kDownSrcP ? kBicgNormRho : kBicgAlpha, red, &sh);
       S = &sh;
@@ -221,7 +227,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
     const bool ownb = ca + 1 >= 3 && ca + 1 < 3 + 2 * CX && ib < n0;
 #pragma unroll
     for (int r = 0; r < RPW; r++) {
-      const int ly = wv + 4 * r, j = gy0 + ly;
+      const int ly = wv + NW * r, j = gy0 + ly;
       if (ly >= 3 && ly < 3 + 2 * CY && j < n1) {
         cplx<R> *row = src.out + (int64_t)j * n0;
         // component selects: a select of the structs goes through scratch
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   // per-lane exit state through the unrolled row loops.
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     if (ly < WY) {
       const int j = gy0 + ly;
       const bool yin = j >= 1 && j <= n1 - 2;
@@ -264,7 +270,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   cplx<R> resB[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     resB[r] = zero_c<R>();
     if (ly >= 1 && ly <= WY - 2) {
       if (pin) {
@@ -286,7 +292,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   const cplx<R> wRo = ared ? xpR : xmR, wRn = ared ? xmR : xpR;
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     if (ly < WY) {
       const int j = gy0 + ly;
       const bool yin = j >= 1 && j <= n1 - 2;
@@ -307,7 +313,7 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
   // I - I0 + 1, row y = 2 (J - J0) + 3 (rows y +- 1 have the other colouring).
   if (lane < CX) {
     const int I = I0 + lane, P = lane + 1;
-    for (int cy = wv; cy < CY; cy += 4) {
+    for (int cy = wv; cy < CY; cy += NW) {
       const int J = J0 + cy;
       if (I >= c.n0 || J >= c.n1) continue;
       cplx<R> acc = zero_c<R>();
@@ -333,28 +339,51 @@ __global__ __launch_bounds__(NT) void k_down_rb(Grid<R> f, Grid<R> c, const cplx
 // on the tile reads red values on ring 1.  Column a = x0 - 4 + 2 lane is even,
 // so both columns of pair l interpolate from coarse column x0/2 - 2 + l
 // (= staged coarse column l).
-template <typename R, int TY, bool MR, bool GS>
-__global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
+//
+// MODE != 0: y = A u of the result as well (UpApply), which needs u on ring 1
+// and so a fourth halo row on each side (the four halo columns hold it already;
+// 12 and 16 staged rows for TY = 4 and 8 take the row slots that 10 and 14 do).
+// The operator's separate pass reads u and k^2 again and is one more launch.
+// Up and matvec, us: 513^2 FP64 7.7 + 6.3 -> 10.8; 2049^2 FP32 21.6 + 23.3 -> 47.1
+// with (r^, v), 21.6 + 21.2 -> 39.1 with (t, s) (3.5-4 TB/s: the waves that its
+// registers leave, 16 a CU, do not cover the memory latency).
+template <typename R, int TY, bool MR, bool GS, int MODE>
+__global__ __launch_bounds__(64 * up_waves(TY)) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                               const cplx<R> *__restrict__ ec, cplx<R> *__restrict__ u_out, R omega,
-                                              int tiles_x, int tiles, RhsSet rs) {
+                                              int tiles_x, int tiles, RhsSet rs, UpApply<R> A) {
   constexpr int TX = 120;
-  constexpr int WY = TY + 6;
-  constexpr int RPW = (WY + 3) / 4;
-  constexpr int CWX = TX / 2 + 5, CWY = TY / 2 + 3;
+  constexpr int H = MODE != 0 ? 4 : 3;  // halo rows
+  constexpr int WY = TY + 2 * H;
+  constexpr int NW = up_waves(TY);
+  constexpr int RPW = (WY + NW - 1) / NW;
+  constexpr int CWX = TX / 2 + 5, CWY = TY / 2 + (MODE != 0 ? 4 : 3);
+  constexpr bool DOT = MODE == kBicgAlpha || MODE == kBicgOmega;
   __shared__ cplx<R> sR[WY][64], sB[WY][64];
   __shared__ cplx<R> se[CWY][CWX];
+  __shared__ cplx<double> red[DOT ? NW : 1];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile = xcd_tile(tiles);
-  if (tile < 0) return;
   if constexpr (MR) {
     const int64_t q = rhs_index(rs), sf = rhs_stride((int64_t)f.n0 * f.n1);
     b += q * sf;
     u_out += q * sf;
     ec += q * rhs_stride((int64_t)c.n0 * c.n1);
+    if constexpr (MODE != 0) A.y += q * sf;
+    if constexpr (DOT) {
+      A.d0 += q * sf;
+      A.partials += q * kRhsPartials;
+    }
+  }
+  if (tile < 0) {
+    if (DOT && threadIdx.x == 0) {
+      A.partials[blockIdx.x] = mk<double>(0, 0);
+      if (MODE == kBicgOmega) A.partials[gridDim.x + blockIdx.x] = mk<double>(0, 0);
+    }
+    return;
   }
   const int x0 = (tile % tiles_x) * TX, y0 = (tile / tiles_x) * TY;
-  const int gx0 = x0 - 4, gy0 = y0 - 3;
-  const int cx0 = x0 / 2 - 2, cy0 = y0 / 2 - 1;  // coarse staging origin
+  const int gx0 = x0 - 4, gy0 = y0 - H;
+  const int cx0 = x0 / 2 - 2, cy0 = y0 / 2 - H / 2;  // coarse staging origin
   const int n0 = f.n0, n1 = f.n1;
   const R om1 = R(1) - omega;
   const int ia = gx0 + 2 * lane, ib = ia + 1;  // ia even
@@ -374,11 +403,14 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
   const uint32_t obR = col_off<cplx<R>>(inR, iR), obB = col_off<cplx<R>>(inBk, iBk);
   const uint32_t okR = col_off<R>(inR, iR), okB = col_off<R>(inBk, iBk);
 
+  const bool own_x = lane >= 2 && lane <= 61;
+  const uint32_t osR = col_off<cplx<R>>(own_x && iR < n0, iR), osB = col_off<cplx<R>>(own_x && iBk < n0, iBk);
+  const int je = min(y0 + TY, n1);
   cplx<R> vR[RPW], vB[RPW], bR[RPW], bB[RPW], dR[RPW], dB[RPW], cym[RPW], cyp[RPW];
   R kR[RPW], kB[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     const int j = gy0 + ly;
     const bool yin = ly < WY && j >= 1 && j <= n1 - 2;
     const int jc = yin ? j : 1;
@@ -390,7 +422,7 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
     kR[r] = ld_r(rk, okR + qk, R());
     kB[r] = ld_r(rk, okB + qk, R());
   }
-  for (int q = threadIdx.x; q < CWY * CWX; q += NT) {
+  for (int q = threadIdx.x; q < CWY * CWX; q += 64 * NW) {
     const int cy = q / CWX, cx = q % CWX;
     const int I = cx0 + cx, J = cy0 + cy;
     se[cy][cx] = (I >= 0 && I < c.n0 && J >= 0 && J < c.n1) ? ec[(int64_t)J * c.n0 + I] : zero_c<R>();
@@ -402,7 +434,7 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
   // per-lane exit state through the unrolled row loops.
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     if (ly < WY) {
       const int j = gy0 + ly;
       const bool yin = j >= 1 && j <= n1 - 2;
@@ -426,7 +458,7 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
   const cplx<R> wBo = ared ? xmB : xpB, wBn = ared ? xpB : xmB;  // black node: own-pair / other-pair weights
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     vB[r] = zero_c<R>();
     if (ly >= 1 && ly <= WY - 2) {  // ring 3: red t only
       const int j = gy0 + ly;
@@ -467,7 +499,7 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
   const cplx<R> wRo = ared ? xpR : xmR, wRn = ared ? xmR : xpR;  // own-pair / other-pair neighbour weights
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     const int j = gy0 + ly;
     if (ly >= 2 && ly <= WY - 3 && j >= 1 && j <= n1 - 2) {
       if (qin && inR) {
@@ -480,26 +512,113 @@ __global__ __launch_bounds__(NT) void k_up_rb(Grid<R> f, Grid<R> c, const cplx<R
     }
   }
   __syncthreads();
-  // black relaxation on the owned tile (pairs 2..61, rows 3..TY+2); write
-  // both nodes of every owned pair
-  const bool own_x = lane >= 2 && lane <= 61;
-  const uint32_t osR = col_off<cplx<R>>(own_x && iR < n0, iR), osB = col_off<cplx<R>>(own_x && iBk < n0, iBk);
-  const __amdgpu_buffer_rsrc_t ro = rows_rsrc(u_out, y0, min(y0 + TY, n1), n0);
+  // black relaxation on the owned tile (pairs 2..61, rows H..TY+H-1) and, for
+  // the operator, on the ring around it; write both nodes of every owned pair
+  const __amdgpu_buffer_rsrc_t ro = rows_rsrc(u_out, y0, je, n0);
+  // the operator's operands, in flight during the relaxation: its weights, k^2
+  // again (cached) and d0.  Loaded with the first loads they cost FP32 a block
+  // per CU (2049^2: 54.6 / 46.7 us instead of 47.1 / 39.1), after the relaxation
+  // their latency shows (513^2 FP64 11.8 us instead of 10.8).
+  cplx<R> aRl = zero_c<R>(), aRr = aRl, aBl = aRl, aBr = aRl;  // towards the left / right neighbour
+  cplx<R> d0R[RPW], d0B[RPW], aym[RPW], ayp[RPW];
+  if constexpr (MODE != 0) {
+    if (inR) aRl = A.cm0[iR], aRr = A.cp0[iR];
+    if (inBk) aBl = A.cm0[iBk], aBr = A.cp0[iBk];
+    const __amdgpu_buffer_rsrc_t rd = rows_rsrc(A.d0, y0, je, n0);
+#pragma unroll
+    for (int r = 0; r < RPW; r++) {
+      const int ly = wv + NW * r, j = gy0 + ly;
+      if (ly < H || ly >= TY + H) continue;
+      const bool yin = j >= 1 && j <= n1 - 2;
+      const int jc = yin ? j : 1;
+      aym[r] = yin ? A.cm1[jc] : zero_c<R>();
+      ayp[r] = yin ? A.cp1[jc] : zero_c<R>();
+      if constexpr (DOT) {
+        const uint32_t qd = row_off<cplx<R>>(j - y0, n0);
+        d0R[r] = ld_c(rd, osR + qd, cplx<R>());
+        d0B[r] = ld_c(rd, osB + qd, cplx<R>());
+      }
+      const uint32_t qk = row_off<R>(j - jl, n0);
+      kR[r] = ld_r(rk, okR + qk, R());
+      kB[r] = ld_r(rk, okB + qk, R());
+    }
+  }
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
-    const int ly = wv + 4 * r;
+    const int ly = wv + NW * r;
     const int j = gy0 + ly;
-    if (ly >= 3 && ly < TY + 3 && j < n1) {
+    if (ly >= 3 && ly <= WY - 4 && j < n1) {
       cplx<R> outB = vB[r];
-      if (own_x && inBk && j >= 1 && j <= n1 - 2) {
+      if ((MODE != 0 || own_x) && inBk && j >= 1 && j <= n1 - 2) {
         const cplx<R> o =
             wBo * sR[ly][lane] + wBn * sR[ly][psc] + cym[r] * sR[ly - 1][lane] + cyp[r] * sR[ly + 1][lane];
         if constexpr (GS) outB = (bB[r] + o) * dB[r];
         else outB = om1 * outB + omega * ((bB[r] + o) * dB[r]);
       }
-      const uint32_t qo = row_off<cplx<R>>(j - y0, n0);
-      st_c(ro, osR + qo, vR[r]);
-      st_c(ro, osB + qo, outB);
+      if constexpr (MODE != 0) {
+        vB[r] = outB;
+        sB[ly][lane] = outB;  // the phase reads red values only
+      }
+      if (ly >= H && ly < TY + H) {
+        const uint32_t qo = row_off<cplx<R>>(j - y0, n0);
+        st_c(ro, osR + qo, vR[r]);
+        st_c(ro, osB + qo, outB);
+      }
+    }
+  }
+  if constexpr (MODE != 0) {
+    __syncthreads();
+    // y = A u on the owned tile: a red node's black neighbours and the other
+    // way round (lanes 2..61 own, so lane -+ 1 holds the neighbouring pair)
+    const __amdgpu_buffer_rsrc_t ry = rows_rsrc(A.y, y0, je, n0);
+    cplx<double> a0 = mk<double>(0, 0);
+    double a1 = 0;
+#pragma unroll
+    for (int r = 0; r < RPW; r++) {
+      const int ly = wv + NW * r;
+      const int j = gy0 + ly;
+      if (ly >= H && ly < TY + H && j < n1) {
+        const bool yin = j >= 1 && j <= n1 - 2;
+        cplx<R> yR = zero_c<R>(), yB = zero_c<R>();
+        const cplx<R> uB = sB[ly][pq], uR = sR[ly][psc];
+        if (yin && inR) {
+          const cplx<R> d = aRl + aRr + aym[r] + ayp[r] + (kR[r] * A.beta + A.c);
+          cplx<R> o = aRl * (ared ? uB : vB[r]) + aRr * (ared ? vB[r] : uB);
+          o = o + aym[r] * sB[ly - 1][lane] + ayp[r] * sB[ly + 1][lane];
+          yR = d * vR[r] - o;
+        }
+        if (yin && inBk) {
+          const cplx<R> d = aBl + aBr + aym[r] + ayp[r] + (kB[r] * A.beta + A.c);
+          cplx<R> o = aBl * (ared ? vR[r] : uR) + aBr * (ared ? uR : vR[r]);
+          o = o + aym[r] * sR[ly - 1][lane] + ayp[r] * sR[ly + 1][lane];
+          yB = d * vB[r] - o;
+        }
+        const uint32_t qo = row_off<cplx<R>>(j - y0, n0);
+        st_c(ry, osR + qo, yR);
+        st_c(ry, osB + qo, yB);
+        if (DOT && own_x) {
+          const cplx<double> vr = cvt<double>(yR), dr = cvt<double>(d0R[r]);
+          const cplx<double> vb = cvt<double>(yB), db = cvt<double>(d0B[r]);
+          if (MODE == kBicgAlpha) {
+            a0 = a0 + conjg(dr) * vr;
+            a0 = a0 + conjg(db) * vb;
+          } else {
+            a0 = a0 + conjg(vr) * dr;
+            a0 = a0 + conjg(vb) * db;
+            a1 += abs2(vr);
+            a1 += abs2(vb);
+          }
+        }
+      }
+    }
+    if constexpr (DOT) {
+      const cplx<double> s0 = block_sum_n<NW>(a0, red);
+      if (threadIdx.x == 0) A.partials[blockIdx.x] = s0;
+      if constexpr (MODE == kBicgOmega) {
+        __syncthreads();
+        const cplx<double> s1 = block_sum_n<NW>(mk<double>(a1, 0), red);
+        if (threadIdx.x == 0) A.partials[gridDim.x + blockIdx.x] = s1;
+      }
     }
   }
 }
@@ -755,7 +874,7 @@ void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b
   constexpr int CX = 61;
   const int tx = (coarse.n0 + CX - 1) / CX;
   const int tiles = tx * ((coarse.n1 + rows - 1) / rows);
-  const dim3 grid(xcd_padded(tiles), rs.count), block(NT);
+  const dim3 grid(xcd_padded(tiles), rs.count), block(64 * down_waves(rows));
   const auto go = [&](auto cy) {
     launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD, false>), grid, block, 0, s, fine, coarse, b, src, rc,
              omega, tx, tiles, rs);
@@ -766,17 +885,28 @@ void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b
   };
   // the heights that the schedule takes by default have the omega = 1 form
   if (omega == R(1) && rows == 2) return go_gs(std::integral_constant<int, 2>());
-  if (omega == R(1) && rows == 4) return go_gs(std::integral_constant<int, 4>());
+  if constexpr (sizeof(R) == 8) {
+    if (omega == R(1) && rows == 4) return go_gs(std::integral_constant<int, 4>());
+  } else {
+    if (omega == R(1) && rows == 8) return go_gs(std::integral_constant<int, 8>());
+  }
   switch (rows) {
     case 2: go(std::integral_constant<int, 2>()); break;
     case 3: go(std::integral_constant<int, 3>()); break;
-    case 4: go(std::integral_constant<int, 4>()); break;
     case 5: go(std::integral_constant<int, 5>()); break;
     case 6: go(std::integral_constant<int, 6>()); break;
+    case 4:
+      if constexpr (sizeof(R) == 8) {  // FP32: 8
+        go(std::integral_constant<int, 4>());
+        break;
+      }
+      [[fallthrough]];
     case 16:
       if constexpr (sizeof(R) == 4) {
-        go(std::integral_constant<int, 16>());
-        break;
+        if (rows == 16) {
+          go(std::integral_constant<int, 16>());
+          break;
+        }
       }
       [[fallthrough]];
     default: go(std::integral_constant<int, 8>()); break;
@@ -809,26 +939,46 @@ void launch_down_rb_src(const Grid<R> &fine, const Grid<R> &coarse, const DownSr
   }
 }
 
+template <typename R, int TY, bool MR, bool GS, int MODE>
+void launch_up(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u_out,
+               R omega, hipStream_t s, const RhsSet &rs, const UpApply<R> &ap) {
+  const int tx = (fine.n0 + 119) / 120;
+  const int tiles = tx * ((fine.n1 + TY - 1) / TY);
+  launch_k((k_up_rb<R, TY, MR, GS, MODE>), dim3(up_rb_blocks(fine.n0, fine.n1, TY), rs.count), dim3(64 * up_waves(TY)), 0, s, fine,
+           coarse, b, ec, u_out, omega, tx, tiles, rs, ap);
+}
+
 template <typename R, bool MR>
-void launch_up_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u_out,
-                  R omega, int rows, hipStream_t s, const RhsSet &rs) {
-  constexpr int TX = 120;
-  const int tx = (fine.n0 + TX - 1) / TX;
-  const int tiles = tx * ((fine.n1 + rows - 1) / rows);
-  const dim3 grid(xcd_padded(tiles), rs.count), block(NT);
-  const auto go = [&](auto ty, auto gs) {
-    launch_k((k_up_rb<R, decltype(ty)::value, MR, decltype(gs)::value>), grid, block, 0, s, fine, coarse, b, ec, u_out,
-             omega, tx, tiles, rs);
-  };
-  if (omega == R(1) && rows == 4) return go(std::integral_constant<int, 4>(), std::true_type());
-  if (omega == R(1) && rows == 8) return go(std::integral_constant<int, 8>(), std::true_type());
+void launch_up_mr(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u, R omega,
+                  int rows, hipStream_t s, const RhsSet &rs) {
+  const UpApply<R> no{};
+  if (omega == R(1) && rows == 4) return launch_up<R, 4, MR, true, 0>(f, c, b, ec, u, omega, s, rs, no);
+  constexpr int kTall = up_tall<R>();
+  if (omega == R(1) && rows == kTall) return launch_up<R, kTall, MR, true, 0>(f, c, b, ec, u, omega, s, rs, no);
   switch (rows) {
-    case 4: go(std::integral_constant<int, 4>(), std::false_type()); break;
-    case 8: go(std::integral_constant<int, 8>(), std::false_type()); break;
-    case 10: go(std::integral_constant<int, 10>(), std::false_type()); break;
-    case 12: go(std::integral_constant<int, 12>(), std::false_type()); break;
-    case 32: go(std::integral_constant<int, 32>(), std::false_type()); break;
-    default: go(std::integral_constant<int, 16>(), std::false_type()); break;
+    case 4: launch_up<R, 4, MR, false, 0>(f, c, b, ec, u, omega, s, rs, no); break;
+    case 8:
+      if constexpr (sizeof(R) == 8) {  // FP32: 16
+        launch_up<R, 8, MR, false, 0>(f, c, b, ec, u, omega, s, rs, no);
+        break;
+      }
+      [[fallthrough]];
+    default: launch_up<R, 16, MR, false, 0>(f, c, b, ec, u, omega, s, rs, no); break;
+    case 10: launch_up<R, 10, MR, false, 0>(f, c, b, ec, u, omega, s, rs, no); break;
+    case 12: launch_up<R, 12, MR, false, 0>(f, c, b, ec, u, omega, s, rs, no); break;
+    case 32: launch_up<R, 32, MR, false, 0>(f, c, b, ec, u, omega, s, rs, no); break;
+  }
+}
+
+template <typename R, bool MR, int TY>
+void launch_up_apply(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u,
+                     const UpApply<R> &ap, hipStream_t s, const RhsSet &rs) {
+  if (ap.mode == kBicgAlpha) {
+    launch_up<R, TY, MR, true, kBicgAlpha>(f, c, b, ec, u, R(1), s, rs, ap);
+  } else if (ap.mode == kBicgOmega) {
+    launch_up<R, TY, MR, true, kBicgOmega>(f, c, b, ec, u, R(1), s, rs, ap);
+  } else if constexpr (!MR) {  // Arnoldi steps have one right-hand side
+    launch_up<R, TY, MR, true, kUpApplyOnly>(f, c, b, ec, u, R(1), s, rs, ap);
   }
 }
 
@@ -837,6 +987,17 @@ void launch_up_rb(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, 
                   R omega, int rows, hipStream_t s, const RhsSet &rs) {
   if (multi_rhs(rs)) launch_up_mr<R, true>(fine, coarse, b, ec, u_out, omega, rows, s, rs);
   else launch_up_mr<R, false>(fine, coarse, b, ec, u_out, omega, rows, s, rs);
+}
+
+template <typename R>
+void launch_up_rb_apply(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec,
+                        cplx<R> *u_out, const UpApply<R> &ap, int rows, hipStream_t s, const RhsSet &rs) {
+  const bool mr = multi_rhs(rs);
+  constexpr int kTall = up_tall<R>();
+  if (mr && rows == 4) launch_up_apply<R, true, 4>(fine, coarse, b, ec, u_out, ap, s, rs);
+  else if (mr) launch_up_apply<R, true, kTall>(fine, coarse, b, ec, u_out, ap, s, rs);
+  else if (rows == 4) launch_up_apply<R, false, 4>(fine, coarse, b, ec, u_out, ap, s, rs);
+  else launch_up_apply<R, false, kTall>(fine, coarse, b, ec, u_out, ap, s, rs);
 }
 
 void launch_tail_wide(const TailArgs &a, hipStream_t s, const RhsSet &rs) {
@@ -850,6 +1011,12 @@ template void launch_down_rb<float>(const Grid<float> &, const Grid<float> &, co
                                     float, int, hipStream_t, const RhsSet &);
 template void launch_up_rb<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
                                    const cplx<double> *, cplx<double> *, double, int, hipStream_t, const RhsSet &);
+template void launch_up_rb_apply<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
+                                         const cplx<double> *, cplx<double> *, const UpApply<double> &, int,
+                                         hipStream_t, const RhsSet &);
+template void launch_up_rb_apply<float>(const Grid<float> &, const Grid<float> &, const cplx<float> *,
+                                        const cplx<float> *, cplx<float> *, const UpApply<float> &, int, hipStream_t,
+                                        const RhsSet &);
 template void launch_down_rb_src<float>(const Grid<float> &, const Grid<float> &, const DownSrc<float> &, cplx<float> *,
                                         float, int, hipStream_t, const RhsSet &);
 template void launch_down_rb_src<double>(const Grid<double> &, const Grid<double> &, const DownSrc<double> &,

@@ -323,6 +323,39 @@ def test_nested_updates_fused_equal_separate(case):
         S.set_tuning(fuse_updates=2)
 
 
+@pytest.mark.parametrize("n,coarsest", [(37, 10), (125, 32), (249, 32), (241, 16)])
+@pytest.mark.parametrize("method,inner,dt", [("bicgstab", 0, "f64"), ("gmres", 0, "f64"), ("fgmres", 2, "f32")])
+def test_operator_inside_the_cycle(method, inner, dt, n, coarsest):
+    """The matvec inside the finest up kernel (tile heights 4, 8 and 16) against the
+    separate matvec (height 10, which has no such form) over three steps: less
+    than a tile, one pair and more beyond one and two tiles (125 = 120 + 5, 249 =
+    240 + 9), one column and one row beyond (241), with the cycle eager and as a
+    graph.  The same expressions summed in another order: a few roundings of the
+    cycle's dtype, amplified by the three steps as they amplify one rounding of b
+    (FP64, measured here: 1e-11 where a step's dot product nearly cancels)."""
+    import torch
+    w = ragged_workload(n=n, coarsest=coarsest)
+    S = gpu_for(w, dt, krylov=E.Krylov(method=method, restart=8, rtol=1e-30, maxit=3, inner=inner))
+    b = to_gpu(w.rhs[0])
+    out = {}
+    for rows in (10, 4, 8, 16):
+        S.set_tuning(tail_nodes=9, pair_grid=0, small_grid=3, up_rows=rows)
+        for graphs in ("auto", True):
+            S.set_graphs(graphs)
+            x, st = S.solve(b)
+            assert st["iterations"] == 3, st
+            out[rows, graphs] = x.clone()
+    ref = to_np(out[10, "auto"])
+    tol = 1e-4
+    if dt == "f64":
+        S.set_tuning(up_rows=10)
+        noise = to_gpu(np.random.default_rng(n).choice([-2.0 ** -53, 2.0 ** -53], size=w.shape))
+        tol = 1e-14 + 8 * relerr(to_np(S.solve(b * (1 + 2 * noise))[0]), ref)
+    for rows in (4, 8, 16):
+        assert relerr(to_np(out[rows, "auto"]), ref) < tol, rows
+        assert torch.equal(out[rows, "auto"], out[rows, True]), rows
+
+
 @pytest.mark.parametrize("case", ["coulomb257", "ragged193"])
 def test_outer_bicgstab_updates_fused_equal_separate(case):
     """FP64 Bi-CGSTAB with the FP64 cycle: the p and s updates formed inside
