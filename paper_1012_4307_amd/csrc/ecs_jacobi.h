@@ -13,9 +13,9 @@ template <typename R>
 void launch_jacobi_down(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *x,
                         const cplx<R> *e, cplx<R> *out, cplx<R> *rc, R omega, hipStream_t s);
 
-// out = J(x + P e), out of place.
+// out = J(x + P e), out of place; with ap (kUpApplyOnly) y = A out as well.
 template <typename R>
 void launch_jacobi_up(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *x,
-                      const cplx<R> *e, cplx<R> *out, R omega, hipStream_t s);
+                      const cplx<R> *e, cplx<R> *out, R omega, hipStream_t s, const UpApply<R> *ap = nullptr);
 
 }  // namespace ecs

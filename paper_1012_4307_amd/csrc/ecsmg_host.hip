@@ -858,7 +858,8 @@ cplx<R> *jacobi_sweeps(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *cur, cplx<R
 
 bool fused_jacobi(const ecs_ctx *C);
 template <typename R>
-void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, int visits);
+void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, int visits,
+                   const UpApply<R> *ap = nullptr);
 
 // Algorithm 1: u <- MG(l, M_l, b, u, nu1, nu2, C, gf, gc).  zero_guess: u == 0
 // on entry (u's contents are not read and need not be cleared).  From level
@@ -935,7 +936,8 @@ bool fused_jacobi(const ecs_ctx *C) {
 // first with (gf, gc), the later ones with the two exchanged), the result in u.
 // Every kernel writes the iterate to the other of u and the level scratch.
 template <typename R>
-void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, int visits) {
+void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int gc, int visits,
+                   const UpApply<R> *ap) {
   DevLevel<R> &D = dev_level<R>(C, l), &Dc = dev_level<R>(C, l + 1);
   const Grid<R> g = grid_M<R>(C, l), gx = grid_M<R>(C, l + 1);
   const R om = (R)C->prec.omega;
@@ -957,9 +959,9 @@ void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int 
       jacobi_visits<R>(C, l + 1, Dc.b, Dc.u, pf, pc, pc);
     }
   }
-  // read x, b, k^2, the correction; write u
-  TimedScope ts(C, l == 0 ? kTUp : kTCoarse, (double)nn * sizeof(R) * 7.5);
-  launch_jacobi_up<R>(g, gx, b, x, Dc.u, u, om, C->stream);
+  // read x, b, k^2, the correction; write u (ap: and y)
+  TimedScope ts(C, l == 0 ? kTUp : kTCoarse, (double)nn * sizeof(R) * (ap ? 9.5 : 7.5));
+  launch_jacobi_up<R>(g, gx, b, x, Dc.u, u, om, C->stream, ap);
 }
 
 // V(1,1) red-black in 2D (the QD set-up of Sec. 4.2) runs on the fused
@@ -1322,6 +1324,11 @@ int general_dense_level(const ecs_ctx *C) {
 // (fuse_apply) A z as well, by a last kernel outside the cycle's graph
 template <typename R>
 void vcycle(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const UpApply<R> *ap = nullptr) {
+  if (ap && fused_jacobi(C)) {
+    C->gt_l = general_dense_level(C);
+    jacobi_visits<R>(C, 0, b0, u0, C->prec.gamma_f, C->prec.gamma_c, 1, ap);
+    return;
+  }
   if (ap) {
     if (vcycle_graph<R>(C, b0, u0, true)) finest_up<R>(C, b0, dev_level<R>(C, 1).u, u0, ap, one_rhs());
     else vcycle_fused<R>(C, b0, u0, nullptr, nullptr, one_rhs(), ap);
@@ -1362,6 +1369,18 @@ void precond<float>(ecs_ctx *C, const cplx<double> *v, cplx<float> *z, const UpA
 template <typename RZ>
 bool outer_fuse_apply(const ecs_ctx *C) {
   return sizeof(RZ) == 8 && !C->timers[kTApply].on && fuse_apply<double>(C, kRhsPartials);
+}
+
+// The same for an Arnoldi step on a fused omega-Jacobi cycle that is launched
+// eagerly (a captured cycle is one graph, and the matvec's launch is then a small
+// part of it).
+template <typename RZ>
+bool jacobi_fuse_apply(ecs_ctx *C) {
+  if (sizeof(RZ) != 8 || C->timers[kTApply].on || C->prec.kind == ECS_PREC_NONE || C->nlev == 1 || !fused_jacobi(C) ||
+      C->graph_mode == ECS_GRAPHS_ALWAYS)
+    return false;
+  C->gt_l = general_dense_level(C);
+  return C->gt_l > 0 && cycle_launches(C, 0, C->prec.gamma_f, C->prec.gamma_c, 4096) <= kEagerLaunches;
 }
 
 // ----------------------------------------------------------- Krylov
@@ -1596,7 +1615,7 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       cplx<double> *vj = K.V + (int64_t)j * ld, *w = vj + ld;
       cplx<RZ> *zj = flexible ? Z + (int64_t)j * ld : tz;
       if (d->inner > 0) inner_bicgstab<RZ>(C, K, vj, zj, d->inner);
-      else if (outer_fuse_apply<RZ>(C)) {
+      else if (outer_fuse_apply<RZ>(C) || jacobi_fuse_apply<RZ>(C)) {
         const UpApply<double> aw = up_apply<double>(grid_A(C), kUpApplyOnly, nullptr, w, nullptr);
         return precond<RZ>(C, vj, zj, &aw);
       } else precond<RZ>(C, vj, zj);

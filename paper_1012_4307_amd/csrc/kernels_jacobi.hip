@@ -152,18 +152,22 @@ __global__ __launch_bounds__(256) void k_jac_down(Grid<R> f, Grid<R> c, const cp
 }
 
 // out = J(x + P e): the correction and the first post-sweep.  62 x TY owned nodes,
-// staged with a ring of one.
-template <typename R, int TY>
+// staged with a ring of one.  AP: also A.y = A out (UpApply, no dot product), which
+// needs out on a ring of one and the staging on a ring of two: 60 x TY owned nodes.
+// 65^2 FP64, where a step of GMRES is a chain of small launches: 3.8 us here and
+// 4.5 of the matvec -> 4.4 in one, a solve of 66 steps 2.93 -> 2.55 ms.
+template <typename R, int TY, bool AP>
 __global__ __launch_bounds__(256) void k_jac_up(Grid<R> f, Grid<R> c, const cplx<R> *__restrict__ b,
                                                 const cplx<R> *__restrict__ x, const cplx<R> *__restrict__ e,
-                                                cplx<R> *__restrict__ out, R omega, int tiles_x, int tiles) {
-  constexpr int TX = 62, WY = TY + 2, RPW = (WY + 3) / 4;
-  __shared__ cplx<R> s0[WY][64];
+                                                cplx<R> *__restrict__ out, R omega, int tiles_x, int tiles,
+                                                UpApply<R> A) {
+  constexpr int H = AP ? 2 : 1, TX = 64 - 2 * H, WY = TY + 2 * H, RPW = (WY + 3) / 4;
+  __shared__ cplx<R> s0[WY][64], s1[AP ? WY : 1][64];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile = xcd_tile(tiles);
   if (tile < 0) return;
   const int x0 = (tile % tiles_x) * TX, y0 = (tile / tiles_x) * TY;
-  const int n0 = f.n0, n1 = f.n1, i = x0 - 1 + lane, gy0 = y0 - 1;
+  const int n0 = f.n0, n1 = f.n1, i = x0 - H + lane, gy0 = y0 - H;
   const R om1 = R(1) - omega;
   const bool xin = i >= 1 && i <= n0 - 2;
   const cplx<R> xm = xin ? f.cm0[i] : zj<R>(), xp = xin ? f.cp0[i] : zj<R>();
@@ -204,11 +208,13 @@ __global__ __launch_bounds__(256) void k_jac_up(Grid<R> f, Grid<R> c, const cplx
   }
   __syncthreads();
   const __amdgpu_buffer_rsrc_t ro = rows_rsrc(out, y0, min(y0 + TY, n1), n0);
-  const uint32_t oo = col_off<cplx<R>>(lane >= 1 && lane <= TX && i < n0, i);
+  const uint32_t oo = col_off<cplx<R>>(lane >= H && lane < TX + H && i < n0, i);
+  // A's weights, in flight during the sweep
+  const cplx<R> am = AP && xin ? A.cm0[i] : zj<R>(), ap = AP && xin ? A.cp0[i] : zj<R>();
 #pragma unroll
   for (int r = 0; r < RPW; r++) {
     const int ly = wv + 4 * r, j = gy0 + ly;
-    if (ly >= 1 && ly <= TY && j < n1) {
+    if (ly >= 1 && ly <= WY - 2 && j < n1) {
       cplx<R> v = zj<R>();
       if (xin && j >= 1 && j <= n1 - 2) {
         const cplx<R> d = xm + xp + ym[r] + yp[r] + (K[r] * f.beta + f.c);
@@ -216,7 +222,30 @@ __global__ __launch_bounds__(256) void k_jac_up(Grid<R> f, Grid<R> c, const cplx
             xm * s0[ly][lm] + xp * s0[ly][lp] + ym[r] * s0[ly - 1][lane] + yp[r] * s0[ly + 1][lane];
         v = om1 * X[r] + omega * cdiv(B[r] + o, d);
       }
-      st_c(ro, oo + row_off<cplx<R>>(j - y0, n0), v);
+      if constexpr (AP) {
+        X[r] = v;
+        s1[ly][lane] = v;
+      }
+      if (ly >= H && ly < TY + H) st_c(ro, oo + row_off<cplx<R>>(j - y0, n0), v);
+    }
+  }
+  if constexpr (AP) {
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t ry = rows_rsrc(A.y, y0, min(y0 + TY, n1), n0);
+#pragma unroll
+    for (int r = 0; r < RPW; r++) {
+      const int ly = wv + 4 * r, j = gy0 + ly;
+      if (ly >= H && ly < TY + H && j < n1) {
+        cplx<R> v = zj<R>();
+        if (xin && j >= 1 && j <= n1 - 2) {
+          const cplx<R> aym = A.cm1[j], ayp = A.cp1[j];
+          const cplx<R> d = am + ap + aym + ayp + (K[r] * A.beta + A.c);
+          cplx<R> o = am * s1[ly][lm] + ap * s1[ly][lp];
+          o = o + aym * s1[ly - 1][lane] + ayp * s1[ly + 1][lane];
+          v = d * X[r] - o;
+        }
+        st_c(ry, oo + row_off<cplx<R>>(j - y0, n0), v);
+      }
     }
   }
 }
@@ -249,22 +278,30 @@ void launch_jacobi_down(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, co
 
 template <typename R>
 void launch_jacobi_up(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *x, const cplx<R> *e,
-                      cplx<R> *out, R omega, hipStream_t s) {
-  const int tx = (f.n0 + 61) / 62;
-  const auto go = [&](auto rows) {
+                      cplx<R> *out, R omega, hipStream_t s, const UpApply<R> *ap) {
+  const auto go = [&](auto rows, auto with) {
     constexpr int TY = decltype(rows)::value;
-    const int tiles = tx * ((f.n1 + TY - 1) / TY);
-    launch_k((k_jac_up<R, TY>), dim3(xcd_padded(tiles)), dim3(256), 0, s, f, c, b, x, e, out, omega, tx, tiles);
+    constexpr bool AP = decltype(with)::value;
+    constexpr int TX = AP ? 60 : 62;
+    const int tx = (f.n0 + TX - 1) / TX, tiles = tx * ((f.n1 + TY - 1) / TY);
+    launch_k((k_jac_up<R, TY, AP>), dim3(xcd_padded(tiles)), dim3(256), 0, s, f, c, b, x, e, out, omega, tx, tiles,
+             AP ? *ap : UpApply<R>{});
   };
-  // six rows a block while the level then is a few blocks per CU, 14 above
-  if (f.n1 <= 513) go(std::integral_constant<int, 6>());
-  else go(std::integral_constant<int, 14>());
+  // six rows a block while the level then is a few blocks per CU, 14 above (with
+  // A two fewer: two and four row slots of a wave as well)
+  const bool low = f.n1 <= 513;
+  if (ap && low) go(std::integral_constant<int, 4>(), std::true_type());
+  else if (ap) go(std::integral_constant<int, 12>(), std::true_type());
+  else if (low) go(std::integral_constant<int, 6>(), std::false_type());
+  else go(std::integral_constant<int, 14>(), std::false_type());
 }
 
 template void launch_jacobi_up<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
-                                       const cplx<double> *, const cplx<double> *, cplx<double> *, double, hipStream_t);
+                                       const cplx<double> *, const cplx<double> *, cplx<double> *, double, hipStream_t,
+                                       const UpApply<double> *);
 template void launch_jacobi_up<float>(const Grid<float> &, const Grid<float> &, const cplx<float> *,
-                                      const cplx<float> *, const cplx<float> *, cplx<float> *, float, hipStream_t);
+                                      const cplx<float> *, const cplx<float> *, cplx<float> *, float, hipStream_t,
+                                      const UpApply<float> *);
 template void launch_jacobi_down<double>(const Grid<double> &, const Grid<double> &, const cplx<double> *,
                                          const cplx<double> *, const cplx<double> *, cplx<double> *, cplx<double> *,
                                          double, hipStream_t);

@@ -356,6 +356,23 @@ def test_operator_inside_the_cycle(method, inner, dt, n, coarsest):
         assert torch.equal(out[rows, "auto"], out[rows, True]), rows
 
 
+@pytest.mark.parametrize("n,coarsest", [(57, 29), (61, 31), (121, 31), (545, 35)])
+def test_operator_inside_the_jacobi_cycle(n, coarsest):
+    """GMRES on an omega-Jacobi V cycle: the matvec inside the last kernel of the
+    eager cycle against the separate one (while it is timed), three steps, less
+    than a tile, one column and row beyond one and two (61 = 60 + 1, 121), tall tiles
+    (545).  The same expressions: a few roundings."""
+    w = ragged_workload(n=n, coarsest=coarsest, kind="csl", smoother="jacobi", omega=0.8)
+    S = gpu_for(w, "f64", krylov=E.Krylov(method="gmres", restart=8, rtol=1e-30, maxit=3))
+    b = to_gpu(w.rhs[0])
+    x, st = S.solve(b)
+    assert st["iterations"] == 3, st
+    S.timing("apply_A", True)
+    y, _ = S.solve(b)
+    assert S.timing_read("apply_A")[0] == 3 + 2  # and the residuals of the start and the end
+    assert relerr(to_np(x), to_np(y)) < 1e-12
+
+
 @pytest.mark.parametrize("case", ["coulomb257", "ragged193"])
 def test_outer_bicgstab_updates_fused_equal_separate(case):
     """FP64 Bi-CGSTAB with the FP64 cycle: the p and s updates formed inside
