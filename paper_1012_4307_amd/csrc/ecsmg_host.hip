@@ -1080,6 +1080,8 @@ CycleBufs<R> hierarchy_bufs(ecs_ctx *C) {
 // ones the kernel takes about what the two took (seven right-hand sides of 1025^2,
 // FP64: 133 us and a reduction, against 71 + 66 with the reduction folded into the
 // next kernel; three sizes batched 170.6 -> 168.7 ms; 2049^2 nested 794 -> 771 ms).
+// In FP64 it loses at 2049^2 (84 and 77 us against 39 + 40 and 39 + 38), beyond the
+// cap of kRhsPartials entries that FP64 callers pass.
 template <typename R>
 bool fuse_apply(const ecs_ctx *C, int64_t cap) {
   if (C->prec.kind == ECS_PREC_NONE || !fused_vcycle(C) || C->prec.omega != 1.0) return false;
@@ -1108,8 +1110,8 @@ template <typename R>
 void finest_up(ecs_ctx *C, const cplx<R> *b0, const cplx<R> *ec, cplx<R> *u0, const UpApply<R> *ap, const RhsSet &rs) {
   const double by = (double)rs.count * C->hl[0].nn * sizeof(R);
   if (ap) {
-    // as below, and d0 (with a dot product) and y
-    TimedScope ts(C, kTUp, by * (ap->mode == kUpApplyOnly ? 7.5 : 9.5));
+    // as below, and r^ (kBicgAlpha; d0 of the other dot products is b) and y
+    TimedScope ts(C, kTUp, by * (ap->mode == kBicgAlpha ? 9.5 : 7.5));
     launch_up_rb_apply<R>(grid_M<R>(C, 0), grid_M<R>(C, 1), b0, ec, u0, *ap, up_rows<R>(C, 0), C->stream, rs);
     return;
   }
@@ -1448,7 +1450,7 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
   // fused (FP32): the finest down kernel forms p (into the other p buffer:
   // blocks read the old p around their tiles) and s; the same values either way
   const bool fuse = sizeof(R) == 4 && fused_updates(C);
-  const bool fa = fuse_apply<R>(C, kRedBlocks * (kMaxRestart + 2));
+  const bool fa = fuse_apply<R>(C, sizeof(R) == 4 ? kRedBlocks * (kMaxRestart + 2) : kRhsPartials);
   const UpApply<R> av = up_apply<R>(gA, kBicgAlpha, frh, fv, C->partials);
   const UpApply<R> at = up_apply<R>(gA, kBicgOmega, fs, ft, C->partials);
   cplx<R> *p_old = reinterpret_cast<cplx<R> *>(K.fp), *p_new = reinterpret_cast<cplx<R> *>(K.fp2);

@@ -37,18 +37,23 @@ TAIL_MARKER = b"\n// -----------------------------------------------------------
 COPY_BYTES = 512 << 20   # the copy probe moves 512 MiB each way
 # class (as bench.py's timing classes) and kernel name pattern; the finest
 # grid of each is the one recorded
-# (the single right-hand side instantiations: a trailing ", false" where the
-# kernel also has a multi-right-hand-side form)
-CLASSES = (("up", r"k_up_rb<float, \d+(, false(, \w+)*)?>"), ("down_p", r"k_down_rb<float, \d+, 1(, false(, \w+)*)?>"),
-           ("down_s", r"k_down_rb<float, \d+, 2(, false(, \w+)*)?>"), ("down_f64", r"k_down_rb<double, \d+, 0(, false(, \w+)*)?>"),
-           ("up_f64", r"k_up_rb<double, \d+(, false(, \w+)*)?>"))
+# (the single right-hand side instantiations: ", false" where the kernel also
+# has a multi-right-hand-side form, then the omega = 1 form and, for the up
+# kernel, the operator it applies: 0 none, 1 and 2 with the dot products of
+# Bi-CGSTAB's two halves, the form the nested solve runs)
+CLASSES = (("up", r"k_up_rb<float, \d+(, false(, \w+, [12])?)?>"),
+           ("down_p", r"k_down_rb<float, \d+, 1(, false(, \w+)*)?>"),
+           ("down_s", r"k_down_rb<float, \d+, 2(, false(, \w+)*)?>"),
+           ("down_f64", r"k_down_rb<double, \d+, 0(, false(, \w+)*)?>"),
+           ("up_f64", r"k_up_rb<double, \d+(, false(, \w+, 0)?)?>"))
 # algorithmic bytes per fine node: every input read once, every output written
-# once.  FP32 complex 8 B, real 4 B: up reads the coarse correction (a quarter
-# node), b, k^2 and writes u (5.5 reals = 22 B); the p-forming down kernel
+# once.  FP32 complex 8 B, real 4 B: up (first half) reads the coarse correction
+# (a quarter node), b, k^2, r^ and writes u and A u (9.5 reals = 38 B); the
+# p-forming down kernel
 # reads r, p, v, k^2 and writes p and the coarse residual (9.5 reals = 38 B);
 # the s-forming one reads r, v, k^2 and writes s and the coarse residual
 # (7.5 reals = 30 B).  FP64: down 3.5 reals = 28 B, up 5.5 reals = 44 B.
-ALGO_BYTES_PER_NODE = dict(up=22, down_p=38, down_s=30, down_f64=28, up_f64=44)
+ALGO_BYTES_PER_NODE = dict(up=38, down_p=38, down_s=30, down_f64=28, up_f64=44)
 
 
 def sources_digest() -> str:
@@ -123,7 +128,7 @@ def _counter(path: str, counter: str):
 
 
 def _finest(d, pattern: str):
-    keys = [k for k in d if re.fullmatch(pattern, k[0])]
+    keys = sorted(k for k in d if re.fullmatch(pattern, k[0]))  # of equal grids the first name
     if not keys:
         raise SystemExit(f"no dispatch of {pattern}")
     k = max(keys, key=lambda k: k[1])
