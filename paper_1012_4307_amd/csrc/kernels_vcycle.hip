@@ -883,13 +883,13 @@ void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b
     launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD, true>), grid, block, 0, s, fine, coarse, b, src, rc,
              omega, tx, tiles, rs);
   };
-  // the heights that the schedule takes by default have the omega = 1 form
+  // the heights that the schedule takes by default (and 8 in FP64, which the tuner
+  // picks) have the omega = 1 form
   if (omega == R(1) && rows == 2) return go_gs(std::integral_constant<int, 2>());
   if constexpr (sizeof(R) == 8) {
     if (omega == R(1) && rows == 4) return go_gs(std::integral_constant<int, 4>());
-  } else {
-    if (omega == R(1) && rows == 8) return go_gs(std::integral_constant<int, 8>());
   }
+  if (omega == R(1) && rows == 8) return go_gs(std::integral_constant<int, 8>());
   switch (rows) {
     case 2: go(std::integral_constant<int, 2>()); break;
     case 3: go(std::integral_constant<int, 3>()); break;
@@ -944,8 +944,8 @@ void launch_up(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, con
                R omega, hipStream_t s, const RhsSet &rs, const UpApply<R> &ap) {
   const int tx = (fine.n0 + 119) / 120;
   const int tiles = tx * ((fine.n1 + TY - 1) / TY);
-  launch_k((k_up_rb<R, TY, MR, GS, MODE>), dim3(up_rb_blocks(fine.n0, fine.n1, TY), rs.count), dim3(64 * up_waves(TY)), 0, s, fine,
-           coarse, b, ec, u_out, omega, tx, tiles, rs, ap);
+  const dim3 grid(up_rb_blocks(fine.n0, fine.n1, TY), rs.count), block(64 * up_waves(TY));
+  launch_k((k_up_rb<R, TY, MR, GS, MODE>), grid, block, 0, s, fine, coarse, b, ec, u_out, omega, tx, tiles, rs, ap);
 }
 
 template <typename R, bool MR>
