@@ -40,6 +40,12 @@ struct BicgScalars {
   int breakdowns;  // restarts (kBicgInit) that found the previous run ended by a bad scalar
 };
 
+// What a Krylov driver's host side reads after each step (pinned host memory).
+struct StepReport {
+  double est;
+  int bad, happy;
+};
+
 enum { kBicgAlpha = 1, kBicgOmega = 2, kBicgInit = 4, kBicgNormRho = 5 };
 
 // Scalars handed to a kernel that follows a dot product of the step.  nb = 0:
@@ -98,8 +104,9 @@ void launch_scale_dev(cplx<double> *x, int64_t n, const double *scal, hipStream_
 void launch_gmres_start(GmresScalars *S, int m, hipStream_t s);
 // The end of Arnoldi step j: ||w||^2 (from nb partials of launch_dcgs2, or with
 // nb = 0 from S->nrm2), the Givens step, w scaled to norm 1.
+// host: also reported there.
 void launch_gmres_end(GmresScalars *S, int j, int m, const cplx<double> *partials, int nb, cplx<double> *w, int64_t n,
-                      hipStream_t s);
+                      hipStream_t s, StepReport *host = nullptr);
 void launch_gmres_backsolve(GmresScalars *S, int k, int m, hipStream_t s);
 void launch_add_h2(GmresScalars *S, int j, int m, hipStream_t s, const int *gate = nullptr);
 
@@ -121,7 +128,8 @@ void launch_bicg_s(cplx<R> *sv, const cplx<R> *r, const cplx<R> *v, int64_t n, c
 template <typename R, typename RZ>
 void launch_bicg_xr(cplx<R> *x, const cplx<RZ> *ph, const cplx<RZ> *sh, cplx<R> *r, const cplx<R> *sv,
                     const cplx<R> *t, const cplx<R> *rh, int64_t n, cplx<double> *partials, const BicgFold &f,
-                    BicgScalars *S2, BicgScalars *S, hipStream_t s, const RhsSet &rs = one_rhs());
+                    BicgScalars *S2, BicgScalars *S, hipStream_t s, const RhsSet &rs = one_rhs(),
+                    StepReport *host = nullptr);
 // The nested Bi-CGSTAB with its x update deferred: r = s - omega t, the
 // same reductions as launch_bicg_xr (left to the next kernel when there are few
 // partials: the result is its BicgFold), and (alpha, omega) of the step stored at
@@ -139,7 +147,7 @@ void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_
 // kBicgOmega -> (y, d0) and (y, y) give omega (multigrid side, kernels_mg.hip)
 // The one-block reduction and update of the recurrence, from *in to *out.
 void launch_bicg_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in, BicgScalars *out,
-                       int mode, hipStream_t s, const RhsSet &rs = one_rhs());
+                       int mode, hipStream_t s, const RhsSet &rs = one_rhs(), StepReport *host = nullptr);
 // few partials: left to the next kernel (the BicgFold returned), else reduced to *out
 inline BicgFold bicg_fold_or_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in,
                                    BicgScalars *out, int mode, hipStream_t s, const RhsSet &rs = one_rhs()) {

@@ -160,6 +160,7 @@ struct ecs_ctx {
   GmresScalars *gs = nullptr;
   BicgScalars *bs = nullptr, *bs_in = nullptr;
   double *pinned = nullptr;  // host-pinned scalars for readback
+  StepReport *report = nullptr;  // pinned, as the device sees it: a step's end, written by its last kernel
   hipEvent_t step_ev = nullptr;  // completion of the last step's readback on this context
 
   Timer timers[kTClasses];
@@ -1412,13 +1413,15 @@ bool run_ahead(const ecs_ctx *C) {
   return nn_of(C) <= kAheadMaxNodes;
 }
 
-// `bytes` (<= 64) from device memory into the pinned buffer, and the event that
-// marks its arrival; take_readback waits for that event only
-bool enqueue_readback(ecs_ctx *C, const void *dev, size_t bytes) {
-  return hipMemcpyAsync(C->pinned, dev, bytes, hipMemcpyDeviceToHost, C->stream) == hipSuccess &&
-         hipEventRecord(C->step_ev, C->stream) == hipSuccess;
+// The event behind the kernel that reports a step's end (StepReport, at the start
+// of the pinned buffer); wait_readback waits for that event only, and only then
+// is the next report enqueued.
+bool mark_report(ecs_ctx *C) { return hipEventRecord(C->step_ev, C->stream) == hipSuccess; }
+bool wait_readback(ecs_ctx *C, StepReport *r) {
+  if (hipEventSynchronize(C->step_ev) != hipSuccess) return false;
+  std::memcpy(r, C->pinned, sizeof *r);
+  return true;
 }
-bool wait_readback(ecs_ctx *C) { return hipEventSynchronize(C->step_ev) == hipSuccess; }
 
 template <typename R>
 Grid<R> grid_A_of(const ecs_ctx *C);
@@ -1632,19 +1635,17 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       st->inner_iterations += d->inner;
       const int nb = orthogonalise(C, K.V, ld, j, w, n, C->partials, S, m, d->orth, s);
       later_steps += j > 0;
-      launch_gmres_end(S, j, m, C->partials, nb, w, n, s);
+      launch_gmres_end(S, j, m, C->partials, nb, w, n, s, C->report);
       it++;
       k = j + 1;
-      // est, resid_true, bad, happy are contiguous: one readback per iteration
-      if (!enqueue_readback(C, &S->est, 2 * sizeof(double) + 2 * sizeof(int))) { bad = true; break; }
+      if (!mark_report(C)) { bad = true; break; }
       // a nested run is far longer than the wait
       opened = d->inner == 0 && j + 1 < m && it < d->maxit && run_ahead(C);
       if (opened) open_step(j + 1);
-      if (!wait_readback(C)) { bad = true; break; }
-      double est;
-      int happy;
-      std::memcpy(&est, C->pinned, sizeof(double));
-      std::memcpy(&happy, reinterpret_cast<char *>(C->pinned) + 2 * sizeof(double) + sizeof(int), sizeof(int));
+      StepReport end;
+      if (!wait_readback(C, &end)) { bad = true; break; }
+      const double est = end.est;
+      const int happy = end.happy;
       if (d->history && it - 1 < d->history_len) d->history[it - 1] = est;
       if (!(est == est) || std::isinf(est)) { bad = true; break; }
       if (est <= d->rtol || happy) break;
@@ -1767,7 +1768,7 @@ void bicg_close_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x, const Bic
     TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
     omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s);
   }
-  launch_bicg_xr<double, RZ>(x, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s);
+  launch_bicg_xr<double, RZ>(x, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s, one_rhs(), C->report);
 }
 
 template <typename RZ>
@@ -1811,16 +1812,15 @@ ecs_status bicgstab(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, co
     while (it < d->maxit) {
       if (!opened) alpha = bicg_open_step<RZ>(C, K);
       bicg_close_step<RZ>(C, K, x, alpha);
-      if (!enqueue_readback(C, &S->est, sizeof(double) + sizeof(int))) break;  // est, bad
+      if (!mark_report(C)) break;
       st->vcycles += 2;
       it++;
       opened = it < d->maxit && run_ahead(C);
       if (opened) alpha = bicg_open_step<RZ>(C, K);
-      if (!wait_readback(C)) break;
-      double est;
-      int bad;
-      std::memcpy(&est, C->pinned, sizeof(double));
-      std::memcpy(&bad, reinterpret_cast<const char *>(C->pinned) + sizeof(double), sizeof(int));
+      StepReport end;
+      if (!wait_readback(C, &end)) break;
+      const double est = end.est;
+      const int bad = end.bad;
       if (d->history && it - 1 < d->history_len) d->history[it - 1] = est;
       if (bad) break;  // restart from the current iterate
       if (est <= d->rtol) break;
@@ -2397,6 +2397,11 @@ ecs_status ecs_create(ecs_ctx **out, int dim, const int64_t *nodes, const double
   C->stream = reinterpret_cast<hipStream_t>(stream);
   if (hipGetDevice(&C->device) != hipSuccess ||
       hipHostMalloc((void **)&C->pinned, kPinnedBytes, hipHostMallocDefault) != hipSuccess) {
+    delete C;
+    return ECS_EDEVICE;
+  }
+  if (hipHostGetDevicePointer((void **)&C->report, C->pinned, 0) != hipSuccess) {
+    (void)hipHostFree(C->pinned);
     delete C;
     return ECS_EDEVICE;
   }
