@@ -330,7 +330,8 @@ ecs_status ecs_timing_calibrate(ecs_ctx *ctx, int launches);
  * solve's outer iteration count by a few percent):
  *   down_rows   coarse rows per block of the fused pre-smoothing/restriction
  *               kernel on grids above small_grid: 2 to 6, 8 (16 in FP32, where
- *               4 runs as 8)
+ *               4 runs as 8; a 16 set for an FP32 cycle runs as 8 when the
+ *               cycle's type becomes FP64)
  *   up_rows     fine rows per block of the fused prolongation/post-smoothing
  *               kernel on grids above small_grid: 4, 8, 10, 12, 16 or 32 (in
  *               FP32 8 runs as 16)

@@ -1046,7 +1046,9 @@ bool small_level(const ecs_ctx *C, int l) {
 template <typename R>
 int down_rows(const ecs_ctx *C, int l) {
   if (small_level(C, l)) return 2;
-  return sizeof(R) == 4 && C->tune.down_rows == 4 ? 8 : C->tune.down_rows;
+  const int rows = C->tune.down_rows;
+  if (sizeof(R) == 4) return rows == 4 ? 8 : rows;
+  return rows == 16 ? 8 : rows;  // a schedule set for FP32 cycles stays when the cycle's type changes
 }
 template <typename R>
 int up_rows(const ecs_ctx *C, int l) {

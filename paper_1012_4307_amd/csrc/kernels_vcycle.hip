@@ -871,18 +871,18 @@ __global__ __launch_bounds__(TT) void k_tail_wide(TailArgs a, RhsSet rs) {
 template <typename R, int SRC, bool MR, bool FOLD>
 void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const DownSrc<R> &src, cplx<R> *rc,
                     R omega, int rows, hipStream_t s, const RhsSet &rs) {
-  constexpr int CX = 61;
-  const int tx = (coarse.n0 + CX - 1) / CX;
-  const int tiles = tx * ((coarse.n1 + rows - 1) / rows);
-  const dim3 grid(xcd_padded(tiles), rs.count), block(64 * down_waves(rows));
-  const auto go = [&](auto cy) {
-    launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD, false>), grid, block, 0, s, fine, coarse, b, src, rc,
+  // the grid follows the height of the kernel, which a height that a type does not
+  // have (16 in FP64, 4 in FP32) does not name
+  const auto launch = [&](auto cy, auto gs) {
+    constexpr int CX = 61, CY = decltype(cy)::value;
+    const int tx = (coarse.n0 + CX - 1) / CX;
+    const int tiles = tx * ((coarse.n1 + CY - 1) / CY);
+    const dim3 grid(xcd_padded(tiles), rs.count), block(64 * down_waves(CY));
+    launch_k((k_down_rb<R, CY, SRC, MR, FOLD, decltype(gs)::value>), grid, block, 0, s, fine, coarse, b, src, rc,
              omega, tx, tiles, rs);
   };
-  const auto go_gs = [&](auto cy) {
-    launch_k((k_down_rb<R, decltype(cy)::value, SRC, MR, FOLD, true>), grid, block, 0, s, fine, coarse, b, src, rc,
-             omega, tx, tiles, rs);
-  };
+  const auto go = [&](auto cy) { launch(cy, std::false_type()); };
+  const auto go_gs = [&](auto cy) { launch(cy, std::true_type()); };
   // the heights that the schedule takes by default (and 8 in FP64, which the tuner
   // picks) have the omega = 1 form
   if (omega == R(1) && rows == 2) return go_gs(std::integral_constant<int, 2>());

@@ -189,6 +189,35 @@ def test_vcycle_tile_heights(dt):
             assert relerr(to_np(S.vcycle(to_gpu(v))), ref) < CYCLE_TOL[dt], (d, u)
 
 
+@pytest.mark.parametrize("omega", [1.0, 0.85])
+def test_tile_height_kept_over_a_change_of_type(omega):
+    """A schedule with 16 coarse rows a block, which FP32 cycles have, stays set when
+    the context's cycle becomes an FP64 one: the cycle is the oracle's on every
+    node (fine levels of 193 and 97 coarse rows, no multiples of 8 or 16)."""
+    import ctypes
+    import torch
+    import paper_1012_4307_amd as E
+    w = ragged_workload(n=385, coarsest=7, omega=omega)
+    P = oracle_for(w)
+    v = W.random_complex(w.shape, np.random.default_rng(23))
+    S = gpu_for(w, "f32")
+    S.set_tuning(down_rows=16, small_grid=3, pair_grid=0)
+    assert relerr(to_np(S.vcycle(to_gpu(v))), P.mg_apply(v)) < CYCLE_TOL["f32"]
+    L, d = E.lib(), S.precond.to_c()
+    d.vcycle_dtype = E.F64
+    assert L.ecs_set_precond(S._h, ctypes.byref(d)) == 0
+    n = ctypes.c_size_t()
+    assert L.ecs_workspace_size(S._h, None, ctypes.byref(n)) == 0
+    ws = torch.empty(n.value + 256, dtype=torch.uint8, device="cuda")
+    assert L.ecs_set_workspace(S._h, ctypes.c_void_p((ws.data_ptr() + 255) & ~255), n.value) == 0
+    got = to_np(S.vcycle(to_gpu(v)))
+    assert relerr(got, P.mg_apply(v)) < CYCLE_TOL["f64"]
+    # no part of the result comes from what the buffers held
+    for other in (1.0, -3.0):
+        S.vcycle(to_gpu(other * W.random_complex(w.shape, np.random.default_rng(5))))
+        assert np.array_equal(to_np(S.vcycle(to_gpu(v))), got)
+
+
 @pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("omega", [1.0, 0.85])
 @pytest.mark.parametrize("n,coarsest", [(37, 10), (125, 32), (193, 7)])
