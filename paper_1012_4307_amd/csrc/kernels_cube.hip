@@ -21,11 +21,12 @@
 //
 // What bounds it: the issue and latency of a step (one barrier, an LDS round
 // trip, 160-220 vector instructions of a thread at 2-3 waves per SIMD: 0.8-1.3
-// us), not HBM.  Finest level of a 129^3 cycle, FP64: down 22 us (56 MB, 2.5
-// TB/s), up 32 us (94 MB, 2.9 TB/s).  The separate kernels
+// us), not HBM.  Finest level of a 129^3 cycle, FP64: down 20 us (56 MB, 2.8
+// TB/s), up 34 us (94 MB, 2.8 TB/s); FP32 17 and 26 us.  The separate kernels
 // of the general cycle make seven passes over a level, and their residual +
 // full weighting forms every fine residual 3.4 times (27 per coarse node): the
-// whole cycle took 390 us FP64, 300 us FP32, now 148 and 119 us.
+// whole cycle took 390 us FP64, 300 us FP32, now 112 and 96 us (148 and 119 before
+// its coarse end was a dense map).
 #include "ecs_cube.h"
 
 namespace ecs {
@@ -59,27 +60,46 @@ __device__ __forceinline__ cplx<R> fma_c(cplx<R> w, cplx<R> u, cplx<R> acc) {
 // value and has no residual, so a down step writes and weights the red residuals
 // alone (five reads in even planes, four in odd ones, of nine) and an up step
 // corrects the black nodes alone.  129^3 FP64 down 24.0 -> 22.1 us, up 34.3 ->
-// 32.1; 97^3 FP32 14.3 -> 13.8 and 18.9 -> 17.8.
+// 32.1; 97^3 FP32, still with an FP32 diagonal (diag3), 14.3 -> 13.8 and 18.9 ->
+// 17.8.
 template <bool GS, typename R>
 __device__ __forceinline__ cplx<R> relaxed(R omega, cplx<R> v) {
   if constexpr (GS) return v;
   else return omega * v;
 }
-// 1 / d.  FP64: the hardware estimate of 1 / |d|^2 and two Newton steps
-// y <- y + y (1 - a y), which doubles the correct bits each time; a third of
-// the instructions of the correctly rounded division.
+// 1 / d in FP64: the hardware estimate of 1 / |d|^2 and Newton steps y <- y +
+// y (1 - a y) in fused arithmetic, each of which doubles the correct bits: one is
+// enough for an FP32 result; after two the reciprocal is the correctly rounded
+// one (no difference from the division over 2^27 random arguments), at a third of
+// its instructions.
 template <typename R>
-__device__ __forceinline__ cplx<R> inv_d(cplx<R> d) {
-  const R a = abs2(d);
-  R s;
-  if constexpr (sizeof(R) == 8) {
-    s = __builtin_amdgcn_rcp(a);
-    s = fma(s, fma(-a, s, R(1)), s);
-    s = fma(s, fma(-a, s, R(1)), s);
-  } else {
-    s = R(1) / a;
+__device__ __forceinline__ cplx<double> inv_d(cplx<double> d) {
+  const double a = abs2(d);
+  double s = __builtin_amdgcn_rcp(a);
+  s = fma(s, fma(-a, s, 1.0), s);
+  if constexpr (sizeof(R) == 8) s = fma(s, fma(-a, s, 1.0), s);
+  return mk<double>(d.re * s, -d.im * s);
+}
+
+// What rounding 1 / D to FP32 leaves off, which the post-relaxation adds back: that
+// error is the same at all nodes where D is (see diag3).  Nothing in FP64.
+template <typename R>
+struct Rest {
+  cplx<R> v;
+  __device__ __forceinline__ void set(cplx<double> inv) {
+    if constexpr (sizeof(R) == 4) v = cvt<R>(inv - cvt<double>(cvt<R>(inv)));
   }
-  return mk<R>(d.re * s, -d.im * s);
+};
+// acc + t / D
+template <typename R>
+__device__ __forceinline__ cplx<R> add_over(cplx<R> t, cplx<R> inv, const Rest<R> &rest, cplx<R> acc) {
+  if constexpr (sizeof(R) == 4) acc = fma_c(rest.v, t, acc);
+  return fma_c(t, inv, acc);
+}
+template <typename R>
+__device__ __forceinline__ cplx<R> over(cplx<R> t, cplx<R> inv, const Rest<R> &rest) {
+  if constexpr (sizeof(R) == 4) return fma_c(t, inv, rest.v * t);
+  else return t * inv;
 }
 
 // one x-y plane of a level as a buffer resource (empty outside [0, n2))
@@ -101,7 +121,7 @@ struct Cols {
   int side[2];             // thread offset (+-1) of the column's x neighbour in the next pair
   cplx<R> wo[2], wn[2];    // x weights of the neighbour in the own pair / in the next pair
   cplx<R> ym[2], yp[2];    // y weights
-  cplx<R> xy[2];           // the diagonal's x and y weights
+  cplx<double> xy[2];      // the diagonal's x and y weights
   uint32_t ob[2], ok[2];   // byte offsets within a plane (outside: kOutside)
 };
 
@@ -127,7 +147,8 @@ __device__ __forceinline__ Cols<R> cols_of(const Grid<R> &g, int gx0, int gy0, i
     // too); the diagonal only has to be invertible
     q.ym[c] = keep(q.in[c], ym);
     q.yp[c] = keep(q.in[c], yp);
-    q.xy[c] = q.in[c] ? xm + xp + ym + yp : mk<R>(1, 0);
+    q.xy[c] = q.in[c] ? cvt<double>(xm) + cvt<double>(xp) + cvt<double>(ym) + cvt<double>(yp)
+                     : mk<double>(1, 0);
     const uint32_t p = (uint32_t)(q.j * g.n0 + q.i[c]);
     q.ob[c] = q.in[c] ? p * (uint32_t)sizeof(cplx<R>) : kOutside;
     q.ok[c] = q.in[c] ? p * (uint32_t)sizeof(R) : kOutside;
@@ -149,11 +170,34 @@ __device__ __forceinline__ cplx<R> zweight(const cplx<R> *w, int k, int n2) {
   return w[k < 0 ? 0 : k >= n2 ? n2 - 1 : k];
 }
 
+// The diagonal of a node, in FP64 for both types.  Where k^2 and the mesh are
+// uniform it has the same rounding error at all nodes, which acts like an error of
+// k^2 and is not averaged away, so FP32 neither forms it nor its inverse in FP32:
+// error of a 97^3 cycle (k = 9) against 64 bits 2.6e-7 with both in FP32, 8.4e-8 so
+// (the general kernels' correction form, u + (b - M u) / D: 1.9e-7), the cycle 69.9
+// -> 71.4 us (finest up 17.8 -> 18.9); over 20 cycles of 17^3 to 161^3 0.22 to 0.94
+// of the general kernels' error.
+template <typename R>
+__device__ __forceinline__ cplx<double> diag3(cplx<double> xy, cplx<R> zm, cplx<R> zp, R k2, const Grid<R> &g) {
+  const cplx<double> z = cvt<double>(zm) + cvt<double>(zp) + cvt<double>(g.c);
+  return xy + z + (double)k2 * cvt<double>(g.beta);
+}
+
 // off-diagonal sum plus `acc` at a column-r node: own / on = x neighbours in
-// the own and the next pair, n + ym / yp = y neighbours, zm / zp in z
+// the own and the next pair, n + ym / yp = y neighbours, zm / zp in z.  FP32 sums
+// axis by axis, half the roundings of a chain on the growing sum (8.4e-8 against
+// 9.5e-8); FP64 is faster with the chain (129^3 112 us, 114 by axis) and its error
+// is that of its weights (against 80-bit arithmetic 1.9e-16 to 4.0e-16 at 17^3 and
+// 33^3, by axis 1.6e-16 to 6.2e-16, the general kernels 1.7e-16 to 4.5e-16).
 template <typename R>
 __device__ __forceinline__ cplx<R> offd3(const Cols<R> &q, int r, cplx<R> acc, cplx<R> own, const cplx<R> *n, int nx,
                                          int nym, int nyp, cplx<R> wzm, cplx<R> zm, cplx<R> wzp, cplx<R> zp) {
+  if constexpr (sizeof(R) == 4) {
+    const cplx<R> x = fma_c(q.wn[r], n[nx], q.wo[r] * own);
+    const cplx<R> y = fma_c(q.yp[r], n[nyp], q.ym[r] * n[nym]);
+    const cplx<R> z = fma_c(wzp, zp, wzm * zm);
+    return acc + ((x + y) + z);
+  }
   acc = fma_c(q.wo[r], own, acc);
   acc = fma_c(wzm, zm, acc);
   acc = fma_c(wzp, zp, acc);
@@ -228,9 +272,8 @@ __global__ __launch_bounds__(DownTile<CY>::NT) void k_down3(Grid<R> f, Grid<R> c
     const int z = gz0 + s;
     // plane z has arrived; its diagonals, and red from zero: omega b / D
     {
-      const cplx<R> zz = zm[m0] + zp[m0] + f.c;
 #pragma unroll
-      for (int e = 0; e < 2; e++) D[e][m0] = inv_d(q.xy[e] + zz + K2[e] * f.beta);
+      for (int e = 0; e < 2; e++) D[e][m0] = cvt<R>(inv_d<R>(diag3(q.xy[e], zm[m0], zp[m0], K2[e], f)));
     }
     load(z + 1, m3);
     T[r][m0] = relaxed<GS>(omega, B[r][m0]) * D[r][m0];
@@ -326,6 +369,7 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
   // t, v = t + P e (not GS: its new value does not use it) and the post-relaxed
   // u; of the black node v
   cplx<R> B[2][4], D[2][4], T[4], vR[4], vB[4], uR[4], nB[2], Ec[2], En[2];
+  Rest<R> X[2][4];
   cplx<R> zm[4], zp[4], nzm, nzp;  // z weights of the planes (uniform)
   R K2[2];
 #pragma unroll
@@ -333,7 +377,10 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
     zm[m] = zp[m] = zc<R>();
     T[m] = vR[m] = vB[m] = uR[m] = zc<R>();
 #pragma unroll
-    for (int e = 0; e < 2; e++) B[e][m] = D[e][m] = zc<R>();
+    for (int e = 0; e < 2; e++) {
+      B[e][m] = D[e][m] = zc<R>();
+      X[e][m].set(zc<double>());
+    }
   }
   Ec[0] = Ec[1] = En[0] = En[1] = zc<R>();
   auto load = [&](int k) {
@@ -356,11 +403,12 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
     {
       zm[m0] = nzm;
       zp[m0] = nzp;
-      const cplx<R> zz = nzm + nzp + f.c;
 #pragma unroll
       for (int e = 0; e < 2; e++) {
         B[e][m0] = nB[e];
-        D[e][m0] = inv_d(q.xy[e] + zz + K2[e] * f.beta);
+        const cplx<double> inv = inv_d<R>(diag3(q.xy[e], nzm, nzp, K2[e], f));
+        D[e][m0] = cvt<R>(inv);
+        X[e][m0].set(inv);
       }
     }
     load(z + 1);
@@ -392,8 +440,8 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
     {
       const cplx<R> o = offd3(q, r, B[r][m2], vB[m2], sBlk[ho], nb[r], ym, yp, zm[m2], vB[m3],
                               zp[m2], vB[m1]);
-      if constexpr (GS) uR[m2] = o * D[r][m2];
-      else uR[m2] = fma_c(omega * o, D[r][m2], om1 * vR[m2]);
+      if constexpr (GS) uR[m2] = over(o, D[r][m2], X[r][m2]);
+      else uR[m2] = add_over(omega * o, D[r][m2], X[r][m2], om1 * vR[m2]);
       sRel[h][tid] = uR[m2];
     }
     // black post-relaxation on z - 3; both nodes are final
@@ -401,8 +449,8 @@ __global__ __launch_bounds__(NT) void k_up3(Grid<R> f, Grid<R> c, const cplx<R> 
       const cplx<R> o = offd3(q, r, B[r][m3], uR[m3], sRel[ho], nb[r], ym, yp, zm[m3], uR[m0],
                               zp[m3], uR[m2]);
       cplx<R> uB;
-      if constexpr (GS) uB = o * D[r][m3];
-      else uB = fma_c(omega * o, D[r][m3], om1 * vB[m3]);
+      if constexpr (GS) uB = over(o, D[r][m3], X[r][m3]);
+      else uB = add_over(omega * o, D[r][m3], X[r][m3], om1 * vB[m3]);
       const bool zin = z - 3 >= 1 && z - 3 <= f.n2 - 2;
       const __amdgpu_buffer_rsrc_t ro = plane_rsrc(u, z - 3, z - 3 < f.n2, plane);
       st_c(ro, os[r], keep(q.in[r] && zin, uB));

@@ -352,6 +352,25 @@ def test_3d_fused_cycle(dt, n, coarsest, omega):
     assert np.array_equal(to_np(S.vcycle_native(to_gpu(v))), got)
 
 
+@pytest.mark.parametrize("n,coarsest,k,omega", [(17, 5, 9.0, 1.0), (33, 5, 5.0, 1.0), (97, 4, 9.0, 1.0),
+                                                (97, 4, 9.0, 0.9)])
+def test_3d_fp32_cycle_accuracy(n, coarsest, k, omega):
+    """The FP32 3D cycle at constant k on a mesh that is uniform inside the layers,
+    where the diagonal has the same rounding error at every node: within two FP32
+    roundings (2 x 2^-24, relative in the 2-norm) of the oracle's 64-bit cycle.  A
+    relaxation's sums, its store and the corrections' are a few independent
+    roundings of half a unit each at most; an error common to all nodes, of a
+    diagonal or an inverse formed in FP32, exceeds that (1.3e-7 to 2.6e-7 here)."""
+    w = W.cube_constant_k(n=n, k=k, coarsest=coarsest)
+    cy = dict(w.cycle, omega=omega)
+    P = oracle_for(w, cycle=cy)
+    S = gpu_for(w, "f32", cycle=cy)
+    v = W.random_complex(w.shape, np.random.default_rng(n)).astype(np.complex64)
+    ref = P.mg_apply(v.astype(np.complex128))
+    err = np.linalg.norm(to_np(S.vcycle_native(to_gpu(v))) - ref) / np.linalg.norm(ref)
+    assert err < 2.0 ** -23, err
+
+
 @pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("dim,n,coarsest,gf,gc,smoother,nu1,nu2",
                          [(2, 81, 6, 1, 3, "jacobi", 1, 1), (2, 41, 6, 1, 4, "jacobi", 1, 2),
