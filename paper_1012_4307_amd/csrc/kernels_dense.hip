@@ -12,7 +12,12 @@
 // or transfer, is a chain of latencies: 33^2 .. 9^2 took 15.5 us FP64, 12.4
 // FP32 per cycle, the 25^2 .. 4^2 end of an F_1^4 cycle 16.4 us per visit, at
 // 13 visits per cycle on 385^2 (10 maps now).  The map of a 33^2 level reads
-// 14.8 MB (FP64) over all CUs instead: 5-6 us.
+// 14.8 MB (FP64) over all CUs instead: 3.8 us, in FP32 3.5; 41^2 8 and 5.2 us.
+//
+// FP32 products and sums are FP64: the entries are rounded once already, and sums
+// of up to 25 products a lane in FP32 left a grid that is one map (41^2
+// omega-Jacobi) 9.0e-8 from the 64-bit cycle, where the level by level one was
+// 6.0e-8; now 3.7e-8, at the same 3.5 us on 33^2 and 4.7 -> 5.2 us on 41^2.
 #include "ecs_dense.h"
 #include "ecs_reduce.h"
 
@@ -81,7 +86,7 @@ __global__ __launch_bounds__(256) void k_dense(const cplx<R> *__restrict__ G, in
   const int count = MR ? rs.count : 1;
   for (int y = 0; y < count; y++) {
     const int64_t off = MR ? rs.slot[y] * rhs_stride(nn) : 0;
-    cplx<R> acc = mk<R>(0, 0);
+    cplx<double> acc = mk<double>(0, 0);
     for (int c0 = 0; c0 < N; c0 += kChunk) {
       cplx<R> v[4];
 #pragma unroll
@@ -98,10 +103,10 @@ __global__ __launch_bounds__(256) void k_dense(const cplx<R> *__restrict__ G, in
       for (int q = 0; q < Q; q++) {
         const Quad<R> x = *reinterpret_cast<const Quad<R> *>(&sb[V * (lane + 64 * q)]);
 #pragma unroll
-        for (int h = 0; h < V; h++) acc = acc + g[q].v[h] * x.v[h];
+        for (int h = 0; h < V; h++) acc = acc + cvt<double>(g[q].v[h]) * cvt<double>(x.v[h]);
       }
     }
-    const double re = wave_sum((double)acc.re), im = wave_sum((double)acc.im);
+    const double re = wave_sum(acc.re), im = wave_sum(acc.im);
     if (lane == 0 && row < N) u[off + in.node(row)] = mk<R>((R)re, (R)im);
     if (edge) u[off + p] = mk<R>(0, 0);
   }

@@ -362,13 +362,29 @@ def test_3d_fp32_cycle_accuracy(n, coarsest, k, omega):
     roundings of half a unit each at most; an error common to all nodes, of a
     diagonal or an inverse formed in FP32, exceeds that (1.3e-7 to 2.6e-7 here)."""
     w = W.cube_constant_k(n=n, k=k, coarsest=coarsest)
-    cy = dict(w.cycle, omega=omega)
-    P = oracle_for(w, cycle=cy)
-    S = gpu_for(w, "f32", cycle=cy)
-    v = W.random_complex(w.shape, np.random.default_rng(n)).astype(np.complex64)
-    ref = P.mg_apply(v.astype(np.complex128))
-    err = np.linalg.norm(to_np(S.vcycle_native(to_gpu(v))) - ref) / np.linalg.norm(ref)
+    err = fp32_cycle_error(w, dict(w.cycle, omega=omega))
     assert err < 2.0 ** -23, err
+
+
+def fp32_cycle_error(w, cycle):
+    """Error of the FP32 cycle against the oracle's, relative in the 2-norm."""
+    P = oracle_for(w, cycle=cycle)
+    S = gpu_for(w, "f32", cycle=cycle)
+    v = W.random_complex(w.shape, np.random.default_rng(w.n[0])).astype(np.complex64)
+    ref = P.mg_apply(v.astype(np.complex128))
+    return np.linalg.norm(to_np(S.vcycle_native(to_gpu(v))) - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("dim,n,coarsest,smoother", [(2, 33, 5, "rbgs"), (2, 41, 6, "jacobi"), (3, 13, 4, "rbgs"),
+                                                     (3, 13, 4, "jacobi")])
+def test_fp32_dense_map_accuracy(dim, n, coarsest, smoother):
+    """A grid that is one FP32 dense map, of two and more products a lane and of more
+    than are staged at a time (41): within one FP32 rounding (2^-24, relative in the
+    2-norm) of the oracle's cycle.  The map's entries and the result are rounded by
+    half a unit at most, independently; the sums are FP64."""
+    w = W.coulomb(E=2.0, n=n, coarsest=coarsest) if dim == 2 else W.cube_constant_k(n=n, k=5.0, coarsest=coarsest)
+    err = fp32_cycle_error(w, dict(w.cycle, smoother=smoother, omega=1.0 if smoother == "rbgs" else 0.8))
+    assert err < 2.0 ** -24, err
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
