@@ -387,6 +387,16 @@ def test_fp32_dense_map_accuracy(dim, n, coarsest, smoother):
     assert err < 2.0 ** -24, err
 
 
+@pytest.mark.parametrize("n,coarsest,gamma,omega", [(129, 5, 3, 0.6), (257, 5, 1, 0.8), (385, 4, 1, 0.8)])
+def test_fp32_jacobi_cycle_accuracy(n, coarsest, gamma, omega):
+    """FP32 omega-Jacobi cycles on the fused level kernels, where the relaxation uses
+    the diagonal's inverse directly: within two FP32 roundings (2 x 2^-24, relative
+    in the 2-norm) of the oracle's cycle, as with the 3D cycle's."""
+    w = W.coulomb(E=2.0, n=n, coarsest=coarsest)
+    err = fp32_cycle_error(w, dict(w.cycle, smoother="jacobi", omega=omega, gamma_c=gamma))
+    assert err < 2.0 ** -23, err
+
+
 @pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("dim,n,coarsest,gf,gc,smoother,nu1,nu2",
                          [(2, 81, 6, 1, 3, "jacobi", 1, 1), (2, 41, 6, 1, 4, "jacobi", 1, 2),
