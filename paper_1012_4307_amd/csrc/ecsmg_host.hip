@@ -146,13 +146,12 @@ struct ecs_ctx {
   DevLevel<double> L64[kMaxLev];
   DevLevel<float> L32[kMaxLev];
   // the coarse end of the cycle as dense maps (kernels_dense.hip), per level
-  // dtop .. coarsest in FP64: dA for a parent level visited with (gamma_f,
-  // gamma_c), dB for one visited with the two exchanged (the same map when they
-  // are equal); dA[coarsest] is the coarsest inverse.  FP32 cycles: copies of the
-  // coarsest inverse and of the maps of level d32_l, the one in use
+  // dtop .. coarsest: dA for a parent level visited with (gamma_f, gamma_c), dB for
+  // one visited with the two exchanged (the same map when they are equal);
+  // dA[coarsest] is the coarsest inverse.  FP32 cycles apply the FP32 copies
   cplx<double> *dA[kMaxLev] = {}, *dB[kMaxLev] = {};
-  cplx<float> *minv32 = nullptr, *dA32 = nullptr, *dB32 = nullptr;
-  int dtop = 0, d32_l = -1;
+  cplx<float> *dA32[kMaxLev] = {}, *dB32[kMaxLev] = {};
+  int dtop = 0;
   size_t host_bytes = 0;  // what set-up uploads: the first bytes of the workspace
   int nunk = 0;
   cplx<double> *partials = nullptr;
@@ -322,7 +321,7 @@ size_t plan_layout(ecs_ctx *C, Carver &cv) {
     }
   }
   C->dA[lc] = C->dB[lc] = cv.take<cplx<double>>(map_size(lc));
-  if (f32) C->minv32 = cv.take<cplx<float>>(map_size(lc));
+  if (f32) C->dA32[lc] = C->dB32[lc] = cv.take<cplx<float>>(map_size(lc));
   C->host_bytes = cv.off;
   C->k2_wide = C->k2_dtype == ECS_F32 ? cv.take<double>(C->hl[0].nn) : nullptr;
   for (int l = 0; l < C->nlev; l++) {
@@ -344,11 +343,11 @@ size_t plan_layout(ecs_ctx *C, Carver &cv) {
   const bool two = C->prec.gamma_f != C->prec.gamma_c;
   for (int l = C->dtop; l < lc; l++) {
     C->dA[l] = cv.take<cplx<double>>(map_size(l));
-    C->dB[l] = two && l > 0 ? cv.take<cplx<double>>(map_size(l)) : C->dA[l];
-  }
-  if (f32 && C->dtop < lc) {
-    C->dA32 = cv.take<cplx<float>>(map_size(C->dtop));
-    C->dB32 = two ? cv.take<cplx<float>>(map_size(C->dtop)) : C->dA32;
+    const bool swapped = two && l > 0;  // (no test on the pointers: they are null while the size is measured)
+    C->dB[l] = swapped ? cv.take<cplx<double>>(map_size(l)) : C->dA[l];
+    if (!f32) continue;
+    C->dA32[l] = cv.take<cplx<float>>(map_size(l));
+    C->dB32[l] = swapped ? cv.take<cplx<float>>(map_size(l)) : C->dA32[l];
   }
   C->partials = cv.take<cplx<double>>((size_t)kRedBlocks * (2 * kMaxRestart + 2));
   C->dscal = cv.take<double>(kRedBlocks + 8);
@@ -590,8 +589,7 @@ DevLevel<double> &dev_level<double>(ecs_ctx *C, int l) { return C->L64[l]; }
 template <>
 DevLevel<float> &dev_level<float>(ecs_ctx *C, int l) { return C->L32[l]; }
 
-// the dense map of level l (the coarsest inverse on the coarsest); FP32: copies
-// of the level chosen last by use_dense
+// the dense map of level l (the coarsest inverse on the coarsest)
 template <typename R>
 const cplx<R> *dense_map(const ecs_ctx *C, int l, bool swapped);
 template <>
@@ -600,8 +598,7 @@ const cplx<double> *dense_map<double>(const ecs_ctx *C, int l, bool swapped) {
 }
 template <>
 const cplx<float> *dense_map<float>(const ecs_ctx *C, int l, bool swapped) {
-  if (l == C->nlev - 1) return C->minv32;
-  return swapped ? C->dB32 : C->dA32;
+  return swapped ? C->dB32[l] : C->dA32[l];
 }
 
 // u_l = (map of level l) b_l
@@ -611,19 +608,6 @@ void dense_apply(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, bool swapped =
   const HostLevel &L = C->hl[l];
   launch_dense<R>(dense_map<R>(C, l, swapped), unknowns(C, l), L.n[0], L.n[1], L.n[2], b, u, C->stream, rs);
 }
-
-// FP32 cycles: the maps of level l in FP32 (outside any capture)
-void use_dense(ecs_ctx *C, int l) {
-  if (C->prec.vcycle_dtype != ECS_F32 || l >= C->nlev - 1 || l < C->dtop || C->d32_l == l) return;
-  const int N = unknowns(C, l);
-  const int64_t size = (int64_t)N * dense_ld(N);
-  launch_cast<double, float>(C->dA[l], C->dA32, size, C->stream);
-  if (C->dB[l] != C->dA[l]) launch_cast<double, float>(C->dB[l], C->dB32, size, C->stream);
-  C->d32_l = l;
-}
-
-int general_dense_level(const ecs_ctx *C);
-int fused_dense_level(const ecs_ctx *C);
 
 // ---------------------------------------------------------- setup
 // scale * src, as it will lie in the workspace at dst, into the host's copy of
@@ -775,7 +759,7 @@ ecs_status setup(ecs_ctx *C) {
     for (int r = 0; r < nu; r++)
       for (int q = 0; q < nu; q++) G[(size_t)r * ld + q] = M[(size_t)r * nu + q];
     stage_cx<double>(C, host, C->dA[lc], G, 1.0);
-    if (f32) stage_cx<float>(C, host, C->minv32, G, 1.0);
+    if (f32) stage_cx<float>(C, host, C->dA32[lc], G, 1.0);
   }
   // one copy (a copy per array cost about 10 us each, 50 and more of them); the
   // host's memory outlives it: set-up ends with a wait for the stream
@@ -783,7 +767,6 @@ ecs_status setup(ecs_ctx *C) {
   // the levels above it whose part of the cycle is a dense map: from the
   // coarsest up, the visits of Algorithm 1 to level l under a parent visited with
   // (gf, gc): a first cycle (gf, gc), then gc - 1 cycles (gc, gf)
-  C->d32_l = -1;
   for (int l = lc - 1; l >= C->dtop; l--) {
     const HostLevel &Lx = C->hl[l + 1];
     DenseGen g{};
@@ -806,8 +789,14 @@ ecs_status setup(ecs_ctx *C) {
       g.G = C->dB[l];
       launch_dense_gen(g, s);
     }
+    if (f32) {
+      // of every level that a schedule may start the dense end from, so that a change
+      // of the schedule launches nothing (6% more than the copy of one level)
+      const int64_t size = (int64_t)unknowns(C, l) * dense_ld(unknowns(C, l));
+      launch_cast<double, float>(C->dA[l], C->dA32[l], size, s);
+      if (C->dB[l] != C->dA[l]) launch_cast<double, float>(C->dB[l], C->dB32[l], size, s);
+    }
   }
-  use_dense(C, fused_vcycle(C) ? fused_dense_level(C) : general_dense_level(C));
   // Krylov scalars start cleared
   HIP_OK(hipMemsetAsync(C->gs, 0, sizeof(GmresScalars), s));
   HIP_OK(hipMemsetAsync(C->bs, 0, 3 * kMaxRhs * sizeof(BicgScalars), s));
@@ -1020,11 +1009,6 @@ FusedPlan fused_plan(const ecs_ctx *C) {
   return P;
 }
 
-int fused_dense_level(const ecs_ctx *C) {
-  const FusedPlan P = fused_plan(C);
-  return P.wide ? C->nlev - 1 : P.lt;
-}
-
 // A Bi-CGSTAB (the nested FP32 one, or the outer one with the FP64 cycle) can
 // form each cycle's right-hand side (its p and s updates) inside the finest
 // level's down kernel when that level has one and the cycle is launched
@@ -1183,7 +1167,7 @@ void vcycle_fused(ecs_ctx *C, const cplx<R> *b0, cplx<R> *u0, const DownSrc<R> *
       }
       a.b0 = lt == 0 ? b0 : B.b[lt];
       a.u0 = lt == 0 ? u0 : B.u[lt];
-      a.minv = C->minv32;
+      a.minv = C->dA32[C->nlev - 1];
       a.nunk = C->nunk;
       a.tpr = 64;
       while (a.tpr > 1 && a.tpr * C->nunk > 1024) a.tpr >>= 1;
@@ -2513,7 +2497,7 @@ ecs_status ecs_set_workspace(ecs_ctx *C, void *dev, size_t bytes) {
   C->ws = reinterpret_cast<char *>(dev);
   C->ws_bytes = bytes;
   C->hier_bytes = hb;
-  plan_hierarchy(C, C->ws);
+  if (plan_hierarchy(C, C->ws) > hb) return fail(C, ECS_ESTATE, "workspace layout exceeds its measured size");
   C->ready = false;
   ecs_status st = setup(C);
   if (st != ECS_OK) return st;
@@ -2902,7 +2886,6 @@ ecs_status ecs_set_tuning(ecs_ctx *C, const ecs_tuning *t) {
   if (t->fuse_updates != 0 && t->fuse_updates != 1) return fail(C, ECS_EINVAL, "fuse_updates must be 0 or 1");
   C->tune = *t;
   drop_graphs(C);
-  if (C->ready) use_dense(C, fused_vcycle(C) ? fused_dense_level(C) : general_dense_level(C));
   return ECS_OK;
 }
 

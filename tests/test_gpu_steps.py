@@ -440,6 +440,27 @@ def test_fused_jacobi_cycle(dt, n, coarsest, gf, gc):
     assert np.all(got[[0, -1]] == 0) and np.all(got[:, [0, -1]] == 0)
 
 
+def test_schedule_change_launches_nothing():
+    """A schedule set while the context's stream is being captured, by a program that
+    then drops the graph: the eager cycles after it use the new schedule's FP32 map
+    (the dense end from 17^2 instead of 33^2)."""
+    import torch
+    w = W.coulomb(E=2.0, n=129)
+    P = oracle_for(w)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        S = gpu_for(w, "f32")
+        v = W.random_complex(w.shape, np.random.default_rng(8))
+        ref = P.mg_apply(v)
+        assert relerr(to_np(S.vcycle(to_gpu(v))), ref) < CYCLE_TOL["f32"]
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            S.set_tuning(tail_nodes=17)
+        del g
+        assert relerr(to_np(S.vcycle(to_gpu(v))), ref) < CYCLE_TOL["f32"]
+
+
 def test_full_size_vcycle_sampled():
     """The benchmark grid (2049^2, h = 0.25, 9 levels): one FP64 cycle checked
     against the oracle on the whole grid (one oracle cycle takes seconds)."""
