@@ -343,7 +343,10 @@ size_t plan_layout(ecs_ctx *C, Carver &cv) {
   const bool two = C->prec.gamma_f != C->prec.gamma_c;
   for (int l = C->dtop; l < lc; l++) {
     C->dA[l] = cv.take<cplx<double>>(map_size(l));
-    const bool swapped = two && l > 0;  // (no test on the pointers: they are null while the size is measured)
+    // the finest level is visited once, with (gamma_f, gamma_c): no cycle applies an
+    // exchanged map of level 1, nor builds one from it (41^2: 37 MB, 0.3 ms of set-up).
+    // (No test on the pointers: they are null while the size is measured.)
+    const bool swapped = two && l > 1;
     C->dB[l] = swapped ? cv.take<cplx<double>>(map_size(l)) : C->dA[l];
     if (!f32) continue;
     C->dA32[l] = cv.take<cplx<float>>(map_size(l));

@@ -440,6 +440,26 @@ def test_fused_jacobi_cycle(dt, n, coarsest, gf, gc):
     assert np.all(got[[0, -1]] == 0) and np.all(got[:, [0, -1]] == 0)
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_exchanged_maps_only_below_level_one(dt):
+    """The workspace of an F cycle holds maps for the exchanged cycle indices from
+    level 2 on: against a W cycle, which has none, 21^2 and 11^2 maps more and no
+    41^2 one."""
+    import ctypes
+    import paper_1012_4307_amd as E
+    w = ragged_workload(n=81, coarsest=6, kind="csl", smoother="jacobi", omega=0.8)
+
+    def size(gf, gc):
+        n = ctypes.c_size_t()
+        S = gpu_for(w, dt, cycle=dict(w.cycle, gamma_f=gf, gamma_c=gc))
+        assert E.lib().ecs_workspace_size(S._h, None, ctypes.byref(n)) == 0
+        return n.value
+
+    entry = 16 + (8 if dt == "f32" else 0)
+    maps = entry * (19 * 19 * (19 * 19 + 1) + 81 * 82)
+    assert abs(size(1, 2) - size(2, 2) - maps) <= 8 * 256
+
+
 def test_schedule_change_launches_nothing():
     """A schedule set while the context's stream is being captured, by a program that
     then drops the graph: the eager cycles after it use the new schedule's FP32 map
