@@ -1392,14 +1392,20 @@ double read_scalar(ecs_ctx *C, const double *dev) {
 // and the matvec, which touch neither the solution nor the state that a stop
 // or a restart uses) before it waits for this step's residual estimate.  The
 // device then has work while the host wakes up, reads and launches: 8-15 us a
-// step (513^2 Bi-CGSTAB 135 -> 125 us, 65^2 GMRES 90 -> 78 us).  One opening
-// per stop or restart is wasted, so not on grids whose step takes much longer
-// than the wait.
+// step (513^2 Bi-CGSTAB 135 -> 125 us, 65^2 GMRES 90 -> 78 us).  An opening before
+// a stop is wasted and delays the call (513^2 40 us, 1409^2 140 us: solves of one
+// step took up to 1.06 and 1.16 times as long), so not where `last`, the estimate
+// of the step before, says that this step may be the last one: within twice the
+// tolerance (Bi-CGSTAB takes a factor of 1.3 off a step), four times after the first
+// step, which takes off more, and where an opening costs many waits; and not on
+// grids whose step takes much longer than the wait.
 constexpr int64_t kAheadMaxNodes = int64_t(1) << 21;
-bool run_ahead(const ecs_ctx *C) {
+constexpr int64_t kAheadDearNodes = int64_t(1) << 19;
+bool run_ahead(const ecs_ctx *C, bool first, double last, double rtol) {
   for (const Timer &T : C->timers)
     if (T.on) return false;  // kernel timers count the launches of the steps reported
-  return nn_of(C) <= kAheadMaxNodes;
+  const int64_t n = nn_of(C);
+  return n <= kAheadMaxNodes && last > (first || n > kAheadDearNodes ? 4 : 2) * rtol;
 }
 
 // The event behind the kernel that reports a step's end (StepReport, at the start
@@ -1617,6 +1623,7 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       launch_apply<double, RZ, double>(grid_A(C), zj, w, s);
     };
     bool opened = false;
+    double last = rt;
     for (int j = 0; j < m && it < d->maxit; j++) {
       cplx<double> *w = K.V + (int64_t)(j + 1) * ld;
       if (!opened) open_step(j);
@@ -1629,7 +1636,7 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       k = j + 1;
       if (!mark_report(C)) { bad = true; break; }
       // a nested run is far longer than the wait
-      opened = d->inner == 0 && j + 1 < m && it < d->maxit && run_ahead(C);
+      opened = d->inner == 0 && j + 1 < m && it < d->maxit && run_ahead(C, j == 0, last, d->rtol);
       if (opened) open_step(j + 1);
       StepReport end;
       if (!wait_readback(C, &end)) { bad = true; break; }
@@ -1638,6 +1645,7 @@ ecs_status gmres(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, const
       if (d->history && it - 1 < d->history_len) d->history[it - 1] = est;
       if (!(est == est) || std::isinf(est)) { bad = true; break; }
       if (est <= d->rtol || happy) break;
+      last = est;
     }
     if (bad) {
       status = fail(C, ECS_EBREAKDOWN, "GMRES: Givens residual estimate is NaN/Inf");
@@ -1797,14 +1805,15 @@ ecs_status bicgstab(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, co
     }
     last_restart = rt;
     bool opened = false;
+    double last = rt;
     BicgFold alpha{};
-    while (it < d->maxit) {
+    for (bool first = true; it < d->maxit; first = false) {
       if (!opened) alpha = bicg_open_step<RZ>(C, K);
       bicg_close_step<RZ>(C, K, x, alpha);
       if (!mark_report(C)) break;
       st->vcycles += 2;
       it++;
-      opened = it < d->maxit && run_ahead(C);
+      opened = it < d->maxit && run_ahead(C, first, last, d->rtol);
       if (opened) alpha = bicg_open_step<RZ>(C, K);
       StepReport end;
       if (!wait_readback(C, &end)) break;
@@ -1813,6 +1822,7 @@ ecs_status bicgstab(ecs_ctx *C, const ecs_solve_desc *d, const KrylovBufs &K, co
       if (d->history && it - 1 < d->history_len) d->history[it - 1] = est;
       if (bad) break;  // restart from the current iterate
       if (est <= d->rtol) break;
+      last = est;
     }
     st->restarts++;
   }

@@ -466,6 +466,24 @@ def test_nested_updates_fused_full_size():
     assert torch.equal(xs[0], xs[1])
 
 
+@pytest.mark.parametrize("method", ["fgmres", "bicgstab"])
+def test_no_opening_before_a_likely_stop(method):
+    """A solve that its first step ends enqueues nothing of a second one: the
+    workspace is left as by the same solve with one iteration allowed (the second
+    step's preconditioned direction would be a vector of it)."""
+    w = W.coulomb(E=2.0, n=257)
+    S = gpu_for(w, "f64", krylov=E.Krylov(method=method, restart=30, rtol=1e-8))
+    b = to_gpu(w.rhs[0])
+    x1, st = S.solve(b, krylov=E.Krylov(method=method, restart=30, rtol=1e-8, maxit=1))
+    first = st["rel_residual"]
+    assert st["iterations"] == 1 and 0.26 < first < 1, st
+    left = S.ws.clone()
+    x, st = S.solve(b, krylov=E.Krylov(method=method, restart=30, rtol=1.001 * first, maxit=100))
+    assert st["status"] == 0 and st["iterations"] == 1, st
+    assert bool((x == x1).all())
+    assert int((S.ws != left).sum()) < 1024
+
+
 def test_status_paths():
     w = W.small_constant_k(n=33)
     S = gpu_for(w, "f64")
