@@ -393,7 +393,10 @@ ecs_status ecs_set_graphs(ecs_ctx *ctx, int mode);
  *   all of them in one launch (per right-hand side the same arithmetic as a
  *   single solve); other set-ups take them one at a time.  The workspace must
  *   hold that many at once (ecs_workspace_size with that nrhs; 1 for other
- *   set-ups), else ECS_ENOMEM.
+ *   set-ups), else ECS_ENOMEM.  Where the cycles form the updates (fuse_updates,
+ *   up to 1025^2, not ECS_GRAPHS_ALWAYS) the size counts a second search direction
+ *   per right-hand side; a workspace sized while they did not is solved in with
+ *   separate updates (the same values).
  *   Scheduling: the driver enqueues one round of a system at a time on that
  *   system's stream (the restarts -- true residuals -- of the right-hand sides
  *   that need one, one iteration of the others, one readback), records an

@@ -415,8 +415,9 @@ struct KrylovBufs {
 constexpr int64_t kFuse64MaxNodes = int64_t(1025) * 1025;
 
 // Storage of the batched Bi-CGSTAB for `slots` right-hand sides at once (one
-// group of a system's right-hand sides; see batch_solve_impl).
-size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
+// group of a system's right-hand sides; see batch_solve_impl).  p2: with the
+// second p buffer of the update inside the cycle (batch_p2).
+size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K, bool p2) {
   Carver cv(base);
   const int64_t n = nn_of(C), sn = rhs_stride(n) * slots;
   const bool f32 = C->prec.vcycle_dtype == ECS_F32;
@@ -434,7 +435,7 @@ size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
   K->ph = cv.take<char>(sn * zs);
   K->sh = cv.take<char>(sn * zs);
   K->b32 = f32 ? cv.take<char>(sn * zs) : nullptr;
-  K->p2 = !f32 && n <= kFuse64MaxNodes ? cv.take<cplx<double>>(sn) : nullptr;
+  K->p2 = p2 ? cv.take<cplx<double>>(sn) : nullptr;
   for (int l = 0; l < C->nlev; l++) {
     const int64_t sl = rhs_stride(C->hl[l].nn) * slots;
     K->lt[l] = cv.take<char>(sl * zs);
@@ -442,6 +443,12 @@ size_t plan_batch(const ecs_ctx *C, int slots, char *base, KrylovBufs *K) {
     K->lu[l] = l == 0 ? nullptr : cv.take<char>(sl * zs);
   }
   return cv.off;
+}
+
+// Whether the batched solve's cycles form p (batch_step).
+bool fused_updates(const ecs_ctx *C);
+bool batch_p2(const ecs_ctx *C) {
+  return C->prec.vcycle_dtype == ECS_F64 && nn_of(C) <= kFuse64MaxNodes && fused_updates(C);
 }
 
 size_t plan_krylov(const ecs_ctx *C, const ecs_solve_desc *d, char *base, KrylovBufs *K) {
@@ -2116,11 +2123,14 @@ ecs_status batch_solve_impl(int n, ecs_ctx *const *ctxs, const ecs_solve_desc *c
     // right-hand sides at once: up to kMaxRhs (or the desc's nrhs) with the fused cycle
     const int cap = d->nrhs > 0 ? std::min(d->nrhs, kMaxRhs) : kMaxRhs;
     I.group = fused_vcycle(C) ? std::max(1, std::min(nrhs[q], cap)) : 1;
-    const size_t need = C->hier_bytes + plan_batch(C, I.group, nullptr, &I.K);
-    if (need > C->ws_bytes)
+    // a workspace sized while the updates were separate has no room for the second
+    // p buffer: they stay separate then
+    const auto need = [&](bool p2) { return C->hier_bytes + plan_batch(C, I.group, nullptr, &I.K, p2); };
+    const bool p2 = batch_p2(C) && need(true) <= C->ws_bytes;
+    if (need(p2) > C->ws_bytes)
       return fail(C, ECS_ENOMEM, "workspace too small for the batched solve (size it with nrhs = " +
                                      std::to_string(I.group) + " right-hand sides at once)");
-    plan_batch(C, I.group, C->ws + C->hier_bytes, &I.K);
+    plan_batch(C, I.group, C->ws + C->hier_bytes, &I.K, p2);
     I.C = C;
     I.d = d;
     I.b0 = reinterpret_cast<const cplx<double> *>(b[q]);
@@ -2490,9 +2500,11 @@ ecs_status ecs_workspace_size(ecs_ctx *C, const ecs_solve_desc *d, size_t *bytes
   if (d && (d->restart < 1 || d->restart > kMaxRestart)) return fail(C, ECS_EINVAL, "restart must be in [1, 64]");
   if (d && (d->nrhs < 0 || d->nrhs > kMaxRhs)) return fail(C, ECS_EINVAL, "nrhs must be in [0, 8]");
   build_host_levels(C);
+  C->dtop = dense_top(C);  // batch_p2 asks for the schedule before a workspace is laid out
   KrylovBufs K, KB;
   size_t kb = plan_krylov(C, d, nullptr, &K);
-  if (d && d->krylov == ECS_KRYLOV_BICGSTAB && d->nrhs > 0) kb = std::max(kb, plan_batch(C, d->nrhs, nullptr, &KB));
+  if (d && d->krylov == ECS_KRYLOV_BICGSTAB && d->nrhs > 0)
+    kb = std::max(kb, plan_batch(C, d->nrhs, nullptr, &KB, batch_p2(C)));
   *bytes = plan_hierarchy(C, nullptr) + 256 + kb + 256;
   return ECS_OK;
 }

@@ -285,3 +285,45 @@ def test_batch_dense_end_equals_single_solves(dt, n, coarsest):
     assert stats[0]["status"] == 0, stats
     for r in range(5):
         assert torch.equal(xs[0][r], S.solve(B[r].contiguous(), krylov=kr)[0]), r
+
+
+def test_second_search_direction_only_where_the_cycle_forms_it():
+    """The batched workspace holds a second p per right-hand side only when the
+    cycles form the updates; a workspace sized while they did not still solves
+    after they were switched on, with the same bits."""
+    import ctypes
+    import dataclasses
+    import torch
+    kr = E.Krylov(method="bicgstab", rtol=1e-9, maxit=5000)
+    k8 = dataclasses.replace(kr, nrhs=8)
+
+    def size(S):
+        n = ctypes.c_size_t()
+        assert E.lib().ecs_workspace_size(S._h, ctypes.byref(k8.to_c()), ctypes.byref(n)) == 0
+        return n.value
+
+    w = W.coulomb(E=1.5, n=257)
+    S = gpu_for(w, "f64", krylov=kr)
+    full = size(S)
+    S.set_graphs(True)
+    graphs = size(S)
+    S.set_graphs("auto")
+    S.set_tuning(fuse_updates=0)
+    separate = size(S)
+    assert full - separate >= 8 * 257 * 257 * 16 and graphs == separate
+    rng = np.random.default_rng(78)
+    B = torch.stack([to_gpu(W.random_complex(w.shape, rng)) for _ in range(8)])
+    S.ws = None
+    S._ensure_workspace(k8)
+    S.set_tuning(fuse_updates=1)
+    x = torch.empty_like(B)
+    d = k8.to_c()
+    torch.cuda.synchronize()
+    rc = E.lib().ecs_batch_solve(1, (ctypes.c_void_p * 1)(S._h.value),
+                                 (ctypes.POINTER(E.SolveDesc) * 1)(ctypes.pointer(d)),
+                                 (ctypes.c_void_p * 1)(B.data_ptr()), (ctypes.c_void_p * 1)(x.data_ptr()),
+                                 (ctypes.c_int * 1)(8), (E.Stats * 1)())
+    assert rc == 0
+    ref, _ = E.batch_solve([gpu_for(w, "f64", krylov=kr)], [B], kr)
+    torch.cuda.synchronize()
+    assert torch.equal(x, ref[0])
