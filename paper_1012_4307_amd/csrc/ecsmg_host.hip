@@ -968,8 +968,8 @@ void jacobi_visits(ecs_ctx *C, int l, const cplx<R> *b, cplx<R> *u, int gf, int 
 // kernels: one down and one up kernel per level.
 bool fused_vcycle(const ecs_ctx *C) {
   const ecs_prec_desc &P = C->prec;
-  return C->dim == 2 && P.smoother == ECS_SMOOTH_RBGS && P.nu1 == 1 && P.nu2 == 1 && P.gamma_f == 1 &&
-         P.gamma_c == 1 && C->nlev > 1;
+  return P.kind != ECS_PREC_NONE && C->dim == 2 && P.smoother == ECS_SMOOTH_RBGS && P.nu1 == 1 && P.nu2 == 1 &&
+         P.gamma_f == 1 && P.gamma_c == 1 && C->nlev > 1;
 }
 
 // The same cycle in 3D: one down and one up kernel per level as well.

@@ -466,6 +466,38 @@ def test_nested_updates_fused_full_size():
     assert torch.equal(xs[0], xs[1])
 
 
+def test_no_preconditioner_runs_no_cycle():
+    """kind "none" is the unpreconditioned method for the Bi-CGSTAB, single and
+    batched, too, also where its cycle settings are those of the fused cycle: no
+    kernel of a cycle runs, and five steps are those of a plain NumPy Bi-CGSTAB."""
+    w = W.coulomb(E=2.0, n=129)
+    P = oracle_for(w)
+    kr = E.Krylov(method="bicgstab", rtol=1e-30, maxit=5)
+    S = gpu_for(w, "f64", prec=dict(kind="none"), krylov=kr)
+    b = w.rhs[0].copy()
+    b[[0, -1]] = b[:, [0, -1]] = 0
+    classes = ("down", "down_p", "down_s", "up")
+    for cls in classes:
+        S.timing(cls, True)
+    x, st = S.solve(to_gpu(b), krylov=kr)
+    xs, _ = E.batch_solve([S], [to_gpu(b)[None].contiguous()], kr)
+    assert st["iterations"] == 5 and all(S.timing_read(cls)[0] == 0 for cls in classes)
+    y, r = np.zeros_like(b), b.copy()
+    rh, p, v = r.copy(), 0 * b, 0 * b
+    rho = alpha = omega = 1.0
+    for _ in range(5):
+        rho, old = np.vdot(rh, r), rho
+        p = r + rho / old * alpha / omega * (p - omega * v)
+        v = P.apply(p)
+        alpha = rho / np.vdot(rh, v)
+        s = r - alpha * v
+        t = P.apply(s)
+        omega = np.vdot(t, s) / np.vdot(t, t)
+        y += alpha * p + omega * s
+        r = s - omega * t
+    assert relerr(to_np(x), y) < 1e-9 and relerr(to_np(xs[0][0]), y) < 1e-9
+
+
 @pytest.mark.parametrize("method", ["fgmres", "bicgstab"])
 def test_no_opening_before_a_likely_stop(method):
     """A solve that its first step ends enqueues nothing of a second one: the
