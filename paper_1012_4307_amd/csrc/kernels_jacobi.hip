@@ -316,9 +316,11 @@ void launch_jacobi_up(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, cons
   // six rows a block while the level then is a few blocks per CU, 14 above (with
   // A two fewer: two and four row slots of a wave as well)
   const bool low = f.n1 <= 513;
-  if (ap && low) go(std::integral_constant<int, 4>(), std::true_type());
-  else if (ap) go(std::integral_constant<int, 12>(), std::true_type());
-  else if (low) go(std::integral_constant<int, 6>(), std::false_type());
+  if constexpr (sizeof(R) == 8) {  // an Arnoldi step's vectors are FP64
+    if (ap && low) return go(std::integral_constant<int, 4>(), std::true_type());
+    if (ap) return go(std::integral_constant<int, 12>(), std::true_type());
+  }
+  if (low) go(std::integral_constant<int, 6>(), std::false_type());
   else go(std::integral_constant<int, 14>(), std::false_type());
 }
 

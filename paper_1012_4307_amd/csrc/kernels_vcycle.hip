@@ -913,11 +913,14 @@ void launch_down_mr(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b
   }
 }
 
+// Several right-hand sides: FP64 forms p and s for them (the batched solve), FP32
+// for one only (the nested Bi-CGSTAB).
 template <typename R, int SRC, bool FOLD>
 void launch_down(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const DownSrc<R> &src, cplx<R> *rc,
                  R omega, int rows, hipStream_t s, const RhsSet &rs) {
-  if (multi_rhs(rs)) launch_down_mr<R, SRC, true, FOLD>(fine, coarse, b, src, rc, omega, rows, s, rs);
-  else launch_down_mr<R, SRC, false, FOLD>(fine, coarse, b, src, rc, omega, rows, s, rs);
+  if constexpr (SRC == kDownSrcB || sizeof(R) == 8)
+    if (multi_rhs(rs)) return launch_down_mr<R, SRC, true, FOLD>(fine, coarse, b, src, rc, omega, rows, s, rs);
+  launch_down_mr<R, SRC, false, FOLD>(fine, coarse, b, src, rc, omega, rows, s, rs);
 }
 
 template <typename R>
@@ -931,8 +934,10 @@ void launch_down_rb_src(const Grid<R> &fine, const Grid<R> &coarse, const DownSr
                         int rows, hipStream_t s, const RhsSet &rs) {
   const bool fold = src.nb > 0;
   if (src.mode == kDownSrcP) {
-    if (fold) launch_down<R, kDownSrcP, true>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
-    else launch_down<R, kDownSrcP, false>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
+    // beta is pending in the nested solve only: FP64 drivers read each step's end
+    if constexpr (sizeof(R) == 4)
+      if (fold) return launch_down<R, kDownSrcP, true>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
+    launch_down<R, kDownSrcP, false>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
   } else {
     if (fold) launch_down<R, kDownSrcS, true>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
     else launch_down<R, kDownSrcS, false>(fine, coarse, nullptr, src, rc, omega, rows, s, rs);
@@ -973,13 +978,10 @@ void launch_up_mr(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cp
 template <typename R, bool MR, int TY>
 void launch_up_apply(const Grid<R> &f, const Grid<R> &c, const cplx<R> *b, const cplx<R> *ec, cplx<R> *u,
                      const UpApply<R> &ap, hipStream_t s, const RhsSet &rs) {
-  if (ap.mode == kBicgAlpha) {
-    launch_up<R, TY, MR, true, kBicgAlpha>(f, c, b, ec, u, R(1), s, rs, ap);
-  } else if (ap.mode == kBicgOmega) {
-    launch_up<R, TY, MR, true, kBicgOmega>(f, c, b, ec, u, R(1), s, rs, ap);
-  } else if constexpr (!MR) {  // Arnoldi steps have one right-hand side
-    launch_up<R, TY, MR, true, kUpApplyOnly>(f, c, b, ec, u, R(1), s, rs, ap);
-  }
+  if (ap.mode == kBicgAlpha) return launch_up<R, TY, MR, true, kBicgAlpha>(f, c, b, ec, u, R(1), s, rs, ap);
+  if (ap.mode == kBicgOmega) return launch_up<R, TY, MR, true, kBicgOmega>(f, c, b, ec, u, R(1), s, rs, ap);
+  // Arnoldi steps have one right-hand side, and FP64 vectors
+  if constexpr (!MR && sizeof(R) == 8) launch_up<R, TY, MR, true, kUpApplyOnly>(f, c, b, ec, u, R(1), s, rs, ap);
 }
 
 template <typename R>
@@ -992,11 +994,15 @@ void launch_up_rb(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, 
 template <typename R>
 void launch_up_rb_apply(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R> *b, const cplx<R> *ec,
                         cplx<R> *u_out, const UpApply<R> &ap, int rows, hipStream_t s, const RhsSet &rs) {
-  const bool mr = multi_rhs(rs);
   constexpr int kTall = up_tall<R>();
-  if (mr && rows == 4) launch_up_apply<R, true, 4>(fine, coarse, b, ec, u_out, ap, s, rs);
-  else if (mr) launch_up_apply<R, true, kTall>(fine, coarse, b, ec, u_out, ap, s, rs);
-  else if (rows == 4) launch_up_apply<R, false, 4>(fine, coarse, b, ec, u_out, ap, s, rs);
+  if constexpr (sizeof(R) == 8) {  // FP32: the nested Bi-CGSTAB, one right-hand side
+    if (multi_rhs(rs)) {
+      if (rows == 4) launch_up_apply<R, true, 4>(fine, coarse, b, ec, u_out, ap, s, rs);
+      else launch_up_apply<R, true, kTall>(fine, coarse, b, ec, u_out, ap, s, rs);
+      return;
+    }
+  }
+  if (rows == 4) launch_up_apply<R, false, 4>(fine, coarse, b, ec, u_out, ap, s, rs);
   else launch_up_apply<R, false, kTall>(fine, coarse, b, ec, u_out, ap, s, rs);
 }
 

@@ -4,6 +4,7 @@ before touching a device.  No compute call is made."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -79,3 +80,16 @@ def test_probe_header_symbols_are_exported_and_check_arguments():
     assert g(8, 0, 0, ctypes.byref(ub), ctypes.byref(ul)) == -1
     assert g(8, 10, (1 << 20) + 8, ctypes.byref(ub), ctypes.byref(ul)) == -1
     assert g(8, 10, 0, None, ctypes.byref(ul)) == -1
+
+
+def test_no_kernel_forms_without_a_caller():
+    """Forms that no call reaches are not compiled: FP32 updates inside the cycle for
+    several right-hand sides, FP64 ones with a pending beta, and the operator inside
+    an FP32 up kernel for several right-hand sides or an Arnoldi step."""
+    names = subprocess.run(["nm", "-C", E.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    kernels = set(re.findall(r"(k_\w+<[^()]*>)\(", names))
+    assert any(k.startswith("k_down_rb<float, 8, 1, false, true") for k in kernels)
+    for form in (r"k_down_rb<float, \d+, [12], true, .*", r"k_down_rb<double, \d+, 1, \w+, true, \w+>",
+                 r"k_up_rb<float, \d+, true, \w+, [1-9]>", r"k_up_rb<float, \d+, \w+, \w+, 3>",
+                 r"k_jac_up<float, \d+, true>"):
+        assert not [k for k in kernels if re.fullmatch(form, k)], form
