@@ -139,7 +139,7 @@ void launch_bicg_xr(cplx<R> *x, const cplx<RZ> *ph, const cplx<RZ> *sh, cplx<R> 
 template <typename R>
 BicgFold launch_bicg_r(cplx<R> *r, const cplx<R> *sv, const cplx<R> *t, const cplx<R> *rh, int64_t n,
                        cplx<double> *partials, const BicgFold &f, BicgScalars *S2, BicgScalars *S,
-                       cplx<double> *coef, hipStream_t s);
+                       cplx<double> *coef, hipStream_t s, int limit);
 template <typename R>
 void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_t ld, int count,
                         const cplx<double> *coef, int64_t n, hipStream_t s);
@@ -148,17 +148,18 @@ void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_
 // The one-block reduction and update of the recurrence, from *in to *out.
 void launch_bicg_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in, BicgScalars *out,
                        int mode, hipStream_t s, const RhsSet &rs = one_rhs(), StepReport *host = nullptr);
-// few partials: left to the next kernel (the BicgFold returned), else reduced to *out
+// up to `limit` partials: left to the next kernel (the BicgFold returned), else
+// reduced to *out (limit: kFoldPartials; a context can lower it, with the same bits)
 inline BicgFold bicg_fold_or_final(const cplx<double> *partials, int nblocks, int npairs, const BicgScalars *in,
-                                   BicgScalars *out, int mode, hipStream_t s, const RhsSet &rs = one_rhs()) {
-  if (nblocks <= kFoldPartials) return BicgFold{in, out, partials, nblocks};
+                                   BicgScalars *out, int mode, hipStream_t s, const RhsSet &rs, int limit) {
+  if (nblocks <= limit) return BicgFold{in, out, partials, nblocks};
   launch_bicg_final(partials, nblocks, npairs, in, out, mode, s, rs);
   return bicg_scalars(out);
 }
 template <typename R, typename RI>
 BicgFold launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
                           cplx<double> *partials, const BicgScalars *in, BicgScalars *out, hipStream_t s,
-                          const RhsSet &rs = one_rhs());
+                          const RhsSet &rs, int limit);
 
 template <typename RI, typename RO>
 void launch_cast(const cplx<RI> *x, cplx<RO> *y, int64_t n, hipStream_t s, const RhsSet &rs = one_rhs());

@@ -87,13 +87,25 @@ __device__ __forceinline__ cplx<double> strided_sum(const cplx<double> *x, int n
   return s;
 }
 
+// The recurrence's products and quotients, with the fused operations written out:
+// the compiler fuses a * b - c * d one way or the other depending on the code
+// around it, and the recurrence runs in kernels of several kinds.
+__device__ __forceinline__ cplx<double> mul_rec(cplx<double> a, cplx<double> b) {
+  return mk<double>(fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re));
+}
+__device__ __forceinline__ double abs2_rec(cplx<double> a) { return fma(a.re, a.re, a.im * a.im); }
+__device__ __forceinline__ cplx<double> div_rec(cplx<double> a, cplx<double> b) {
+  const double inv = 1.0 / abs2_rec(b);
+  return inv * mul_rec(a, conjg(b));
+}
+
 // Bi-CGSTAB scalar recurrence on the reduced dot products d0, d1.
 __device__ inline void bicg_update(BicgScalars *S, int mode, cplx<double> d0, cplx<double> d1) {
   const cplx<double> zero = mk<double>(0, 0);
   switch (mode) {
     case kBicgAlpha:  // alpha = rho / (r^, v)
-      if (abs2(d0) == 0 || S->bad) { S->bad = 1; S->alpha = zero; break; }
-      S->alpha = cdiv(S->rho, d0);
+      if (abs2_rec(d0) == 0 || S->bad) { S->bad = 1; S->alpha = zero; break; }
+      S->alpha = div_rec(S->rho, d0);
       break;
     case kBicgOmega:  // omega = (t, s) / (t, t)
       if (d1.re == 0 || S->bad) { S->bad = 1; S->omega = zero; break; }
@@ -113,11 +125,11 @@ __device__ inline void bicg_update(BicgScalars *S, int mode, cplx<double> d0, cp
       S->rnorm2 = d0.re;
       S->est = sqrt(d0.re) / S->bnorm;
       if (!(S->est == S->est) || isinf(S->est)) S->bad = 1;
-      if (abs2(d1) == 0 || abs2(S->rho) == 0 || abs2(S->omega) == 0 || S->bad) {
+      if (abs2_rec(d1) == 0 || abs2_rec(S->rho) == 0 || abs2_rec(S->omega) == 0 || S->bad) {
         S->bad = 1; S->beta = zero; S->alpha = zero; S->omega = zero;
         break;
       }
-      S->beta = cdiv(d1, S->rho) * cdiv(S->alpha, S->omega);
+      S->beta = mul_rec(div_rec(d1, S->rho), div_rec(S->alpha, S->omega));
       S->rho = d1;
       break;
     }

@@ -183,6 +183,7 @@ struct ecs_ctx {
   std::vector<GraphEntry> graphs;
   hipStream_t capture = nullptr;
   int graph_mode = ECS_GRAPHS_AUTO;
+  int fold = kFoldPartials;  // ecs_test_fold_limit
 
   // launch schedule of the fused V(1,1) cycle (autotuned per grid and dtype)
   ecs_tuning tune{4, 8, 513, 33, 129, 1};
@@ -1098,7 +1099,7 @@ template <typename R>
 BicgFold up_apply_dot(const ecs_ctx *C, const UpApply<R> &ap, const BicgScalars *in, BicgScalars *out, hipStream_t s,
                       const RhsSet &rs = one_rhs()) {
   return bicg_fold_or_final(ap.partials, up_rb_blocks(C->hl[0].n[0], C->hl[0].n[1], up_rows<R>(C, 0)),
-                            ap.mode == kBicgAlpha ? 1 : 2, in, out, ap.mode, s, rs);
+                            ap.mode == kBicgAlpha ? 1 : 2, in, out, ap.mode, s, rs, C->fold);
 }
 
 // The finest level's up pass of the fused cycle, with A applied to its result
@@ -1476,7 +1477,8 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
       vcycle<R>(C, p_old, fph, fa ? &av : nullptr);
     }
     const BicgFold alpha = fa ? up_apply_dot<R>(C, av, S, S1, s)
-                              : launch_apply_dot<R, R>(gA, fph, fv, frh, kBicgAlpha, C->partials, S, S1, s);
+                              : launch_apply_dot<R, R>(gA, fph, fv, frh, kBicgAlpha, C->partials, S, S1, s, one_rhs(),
+                                                       C->fold);
     if (fuse) {
       const DownSrc<R> ss{kDownSrcS, fr, nullptr, fv, fs, alpha.in, alpha.out, alpha.partials, alpha.nb};
       vcycle_fused<R>(C, fs, fsh, &ss, nullptr, one_rhs(), fa ? &at : nullptr);
@@ -1485,8 +1487,9 @@ void inner_bicgstab(ecs_ctx *C, const KrylovBufs &K, const cplx<double> *v, cplx
       vcycle<R>(C, fs, fsh, fa ? &at : nullptr);
     }
     const BicgFold omega = fa ? up_apply_dot<R>(C, at, S1, S2, s)
-                              : launch_apply_dot<R, R>(gA, fsh, ft, fs, kBicgOmega, C->partials, S1, S2, s);
-    beta = launch_bicg_r<R>(fr, fs, ft, frh, n, C->partials, omega, S2, S, K.fcoef + 2 * slot, s);
+                              : launch_apply_dot<R, R>(gA, fsh, ft, fs, kBicgOmega, C->partials, S1, S2, s, one_rhs(),
+                                                       C->fold);
+    beta = launch_bicg_r<R>(fr, fs, ft, frh, n, C->partials, omega, S2, S, K.fcoef + 2 * slot, s, C->fold);
     if (slot == K.fdefer - 1 || it == iters - 1) launch_bicg_xdefer<R>(x, ph0, sh0, K.ld, slot + 1, K.fcoef, n, s);
   }
   // the last step's flag is read with the next run's start or the solve's end
@@ -1744,7 +1747,8 @@ BicgFold bicg_open_step(ecs_ctx *C, const KrylovBufs &K) {
   }
   if (fa) return up_apply_dot<double>(C, av, S, S + kMaxRhs, s);
   TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
-  return launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S + kMaxRhs, s);
+  return launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S + kMaxRhs, s, one_rhs(),
+                                      C->fold);
 }
 
 template <typename RZ>
@@ -1770,7 +1774,8 @@ void bicg_close_step(ecs_ctx *C, const KrylovBufs &K, cplx<double> *x, const Bic
     omega = up_apply_dot<double>(C, at, S1, S2, s);
   } else {
     TimedScope ts(C, kTApply, (double)n * (2 * sizeof(RZ) + 40));
-    omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s);
+    omega = launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s, one_rhs(),
+                                         C->fold);
   }
   launch_bicg_xr<double, RZ>(x, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s, one_rhs(), C->report);
 }
@@ -1959,7 +1964,7 @@ void batch_step(ecs_ctx *C, const KrylovBufs &K, const RhsSet &rs) {
   }
   const BicgFold alpha =
       fa ? up_apply_dot<double>(C, av, S, S1, s, rs)
-         : launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S1, s, rs);
+         : launch_apply_dot<double, RZ>(grid_A(C), ph, K.v, K.rh, kBicgAlpha, C->partials, S, S1, s, rs, C->fold);
   if (fuse) {
     if constexpr (sizeof(RZ) == 8) {
       const CycleBufs<double> B = batch_bufs<double>(C, K);
@@ -1972,7 +1977,7 @@ void batch_step(ecs_ctx *C, const KrylovBufs &K, const RhsSet &rs) {
   }
   const BicgFold omega =
       fa ? up_apply_dot<double>(C, at, S1, S2, s, rs)
-         : launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s, rs);
+         : launch_apply_dot<double, RZ>(grid_A(C), sh, K.tt, K.s, kBicgOmega, C->partials, S1, S2, s, rs, C->fold);
   launch_bicg_xr<double, RZ>(K.bx, ph, sh, K.r, K.s, K.tt, K.rh, n, C->partials, omega, S2, S, s, rs);
 }
 
@@ -2917,6 +2922,15 @@ ecs_status ecs_set_tuning(ecs_ctx *C, const ecs_tuning *t) {
 ecs_status ecs_get_tuning(ecs_ctx *C, ecs_tuning *t) {
   if (!C || !t) return ECS_EINVAL;
   *t = C->tune;
+  return ECS_OK;
+}
+
+// For the tests, in no header: up to `partials` entries of a dot product are summed
+// by the kernel that follows it instead of a reduction of its own (0: none, at
+// most and by default kFoldPartials).  The bits are the same either way.
+ecs_status ecs_test_fold_limit(ecs_ctx *C, int partials) {
+  if (!C || partials < 0 || partials > kFoldPartials) return ECS_EINVAL;
+  C->fold = partials;
   return ECS_OK;
 }
 

@@ -1021,11 +1021,11 @@ void launch_bicg_xr(cplx<R> *x, const cplx<RZ> *ph, const cplx<RZ> *sh, cplx<R> 
 template <typename R>
 BicgFold launch_bicg_r(cplx<R> *r, const cplx<R> *sv, const cplx<R> *t, const cplx<R> *rh, int64_t n,
                        cplx<double> *partials, const BicgFold &f, BicgScalars *S2, BicgScalars *S,
-                       cplx<double> *coef, hipStream_t s) {
+                       cplx<double> *coef, hipStream_t s, int limit) {
   const int nb = red_blocks(n);
   cplx<double> *last = partials + kLastPartials;
   launch_k((k_bicg_r<R>), dim3(nb), dim3(BS), 0, s, r, sv, t, rh, n, f, last, coef);
-  return bicg_fold_or_final(last, nb, 2, S2, S, (int)kBicgNormRho, s);
+  return bicg_fold_or_final(last, nb, 2, S2, S, (int)kBicgNormRho, s, one_rhs(), limit);
 }
 template <typename R>
 void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_t ld, int count,
@@ -1034,10 +1034,10 @@ void launch_bicg_xdefer(cplx<R> *x, const cplx<R> *ph, const cplx<R> *sh, int64_
 }
 template BicgFold launch_bicg_r<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, const cplx<float> *,
                                        int64_t, cplx<double> *, const BicgFold &, BicgScalars *, BicgScalars *,
-                                       cplx<double> *, hipStream_t);
+                                       cplx<double> *, hipStream_t, int);
 template BicgFold launch_bicg_r<double>(cplx<double> *, const cplx<double> *, const cplx<double> *,
                                         const cplx<double> *, int64_t, cplx<double> *, const BicgFold &,
-                                        BicgScalars *, BicgScalars *, cplx<double> *, hipStream_t);
+                                        BicgScalars *, BicgScalars *, cplx<double> *, hipStream_t, int);
 template void launch_bicg_xdefer<float>(cplx<float> *, const cplx<float> *, const cplx<float> *, int64_t, int,
                                         const cplx<double> *, int64_t, hipStream_t);
 template void launch_bicg_xdefer<double>(cplx<double> *, const cplx<double> *, const cplx<double> *, int64_t, int,

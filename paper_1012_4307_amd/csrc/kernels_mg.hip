@@ -494,7 +494,7 @@ void launch_prolong_to(const Grid<R> &fine, const Grid<R> &coarse, const cplx<R>
 template <typename R, typename RI>
 BicgFold launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const cplx<R> *d0, int mode,
                           cplx<double> *partials, const BicgScalars *in, BicgScalars *out, hipStream_t s,
-                          const RhsSet &rs) {
+                          const RhsSet &rs, int limit) {
   // one block per 64 x 4 tile while the partials (two per block) fit the
   // reduction buffer (kRedBlocks x (kMaxRestart + 2) entries); batched
   // launches (2D only) give every right-hand side kRhsPartials of them
@@ -514,12 +514,12 @@ BicgFold launch_apply_dot(const Grid<R> &g, const cplx<RI> *x, cplx<R> *y, const
                rs);
     else
       launch_k((k_apply2d<R, RI, R, kBicgOmega, sy>), grid, dim3(256), 0, s, g, x, y, d0, partials, tx, tiles, rs);
-    return bicg_fold_or_final(partials, nb, mode == kBicgAlpha ? 1 : 2, in, out, mode, s, rs);
+    return bicg_fold_or_final(partials, nb, mode == kBicgAlpha ? 1 : 2, in, out, mode, s, rs, limit);
   }
   const int ntiles = ((g.n0 + TX - 1) / TX) * ((g.n1 + TY - 1) / TY) * g.n2;
   const int nb = ntiles < kRedBlocks ? ntiles : kRedBlocks;
   launch_k((k_apply_dot<R, RI>), dim3(nb), dim3(256), 0, s, g, x, y, d0, mode, partials);
-  return bicg_fold_or_final(partials, nb, mode == kBicgAlpha ? 1 : 2, in, out, mode, s);
+  return bicg_fold_or_final(partials, nb, mode == kBicgAlpha ? 1 : 2, in, out, mode, s, rs, limit);
 }
 
 template <typename R>
@@ -549,7 +549,7 @@ ECS_INST_MG(float)
 #define ECS_INST_APPLY_DOT(R, RI)                                                                              \
   template BicgFold launch_apply_dot<R, RI>(const Grid<R> &, const cplx<RI> *, cplx<R> *, const cplx<R> *, int, \
                                             cplx<double> *, const BicgScalars *, BicgScalars *, hipStream_t,    \
-                                            const RhsSet &);
+                                            const RhsSet &, int);
 ECS_INST_APPLY_DOT(double, double)
 ECS_INST_APPLY_DOT(double, float)
 ECS_INST_APPLY_DOT(float, float)

@@ -656,3 +656,37 @@ def test_scalar_folds_by_size(n, coarsest, dim, inner):
     x, st = S.solve(to_gpu(w.rhs[0]), krylov=kr)
     assert st["status"] == 0 and st["inner_breakdowns"] == 0, st
     assert oracle_resid(P, to_np(x), w.rhs[0]) <= 1.05e-8
+
+
+@pytest.mark.parametrize("n,coarsest,dim,inner", [(33, 5, 2, 0), (193, 7, 2, 0), (513, 5, 2, 0), (1025, 5, 2, 0),
+                                                  (33, 5, 3, 0), (65, 5, 3, 0), (865, 28, 2, 4), (897, 8, 2, 4),
+                                                  (1153, 10, 2, 4), (1217, 20, 2, 4)])
+def test_folded_sums_have_the_bits_of_the_reduction(n, coarsest, dim, inner):
+    """Four steps with the dot products summed by the kernels that follow them and by
+    one-block reductions of their own: equal bits, alone (the p and s updates inside
+    the cycle and separate), nested, and for three right-hand sides together, on
+    both sides of the sizes at which the folds end (768 partials)."""
+    import torch
+    if dim == 3:
+        w = W.cube_constant_k(n=n, k=6.0, coarsest=coarsest)
+    else:
+        w = W.coulomb(E=2.0, n=n, coarsest=coarsest)
+    kr = E.Krylov(method="fgmres" if inner else "bicgstab", restart=8, rtol=1e-30, maxit=4, inner=inner)
+    S = gpu_for(w, "f32" if inner else "f64", krylov=kr)
+    rng = np.random.default_rng(n)
+    b = to_gpu(W.random_complex(w.shape, rng))
+    B = torch.stack([b, to_gpu(W.random_complex(w.shape, rng)), to_gpu(w.rhs[0])])
+    for fuse in (0, 1):
+        S.set_tuning(fuse_updates=fuse)
+        out = []
+        for limit in (768, 0, 100):
+            assert E.lib().ecs_test_fold_limit(S._h, limit) == 0
+            x, st = S.solve(b, krylov=kr)
+            assert st["iterations"] == 4 and st["inner_breakdowns"] == 0, st
+            xs = [x.clone()] + ([] if inner else [E.batch_solve([S], [B], kr)[0][0].clone()])
+            torch.cuda.synchronize()
+            out.append(xs)
+        for other in out[1:]:
+            for x, y in zip(out[0], other):
+                assert torch.equal(x, y), (fuse, relerr(to_np(x), to_np(y)))
+    assert E.lib().ecs_test_fold_limit(S._h, 769) == -1 and E.lib().ecs_test_fold_limit(S._h, -1) == -1
