@@ -73,3 +73,29 @@ def test_option_names_are_checked():
     with pytest.raises(ValueError, match="preconditioner kind"):
         E.Precond(kind="ilu").to_c()
     assert E.Krylov().to_c().orth == E.ORTH["dcgs2"] == 0
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_schedule_candidates_are_different_schedules(dt):
+    """The tuner times no schedule twice (FP32 tiles of 4 coarse rows run as 8, of 8
+    fine rows as 16), and only fine heights with the matvec inside the cycle."""
+    from paper_1012_4307_amd import autotune
+    cands = list(autotune.candidates(dt))
+    runs = {(8 if dt == "f32" and c["down_rows"] == 4 else c["down_rows"],
+             16 if dt == "f32" and c["up_rows"] == 8 else c["up_rows"],
+             c["small_grid"], c["tail_nodes"], c["pair_grid"]) for c in cands}
+    assert len(runs) == len(cands)
+    assert {r[1] for r in runs} == ({4, 16} if dt == "f32" else {4, 8})
+    assert autotune.DEFAULT in cands
+
+
+def test_cached_schedules_belong_to_the_kernels(monkeypatch):
+    """A schedule cached under another generation of the kernels is not taken."""
+    import types
+    from paper_1012_4307_amd import autotune
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: types.SimpleNamespace(gcnArchName="gfx950:x"))
+    s = types.SimpleNamespace(device=None, dim=2, n=(257, 257), precond=types.SimpleNamespace(vcycle_dtype="f64"))
+    key = autotune._key(s)
+    assert key != "gfx950|2d|257x257|f64"
+    monkeypatch.setattr(autotune, "KERNELS", autotune.KERNELS + 1)
+    assert autotune._key(s) != key
