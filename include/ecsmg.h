@@ -133,7 +133,9 @@ typedef struct {
 typedef struct {
   int iterations;          /* outer Krylov iterations                         */
   int restarts;            /* restart cycles (GMRES) / true-residual restarts */
-  int64_t vcycles;         /* preconditioner applications (multigrid cycles)  */
+  int64_t vcycles;         /* preconditioner applications (multigrid cycles);
+                              without the one of a next step's opening that a
+                              driver enqueued ahead and a stop discarded      */
   int64_t inner_iterations;/* inner Bi-CGSTAB iterations (nested form)       */
   double rel_residual;     /* true ||b - A x|| / ||b|| at exit (FP64)         */
   double seconds;          /* host wall time inside the call                  */
@@ -305,6 +307,18 @@ ecs_status ecs_level_info(ecs_ctx *ctx, int level, int *nlevels, int64_t *nodes)
  *     (classes 10 and 11 run instead of 7 in the nested FP32 Bi-CGSTAB, and
  *     in the outer Bi-CGSTAB with the FP64 cycle up to 1025^2 finest nodes,
  *     when ecs_tuning.fuse_updates applies)
+ * Classes 0, 5 and 6 are the launches of general cycles; the fused cycles (2D and
+ * 3D V(1,1) red-black, 2D omega-Jacobi with nu1 = nu2 = 1) report theirs as 7 and
+ * 8.  What a timed solve runs differs from an untimed one:
+ *   - the matvec inside a cycle's last kernel (ecs_solve, ecs_batch_solve) counts
+ *     in class 8, its dot products and output included; while class 2 is enabled
+ *     an outer method's matvec is a launch of its own instead, so times of class 2
+ *     and class 8 do not add up to those of an untimed solve;
+ *   - with any class enabled the Krylov drivers do not enqueue the next step's
+ *     opening ahead of the host's wait; with one of a cycle's, cycles are not
+ *     launched as graphs.
+ * The separate matvec sums its dot products in another order: enabling class 2 can
+ * change a solution by rounding, and with it the iteration count.
  * A timed duration runs from the dispatch of the kernel to its completion.
  * ecs_timing_read synchronises the stream and returns the number of timed
  * launches, their summed duration in ms and their summed algorithmic bytes
@@ -346,9 +360,9 @@ ecs_status ecs_timing_calibrate(ecs_ctx *ctx, int launches);
  *               run two per kernel (pairs counted from the tail up); 0: none
  *   fuse_updates  1: the FP32 Bi-CGSTAB inside FGMRES (desc->inner > 0), and
  *               the Bi-CGSTAB solve (single and batched) with the FP64 cycle
- *               on grids of at most 1025^2 nodes, form their p and s updates inside the finest
- *               level's down kernel when that level has its own down kernel
- *               and the cycle is not launched as a graph
+ *               on grids of at most 1025^2 nodes, form their p and s updates
+ *               inside the finest level's down kernel when that level has its
+ *               own down kernel and the cycle is not launched as a graph
  *               (ECS_GRAPHS_ALWAYS), with the same values as the separate
  *               update kernels; 0: separate update kernels
  * Defaults {4, 8, 513, 33, 129, 1}; a project autotuner picks the tile
