@@ -39,7 +39,8 @@ __device__ __forceinline__ cplx<R> zj() {
 // same at all nodes, acts like an error of k^2 and is not averaged away.  FP32
 // cycles of 129^2 to 641^2 against the 64-bit one: 1.1 to 1.2 times the error of the
 // general kernels (which correct by the quotient of the residual) with an FP32
-// diagonal, 0.4 to 0.9 times so, the kernels' times unchanged within 0.2 us.
+// diagonal, 0.4 to 0.9 times so.  A kernel takes up to 0.2 us more, an FP32 cycle 2
+// to 4% (F_1^3 on 641^2 137.5 -> 143.2 us).
 template <typename R>
 __device__ __forceinline__ cplx<double> diag_j(cplx<R> xm, cplx<R> xp, cplx<R> ym, cplx<R> yp, R k2, cplx<R> beta,
                                                cplx<R> c) {
